@@ -37,7 +37,7 @@ __device__ __forceinline__ Q4 qfma(float s, Q4 a, Q4 b) {   // s a + b, fused pe
 // gh + dt dbar (right end) and gl - dt dbar (left end).
 __device__ __forceinline__ V3 impulse_adjoint(V3 d, float ci, float cil, float wl, float wh, V3 gl,
                                               V3 gh) {
-  const float il = rsqrtf(fmaxf(dot(d, d), 1e-30f));
+  const float il = rsq(fmaxf(dot(d, d), 1e-30f));
   const float s = ci - cil * il;
   const V3 Db = fnma3(wh, gh, wl * gl);     // Delta = s d; v_hi -= w_hi Delta; v_lo += w_lo Delta
   const float sb = dot(Db, d);
@@ -52,7 +52,7 @@ __global__ __launch_bounds__(64 * W) void rod_adjoint_kernel(
     float* __restrict__ ax, float* __restrict__ av, float* __restrict__ aq, float* __restrict__ aw,
     double* __restrict__ gacc, const float* __restrict__ fext, const float* __restrict__ text,
     int* __restrict__ status) {
-  __shared__ Mailbox<W, kMergedExchange<W, E>> mb;
+  __shared__ Mailbox<W> mb;
   mailbox_init(mb);
   const int rod = rod_ids[blockIdx.x];
   const RodDev rd = rods[rod];
@@ -60,7 +60,6 @@ __global__ __launch_bounds__(64 * W) void rod_adjoint_kernel(
   L.load_params(rd, prm, prm_stride);
   const int g = L.g, j0 = L.j0;
   const float dt = L.dt;
-  int par = 0;
 
   // coefficients without the stiffness multipliers, and the right-neighbour inverse mass
   float C1b[E], C3b[E], D0b[E], D1b[E], D2b[E], WN[E];
@@ -158,7 +157,7 @@ __global__ __launch_bounds__(64 * W) void rod_adjoint_kernel(
     // ---- recompute the forward step, keeping what the reverse needs
     V3 xl, xll;
     Q4 qn, qnl;
-    L.exchange_a(mb, par, xl, xll, qn, qnl);
+    L.exchange_a(mb, xl, xll, qn, qnl);
     V3 Om0[E];
     Q4 Q0[E], Q0L[E];
 #pragma unroll
@@ -169,14 +168,15 @@ __global__ __launch_bounds__(64 * W) void rod_adjoint_kernel(
     }
     {
       V3 F[E], T[E], Ev[E], fs0, enext;
-      L.forces(mb, par, xl, xll, qn, qnl, F, T, Ev, fs0, enext);
+      L.forces(mb, xl, xll, qn, qnl, F, T, Ev, fs0, enext);
       L.integrate_forces(rd, F, T, fs0, xc, wc, fext, text);
       V3 ds[kAdjointMaxIter][2][E];
 #pragma unroll
       for (int it = 0; it < kAdjointMaxIter; ++it) {
         if (it < rd.n_iter) {
-          L.half_sweep(rd, mb, par, 0, Ev, enext, ds[it][0]);
-          L.half_sweep(rd, mb, par, 1, Ev, enext, ds[it][1]);
+          if (it % 2 == 0) L.template half_sweep<0, true, false>(mb, Ev, enext, ds[it][0]);
+          else L.template half_sweep<0, true, true>(mb, Ev, enext, ds[it][0]);
+          L.template half_sweep<1, true, false>(mb, Ev, enext, ds[it][1]);
         }
       }
       // L.Om = omega' (after force integration), L.Vv = v'' (after the impulses)
@@ -196,7 +196,7 @@ __global__ __launch_bounds__(64 * W) void rod_adjoint_kernel(
                       q.x + hdt * (q.w * o.x + q.y * o.z - q.z * o.y),
                       q.y + hdt * (q.w * o.y - q.x * o.z + q.z * o.x),
                       q.z + hdt * (q.w * o.z + q.x * o.y - q.y * o.x)};
-        const float ip = rsqrtf(q_dot(p, p));
+        const float ip = rsq(q_dot(p, p));
         const Q4 qo = q_scale(ip, p);
         Q4 pb = q_scale(ip, qfma(-q_dot(qo, AQ[e]), qo, AQ[e]));
         if (clamp0 && e == 0) pb = {0.f, 0.f, 0.f, 0.f};   // q'_0 = q_c
@@ -225,17 +225,18 @@ __global__ __launch_bounds__(64 * W) void rod_adjoint_kernel(
         if (it < rd.n_iter) {
 #pragma unroll
           for (int h = 1; h >= 0; --h) {
-            const bool cross_lanes = (E % 2 == 1) || (h == 0);
             V3 glo = {0.f, 0.f, 0.f}, ghi = {0.f, 0.f, 0.f};
-            if (cross_lanes) {
+            if (h == 0) {
               float mh[3] = {AVc[E - 1].x, AVc[E - 1].y, AVc[E - 1].z};
               float ml[3] = {AVc[0].x, AVc[0].y, AVc[0].z};
               const float base[3] = {abvc.x, abvc.y, abvc.z};
               float lo[3], hi[3];
-              exchange<W, E, 3, 3, true, kMergedExchange<W, E>>(mh, lo, ml, hi, base, mb, par);
+              // (not the section of this iteration's forward sweep, which came just before the
+              // last iteration's reverse)
+              if (it % 2 == 0) exchange<W, kSecVelOdd, 3, 3, true>(mh, lo, ml, hi, base, mb, L.wave);
+              else exchange<W, kSecVel, 3, 3, true>(mh, lo, ml, hi, base, mb, L.wave);
               glo = {lo[0], lo[1], lo[2]};
               ghi = {hi[0], hi[1], hi[2]};
-              if (!kMergedExchange<W, E> && g == 0) glo = abvc;
             }
             V3 nv[E];
             V3 dbase = {0.f, 0.f, 0.f};
@@ -260,33 +261,33 @@ __global__ __launch_bounds__(64 * W) void rod_adjoint_kernel(
                 dbase = db0;
 #pragma unroll
                 for (int a = 1; a + 1 < E; a += 2) pair(a);
-                const V3 dbl = impulse_adjoint(ds[it][0][E - 1], L.P[P_CI_NEXT][E - 1],
-                                               L.P[P_CIL_NEXT][E - 1], L.P[P_WINV][E - 1], WN[E - 1],
-                                               AVc[E - 1], ghi);
+                V3 dbl;
+                if constexpr (W == 1)   // the next lane's first segment (as in the forward sweep)
+                  dbl = {from_upper_lane(db0.x), from_upper_lane(db0.y), from_upper_lane(db0.z)};
+                else
+                  dbl = impulse_adjoint(ds[it][0][E - 1], L.P[P_CI_NEXT][E - 1],
+                                        L.P[P_CIL_NEXT][E - 1], L.P[P_WINV][E - 1], WN[E - 1],
+                                        AVc[E - 1], ghi);
                 nv[E - 1] = fnma3(dt, dbl, AVc[E - 1]);
               } else {
 #pragma unroll
                 for (int a = 0; a < E; a += 2) pair(a);
               }
             } else {
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-              const int j = j0 + e;
-              const bool is_hi = ((j & 1) == h);
-              const float w_me = L.P[P_WINV][e];
-              const V3 g_lo = (e == 0) ? glo : AVc[e - 1];
-              const V3 g_hi = (e == E - 1) ? ghi : AVc[e + 1];
-              const V3 d = ds[it][h][e];
-              // as right end of segment j
-              const V3 db_h = impulse_adjoint(d, L.P[P_CI][e], L.P[P_CIL][e], L.P[P_WINV_PREV][e],
-                                              w_me, g_lo, AVc[e]);
-              // as left end of segment j+1
-              const V3 db_l = impulse_adjoint(d, L.P[P_CI_NEXT][e], L.P[P_CIL_NEXT][e], w_me,
-                                              WN[e], AVc[e], g_hi);
-              nv[e] = sel(is_hi, fma3(dt, db_h, AVc[e]), fnma3(dt, db_l, AVc[e]));
-              EB[e] = sel(is_hi, EB[e] + db_h, EB[e]);
-              if (e == 0) dbase = db_h;
-            }
+              // one slot per lane: the segment it was an end of in this half-sweep (see
+              // RodLane::half_sweep)
+              const bool is_hi = ((j0 & 1) == h);
+              const V3 go = h == 0 ? sel(is_hi, glo, ghi)
+                                   : V3{from_pair_lane(AVc[0].x), from_pair_lane(AVc[0].y),
+                                        from_pair_lane(AVc[0].z)};
+              const float w_me = L.P[P_WINV][0];
+              const V3 db = impulse_adjoint(
+                  ds[it][h][0], is_hi ? L.P[P_CI][0] : L.P[P_CI_NEXT][0],
+                  is_hi ? L.P[P_CIL][0] : L.P[P_CIL_NEXT][0], is_hi ? L.P[P_WINV_PREV][0] : w_me,
+                  is_hi ? w_me : WN[0], sel(is_hi, go, AVc[0]), sel(is_hi, AVc[0], go));
+              nv[0] = fma3(is_hi ? dt : -dt, db, AVc[0]);
+              EB[0] = sel(is_hi, EB[0] + db, EB[0]);
+              dbase = db;
             }
 #pragma unroll
             for (int e = 0; e < E; ++e) AVc[e] = nv[e];
@@ -329,10 +330,9 @@ __global__ __launch_bounds__(64 * W) void rod_adjoint_kernel(
         float ml[3] = {TB[0].x, TB[0].y, TB[0].z};
         const float base[3] = {fb0.x, fb0.y, fb0.z};
         float lo[3], hi[3];
-        exchange<W, E, 3, 3, true, kMergedExchange<W, E>>(mh, lo, ml, hi, base, mb, par);
+        exchange<W, kSecVel, 3, 3, true>(mh, lo, ml, hi, base, mb, L.wave);   // (the last was odd's)
         fb_lo = {lo[0], lo[1], lo[2]};
         tb_hi = {hi[0], hi[1], hi[2]};
-        if (!kMergedExchange<W, E> && g == 0) fb_lo = fb0;
       }
       V3 dneg_first = {0.f, 0.f, 0.f};
       Q4 qb_last = {0.f, 0.f, 0.f, 0.f};
@@ -341,7 +341,7 @@ __global__ __launch_bounds__(64 * W) void rod_adjoint_kernel(
       for (int e = 0; e < E; ++e) {
         const V3 d = Ev[e];                                   // the forward's segment vector
         const float len2 = dot(d, d);
-        const float il = rsqrtf(len2);
+        const float il = rsq(len2);
         const V3 t = il * d;
         const float len = len2 * il;
         const Q4 q = Q0[e];
@@ -419,7 +419,7 @@ __global__ __launch_bounds__(64 * W) void rod_adjoint_kernel(
         float ml[3] = {dneg_first.x, dneg_first.y, dneg_first.z};
         const float base[4] = {0.f, 0.f, 0.f, 0.f};   // frame 0 has no joint below
         float lo[4], hi[3];
-        exchange<W, E, 4, 3, false, kMergedExchange<W, E>>(mh, lo, ml, hi, base, mb, par);
+        exchange<W, kSecForce, 4, 3, false>(mh, lo, ml, hi, base, mb, L.wave);
         // joint j-1's adjoint for frame j (from below); segment j+1's -d for point j+1 (above)
         const Q4 qfrom = {lo[0], lo[1], lo[2], lo[3]};
         const V3 dfrom = {hi[0], hi[1], hi[2]};

@@ -25,6 +25,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace corde {
 
 // Per-slot coefficient rows (FP32, derived in FP64 on the host), stored row-major:
@@ -123,6 +125,7 @@ struct RodDev {
 constexpr int kFeatHaptic = 1;
 constexpr int kFeatEnv = 2;
 constexpr int kFeatDamp = 4;   // internal friction
+constexpr int kFeatTrace = 8;  // per-step states and tip positions recorded (the adjoint's forward)
 
 struct V3 {
   float x, y, z;
@@ -153,6 +156,11 @@ __device__ __forceinline__ Q4 sel4(bool c, Q4 a, Q4 b) {
   return {c ? a.w : b.w, c ? a.x : b.x, c ? a.y : b.y, c ? a.z : b.z};
 }
 
+// 1 / sqrt(x) for normal x, the instruction itself (rsqrtf adds five instructions that rescale
+// denormal arguments and returns the same bits elsewhere; used where a denormal argument means a
+// segment below 1e-19 m or a vanished quaternion).
+__device__ __forceinline__ float rsq(float x) { return __builtin_amdgcn_rsqf(x); }
+
 // DPP whole-wavefront shifts.  from_lower_lane / from_upper_lane: the lane without a source
 // (lane 0 / lane 63) receives 0 (bound_ctrl).  The `_or` forms leave that lane's destination
 // unwritten, so it keeps `edge`: one instruction moves the neighbour's value and merges what the
@@ -162,6 +170,9 @@ __device__ __forceinline__ float from_lower_lane(float v) {  // lane i <- lane i
 }
 __device__ __forceinline__ float from_upper_lane(float v) {  // lane i <- lane i+1
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x130, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float from_pair_lane(float v) {   // lanes 2 i and 2 i + 1 swap
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xb1, 0xf, 0xf, true));
 }
 __device__ __forceinline__ float from_lower_lane_or(float edge, float v) {  // lane i <- lane i-1
   return __int_as_float(
@@ -175,134 +186,93 @@ __device__ __forceinline__ float from_upper_lane_or(float edge, float v) {  // l
 // Neighbour exchange across the rod's lanes.  `lo` receives the KL values `mine_hi` of the
 // lane below (its last slot), `hi` receives the KH values `mine_lo` of the lane above (its
 // first slot).  The rod's last lane receives 0.  Its first lane (g = 0) receives `base` (B:
-// values that stand for what lies below the rod, such as its base point) in the merged form;
-// otherwise 0, and the caller substitutes (the substitution inside the plain form kept a lane
-// mask live across the step loop, which spilled scalar registers).  E (the elements per lane)
-// only sets how much register room the reads may use.
-constexpr int kMailboxWords = 11;  // the widest exchange: quaternion (two parts), angular velocity
-// buf: what each wavefront's edge lanes publish ([0]: lane 0's, [1]: lane 63's), per parity.
-// edge (merged form, M): [1] is what lane 0 of wavefront 0 reads from below (written by that
-// lane at every exchange: the base values, or zeros), [0] what the last wavefront's lane 63
-// reads from above (zero, set once by mailbox_init and never written).
-template <int W, bool M = false>
-struct Mailbox {
-  float buf[2][W][2][kMailboxWords];
-  float edge[2][2][kMailboxWords];
+// values that stand for what lies below the rod, such as its base point), otherwise 0.
+//
+// Between wavefronts the words travel through LDS: row[w + 1][0] holds what wavefront w's lane 0
+// publishes and row[w + 1][1] what its lane 63 does.  The row below the first wavefront holds
+// the base words (zero where there are none), the one above the last stays zero (mailbox_init).
+// A row has one section per kind of exchange.  Words written for one exchange may be rewritten
+// for any but the next one: the barrier of the exchange between them comes after every read of
+// them.  So each section is written once per step, except for the constraint iterations', which
+// follow each other directly and alternate between two; no parity has to be kept, and every
+// LDS address is a constant offset from the wavefront's rows.
+enum MailboxSection : int {
+  kSecState = 0,    // exchange A: at most 11 words (quaternion in two parts, angular velocity)
+  kSecForce = 12,   // exchange B and the adjoint's last: at most 6 words
+  kSecVel = 20,     // the even constraint iterations' velocities: 3 words
+  kSecVelOdd = 24,  // the odd ones'
+  kSecRow = 28      // floats per row (sections start at 16-byte addresses)
+};
+template <int W>
+struct alignas(16) Mailbox {
+  float row[W + 2][2][kSecRow];
 };
 
-// Two forms of the exchange move the same values (the states are bitwise the same).  The
-// merged form (M) reads the mailbox words into the DPP moves' kept operand (one instruction per
-// word, the base values travelling through the mailbox); the plain form moves before the
-// barrier and selects the mailbox words into the edge lanes afterwards.  Measured (device time
-// per step, 2 rods and 2048 rods per launch, every shape): the merged form is faster for four
-// wavefronts of 2 or 4 elements per lane, one per SIMD, and slower for every other shape, for
-// two rods of four wavefronts in one workgroup (two wavefronts per SIMD), and in the chunked
-// long-rod kernel's extensible steps (two exchanges per step); those use the plain form.
-template <int W, int E>
-constexpr bool kMergedExchange = (W == 4) && (E == 2 || E == 4);
-
-// Zeroes the words above the last wavefront (merged form only); must run before the kernel's
-// first exchange (whose barrier orders it before the reads).  It touches no word that an
-// exchange writes.
-template <int W, bool M>
-__device__ __forceinline__ void mailbox_init(Mailbox<W, M>& mb) {
-  if constexpr (M) {
-    if (threadIdx.x < kMailboxWords) {
-      mb.edge[0][0][threadIdx.x] = 0.f;
-      mb.edge[1][0][threadIdx.x] = 0.f;
+// Zeroes the rows below the first and above the last wavefront.  Exchanges write into them only
+// the base words, from the thread that holds them.  Must be reached by the whole workgroup.
+template <int W>
+__device__ __forceinline__ void mailbox_init(Mailbox<W>& mb) {
+  if constexpr (W > 1) {
+    const int t = threadIdx.x & (64 * W - 1);
+    if (t < kSecRow) {
+      mb.row[0][1][t] = 0.f;
+      mb.row[W + 1][0][t] = 0.f;
     }
+    __syncthreads();
   }
 }
 
-template <int W, int E, int KL, int KH, bool B, bool M>
+// The wavefront's number within the rod's W, as a scalar.
+template <int W>
+__device__ __forceinline__ int wave_of_rod() {
+  return __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & (W - 1));
+}
+
+// Lane masks of a wavefront's first, last and both edge lanes.
+__device__ __forceinline__ bool first_lane() { return __builtin_amdgcn_inverse_ballot_w64(1ull); }
+__device__ __forceinline__ bool last_lane() {
+  return __builtin_amdgcn_inverse_ballot_w64(0x8000000000000000ull);
+}
+__device__ __forceinline__ bool edge_lane() {
+  return __builtin_amdgcn_inverse_ballot_w64(0x8000000000000001ull);
+}
+
+template <int W, int S, int KL, int KH, bool B>
 __device__ __forceinline__ void exchange(const float (&mine_hi)[KL], float (&lo)[KL],
                                          const float (&mine_lo)[KH], float (&hi)[KH],
-                                         const float (&base)[KL], Mailbox<W, M>& mb, int& parity) {
-  static_assert(KL <= kMailboxWords && KH <= kMailboxWords, "exchange wider than the mailbox");
-  const int lane = threadIdx.x & 63;
+                                         const float (&base)[KL], Mailbox<W>& mb, int wave) {
+  static_assert(S + KL <= kSecRow && S + KH <= kSecRow, "exchange wider than its section");
   if constexpr (W == 1) {
 #pragma unroll
-    for (int k = 0; k < KL; ++k) lo[k] = from_lower_lane(mine_hi[k]);
+    for (int k = 0; k < KL; ++k) {
+      lo[k] = from_lower_lane(mine_hi[k]);
+      if (B) lo[k] = first_lane() ? base[k] : lo[k];
+    }
 #pragma unroll
     for (int k = 0; k < KH; ++k) hi[k] = from_upper_lane(mine_lo[k]);
-  } else if constexpr (M) {
-    const int wave = (threadIdx.x >> 6) & (W - 1);   // wavefront within the rod's W
-    if (lane == 63) {
+  } else {
+    // rows of the wavefronts below ([.][1] at R), own (2 R, 3 R) and above ([.][0] at 4 R)
+    constexpr int R = kSecRow;
+    float* const at = mb.row[wave][0] + S;
+    if (last_lane()) {
 #pragma unroll
-      for (int k = 0; k < KL; ++k) mb.buf[parity][wave][1][k] = mine_hi[k];
+      for (int k = 0; k < KL; ++k) at[3 * R + k] = mine_hi[k];
     }
-    if (lane == 0) {
+    if (first_lane()) {
 #pragma unroll
-      for (int k = 0; k < KH; ++k) mb.buf[parity][wave][0][k] = mine_lo[k];
-      if (wave == 0) {   // (zeros without B: faster on c1 than reading the zero words)
+      for (int k = 0; k < KH; ++k) at[2 * R + k] = mine_lo[k];
+      if (B && wave == 0) {
 #pragma unroll
-        for (int k = 0; k < KL; ++k) mb.edge[parity][1][k] = B ? base[k] : 0.f;
+        for (int k = 0; k < KL; ++k) at[R + k] = base[k];
       }
     }
     __syncthreads();
     // every lane reads the same (broadcast) words; the DPP move keeps them only in the
     // wavefront's edge lane, which has no source inside the wavefront
-    const float* from_lo = wave > 0 ? mb.buf[parity][wave - 1][1] : mb.edge[parity][1];
-    const float* from_hi = wave < W - 1 ? mb.buf[parity][wave + 1][0] : mb.edge[parity][0];
 #pragma unroll
-    for (int k = 0; k < KL; ++k) lo[k] = from_lower_lane_or(from_lo[k], mine_hi[k]);
+    for (int k = 0; k < KL; ++k) lo[k] = from_lower_lane_or(at[R + k], mine_hi[k]);
 #pragma unroll
-    for (int k = 0; k < KH; ++k) hi[k] = from_upper_lane_or(from_hi[k], mine_lo[k]);
-    parity ^= 1;
-  } else {
-    static_assert((W & (W - 1)) == 0, "W must be a power of two");
-#pragma unroll
-    for (int k = 0; k < KL; ++k) lo[k] = from_lower_lane(mine_hi[k]);
-#pragma unroll
-    for (int k = 0; k < KH; ++k) hi[k] = from_upper_lane(mine_lo[k]);
-    const int wave = (threadIdx.x >> 6) & (W - 1);   // wavefront within the rod's W
-    if (lane == 63) {
-#pragma unroll
-      for (int k = 0; k < KL; ++k) mb.buf[parity][wave][1][k] = mine_hi[k];
-    }
-    if (lane == 0) {
-#pragma unroll
-      for (int k = 0; k < KH; ++k) mb.buf[parity][wave][0][k] = mine_lo[k];
-    }
-    __syncthreads();
-    // every lane reads the same (broadcast) words and only the wave's edge lanes keep them.
-    // Where registers allow, an empty asm consumes the loaded values so the loads stay
-    // unconditional (a load moved under the lane test becomes an exec-mask branch per word);
-    // 8 waves x 4 elements (256 registers) and 16 waves (128) would spill with all words live.
-    constexpr bool kPinLoads = (W <= 4) || (W <= 8 && E <= 2);
-    const int wl = wave > 0 ? wave - 1 : 0;
-    const int wh = wave < W - 1 ? wave + 1 : W - 1;
-    const bool take_lo = (lane == 0) && (wave > 0);
-    const bool take_hi = (lane == 63) && (wave < W - 1);
-    if constexpr (kPinLoads) {
-      float tl[KL], th[KH];
-#pragma unroll
-      for (int k = 0; k < KL; ++k) tl[k] = mb.buf[parity][wl][1][k];
-#pragma unroll
-      for (int k = 0; k < KH; ++k) th[k] = mb.buf[parity][wh][0][k];
-#pragma unroll
-      for (int k = 0; k < KL; ++k) {
-        asm volatile("" : "+v"(tl[k]));
-        lo[k] = take_lo ? tl[k] : lo[k];
-      }
-#pragma unroll
-      for (int k = 0; k < KH; ++k) {
-        asm volatile("" : "+v"(th[k]));
-        hi[k] = take_hi ? th[k] : hi[k];
-      }
-    } else {
-#pragma unroll
-      for (int k = 0; k < KL; ++k) {
-        const float t = mb.buf[parity][wl][1][k];
-        lo[k] = take_lo ? t : lo[k];
-      }
-#pragma unroll
-      for (int k = 0; k < KH; ++k) {
-        const float t = mb.buf[parity][wh][0][k];
-        hi[k] = take_hi ? t : hi[k];
-      }
-    }
-    parity ^= 1;
+    for (int k = 0; k < KH; ++k) hi[k] = from_upper_lane_or(at[4 * R + k], mine_lo[k]);
   }
 }
 
@@ -311,9 +281,10 @@ __device__ __forceinline__ void exchange(const float (&mine_hi)[KL], float (&lo)
 //   d = p_hi - p_lo = e + dt (v_hi - v_lo),  C = |d| - l,  lambda = C / (dt (w_lo + w_hi)),
 //   lambda n = ci (1 - l / |d|) d   with ci = 1 / (dt (w_lo + w_hi)), cil = ci l.
 // Both owners of a segment compute it from identical operands, so both apply the same impulse.
-// A missing segment has ci = cil = 0 and yields 0 (the max keeps the reciprocal finite).
+// A missing segment has ci = cil = 0 and yields 0 (the max keeps the reciprocal finite; adding
+// 1e-30 inside the sum instead saves the instruction, but breaks ties of its rounding).
 __device__ __forceinline__ V3 impulse_d(V3 d, float ci, float cil) {
-  const float il = rsqrtf(fmaxf(dot(d, d), 1e-30f));
+  const float il = rsq(fmaxf(dot(d, d), 1e-30f));
   const float s = ci - cil * il;
   return s * d;
 }
@@ -352,7 +323,7 @@ __device__ __forceinline__ void advance_quat(Q4& h, Q4& l, V3 o, float dt) {
                 hdt * (h.w * o.y - h.x * o.z + h.z * o.x), hdt * (h.w * o.z + h.x * o.y - h.y * o.x)};
   const float n2 = (h.w * h.w + h.x * h.x + h.y * h.y + h.z * h.z) +
                    (d.w * d.w + d.x * d.x + d.y * d.y + d.z * d.z);
-  const float eps = rsqrtf(n2) - 1.f;
+  const float eps = rsq(n2) - 1.f;
   add_pair(h.w, l.w, __builtin_fmaf(eps, h.w, __builtin_fmaf(eps, d.w, d.w)));
   add_pair(h.x, l.x, __builtin_fmaf(eps, h.x, __builtin_fmaf(eps, d.x, d.x)));
   add_pair(h.y, l.y, __builtin_fmaf(eps, h.y, __builtin_fmaf(eps, d.y, d.y)));
@@ -533,9 +504,12 @@ struct RodLane {
   Q4 Qf[E], QL[E];
   float P[P_NROWS][E];
   bool ok[E];
+  float dts[E];    // dt of the slot (0 past the rod's end)
   V3 bx, bxl, bv;
   int g, j0, n;
+  int wave;        // wavefront within the rod's W (scalar)
   int off, nloc;   // window of the rod held by this workgroup: slots [off, off + nloc)
+  bool clamp0;     // this lane holds the rod's clamped frame 0
   bool ghost;      // off > 0: lane 0's "base point" is point `off`, held fixed (a halo edge)
   V3 imp0;         // lane 0: momentum passed to point 0 (forces x dt + impulses)
   V3 en[E];        // environment collision of each slot's point this step: normal, depth
@@ -550,17 +524,20 @@ struct RodLane {
   __device__ __forceinline__ void load_params(const RodDev& rd, const float* __restrict__ prm,
                                               int prm_stride, int win_off = 0, int win_n = -1) {
     g = threadIdx.x & (64 * W - 1);   // lane within the rod's 64 W (a workgroup may hold two)
+    wave = wave_of_rod<W>();
     n = rd.n;
     off = win_off;
     nloc = win_n < 0 ? rd.n : win_n;
     ghost = off > 0;
     j0 = g * E;
     dt = rd.dt;
+    clamp0 = g == 0 && rd.clamp && !ghost;
     const bool cut_right = off + nloc < n;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const int jl = j0 + e;
       ok[e] = jl < nloc;
+      dts[e] = ok[e] ? dt : 0.f;
 #pragma unroll
       for (int r = 0; r < P_NROWS; ++r)
         P[r][e] = ok[e] ? prm[r * prm_stride + rd.slot_off + off + jl] : 0.f;
@@ -583,7 +560,11 @@ struct RodLane {
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const int j = off + j0 + e;
-      X[e] = XL[e] = Vv[e] = Om[e] = {0.f, 0.f, 0.f};
+      // Slots past the rod's end stay where they are put (dts = 0) with all coefficients 0, so
+      // that their forces, torques and impulses come out 0 without a select; they lie far from
+      // any rod and apart from each other, so that their segments have finite lengths.
+      X[e] = {((j0 + e) & 1) ? 1e9f : 2e9f, 0.f, 0.f};
+      XL[e] = Vv[e] = Om[e] = {0.f, 0.f, 0.f};
       Qf[e] = {1.f, 0.f, 0.f, 0.f};
       QL[e] = {0.f, 0.f, 0.f, 0.f};
       if (ok[e]) {
@@ -665,8 +646,8 @@ struct RodLane {
   // Exchange A: the left neighbour point's position (both parts: xl, xll; the base point for
   // lane 0) and the next frame's quaternion (both parts: qn, qnl; from the lane above); with
   // internal friction (D) also that point's velocity vl and that frame's angular velocity wn.
-  template <bool D, bool M>
-  __device__ __forceinline__ void exchange_a(Mailbox<W, M>& mb, int& par, V3& xl, V3& xll, Q4& qn,
+  template <bool D>
+  __device__ __forceinline__ void exchange_a(Mailbox<W>& mb, V3& xl, V3& xll, Q4& qn,
                                              Q4& qnl, V3& vl, V3& wn) const {
     const V3 a = X[E - 1], al = XL[E - 1];
     const Q4 b = Qf[0], bl = QL[0];
@@ -676,15 +657,10 @@ struct RodLane {
       float ml[11] = {b.w, b.x, b.y, b.z, bl.w, bl.x, bl.y, bl.z, o.x, o.y, o.z};
       const float base[9] = {bx.x, bx.y, bx.z, bxl.x, bxl.y, bxl.z, bv.x, bv.y, bv.z};
       float lo[9], hi[11];
-      exchange<W, E, 9, 11, true, M>(mh, lo, ml, hi, base, mb, par);
+      exchange<W, kSecState, 9, 11, true>(mh, lo, ml, hi, base, mb, wave);
       xl = {lo[0], lo[1], lo[2]};
       xll = {lo[3], lo[4], lo[5]};
       vl = {lo[6], lo[7], lo[8]};
-      if (!M && g == 0) {
-        xl = bx;
-        xll = bxl;
-        vl = bv;
-      }
       qn = {hi[0], hi[1], hi[2], hi[3]};
       qnl = {hi[4], hi[5], hi[6], hi[7]};
       wn = {hi[8], hi[9], hi[10]};
@@ -693,24 +669,19 @@ struct RodLane {
       float ml[8] = {b.w, b.x, b.y, b.z, bl.w, bl.x, bl.y, bl.z};
       const float base[6] = {bx.x, bx.y, bx.z, bxl.x, bxl.y, bxl.z};
       float lo[6], hi[8];
-      exchange<W, E, 6, 8, true, M>(mh, lo, ml, hi, base, mb, par);
+      exchange<W, kSecState, 6, 8, true>(mh, lo, ml, hi, base, mb, wave);
       xl = {lo[0], lo[1], lo[2]};
       xll = {lo[3], lo[4], lo[5]};
-      if (!M && g == 0) {
-        xl = bx;
-        xll = bxl;
-      }
       qn = {hi[0], hi[1], hi[2], hi[3]};
       qnl = {hi[4], hi[5], hi[6], hi[7]};
       vl = {0.f, 0.f, 0.f};
       wn = {0.f, 0.f, 0.f};
     }
   }
-  template <bool M>
-  __device__ __forceinline__ void exchange_a(Mailbox<W, M>& mb, int& par, V3& xl, V3& xll, Q4& qn,
+  __device__ __forceinline__ void exchange_a(Mailbox<W>& mb, V3& xl, V3& xll, Q4& qn,
                                              Q4& qnl) const {
     V3 vl, wn;
-    exchange_a<false>(mb, par, xl, xll, qn, qnl, vl, wn);
+    exchange_a<false>(mb, xl, xll, qn, qnl, vl, wn);
   }
 
   // F: segment forces (stretch eq. (2), penalty eq. (8)) and joint torques (eq. (3) with the
@@ -721,8 +692,8 @@ struct RodLane {
   // (len - l) + td d(len)/dt and a joint's moment K (u - uhat + td du/dt), where
   // du/dt = (rw (w_{j+1} - w_j) + rv x (w_{j+1} + w_j)) / lbar for the relative rotation
   // r = conj(q_j) q_{j+1}; vl and wn are the exchanged neighbour velocities.
-  template <bool D = false, bool M = false>
-  __device__ __forceinline__ void forces(Mailbox<W, M>& mb, int& par, V3 xl, V3 xll, Q4 qn, Q4 qnl,
+  template <bool D = false>
+  __device__ __forceinline__ void forces(Mailbox<W>& mb, V3 xl, V3 xll, Q4 qn, Q4 qnl,
                                          V3 (&F)[E],
                                          V3 (&T)[E], V3 (&Ev)[E], V3& fs0, V3& enext,
                                          float td = 0.f, V3 vl = {0.f, 0.f, 0.f},
@@ -738,7 +709,7 @@ struct RodLane {
       const V3 d = (X[e] - xa) + (XL[e] - xal);
       Ev[e] = d;
       const float len2 = dot(d, d);
-      const float il = rsqrtf(len2);
+      const float il = rsq(len2);
       const V3 t = il * d;
       const Q4 q = Qf[e];
       const float ww = q.w * q.w, xx = q.x * q.x, yy = q.y * q.y, zz = q.z * q.z;
@@ -754,7 +725,6 @@ struct RodLane {
       float sd = len - P[P_LEN][e];
       if constexpr (D) sd = fmaf(td, dot(t, Vv[e] - ((e == 0) ? vl : Vv[e - 1])), sd);
       f = fnma3(P[P_KS_L][e] * sd, t, f);                         // stretch, eq. (2)
-      f = sel(ok[e], f, V3{0.f, 0.f, 0.f});                      // force on point j+1
       const V3 tpen = {-lkp * dot(d2, t), lkp * dot(d1, t), 0.f};  // l K_p e_3 x R^T t
       const Q4 qb = (e == E - 1) ? qn : Qf[e + 1];
       const Q4 qbl = (e == E - 1) ? qnl : QL[e + 1];
@@ -778,8 +748,8 @@ struct RodLane {
              fmaf(h * P[P_C3][e], gs.z, m.z)};
       }
       const V3 rxm = cross(rv, m);
-      const V3 tj = sel(ok[e], fma3(rw, m, rxm), V3{0.f, 0.f, 0.f});   // on frame j
-      const V3 tn = sel(ok[e], fnma3(rw, m, rxm), V3{0.f, 0.f, 0.f});  // on frame j+1
+      const V3 tj = fma3(rw, m, rxm);                             // on frame j
+      const V3 tn = fnma3(rw, m, rxm);                            // on frame j+1
       F[e] = f;
       if (e == 0) fs0 = f;
       else F[e - 1] = F[e - 1] - f;                              // reaction on point j
@@ -790,73 +760,63 @@ struct RodLane {
     float ml[6] = {fs0.x, fs0.y, fs0.z, Ev[0].x, Ev[0].y, Ev[0].z};
     const float base[3] = {0.f, 0.f, 0.f};   // no joint below frame 0
     float lo[3], hi[6];
-    exchange<W, E, 3, 6, false, M>(mh, lo, ml, hi, base, mb, par);
+    exchange<W, kSecForce, 3, 6, false>(mh, lo, ml, hi, base, mb, wave);
     T[0] = T[0] + V3{lo[0], lo[1], lo[2]};
     F[E - 1] = F[E - 1] - V3{hi[0], hi[1], hi[2]};
     enext = {hi[3], hi[4], hi[5]};
   }
 
-  // V: integrate forces (points as particles) and torques (frames as rigid bodies).
-  __device__ __forceinline__ void integrate_forces(const RodDev& rd, const V3 (&F)[E],
-                                                   const V3 (&T)[E], V3 fs0, V3 xc, V3 wc,
+  // V: integrate forces (points as particles) and torques (frames as rigid bodies).  What every
+  // step of a clamped rod does is written without branches (a taken one costs some 40 cycles).
+  __device__ __forceinline__ void integrate_forces(const RodDev& rd, V3 (&F)[E], V3 (&T)[E],
+                                                   V3 fs0, V3 xc, V3 wc,
                                                    const float* __restrict__ fext,
                                                    const float* __restrict__ text) {
     const V3 grav = {rd.g[0], rd.g[1], rd.g[2]};
+    V3 Fb = V3{0.f, 0.f, 0.f} - fs0;
+    if (__builtin_expect(rd.has_ext, 0)) {
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      V3 Fe = F[e];
-      V3 tau = T[e];
-      if (rd.has_ext && ok[e]) {
+      for (int e = 0; e < E; ++e) {
+        if (!ok[e]) continue;
         const float* pf = fext + 3 * (rd.pt_off + off + j0 + e + 1);
         const float* pt = text + 3 * (rd.fr_off + off + j0 + e);
-        Fe = Fe + V3{pf[0], pf[1], pf[2]};
-        tau = tau + V3{pt[0], pt[1], pt[2]};
+        F[e] = F[e] + V3{pf[0], pf[1], pf[2]};
+        T[e] = T[e] + V3{pt[0], pt[1], pt[2]};
       }
-      const V3 a = fma3(P[P_WINV][e], Fe, fnma3(rd.damp_lin, Vv[e], grav));
-      Vv[e] = fma3(dt, a, Vv[e]);
+      if (g == 0) {
+        const float* pf = fext + 3 * rd.pt_off;
+        Fb = Fb + V3{pf[0], pf[1], pf[2]};
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const V3 tau = T[e];
+      const V3 a = fma3(P[P_WINV][e], F[e], fnma3(rd.damp_lin, Vv[e], grav));
+      Vv[e] = fma3(dts[e], a, Vv[e]);
       const V3 o = Om[e];
       const float i1 = P[P_IINV1][e], i3 = P[P_IINV3][e], kg = P[P_GYRO][e];
       const V3 al = {i1 * tau.x - kg * o.y * o.z - rd.damp_ang * o.x,
                      i1 * tau.y + kg * o.x * o.z - rd.damp_ang * o.y,
                      i3 * tau.z - rd.damp_ang * o.z};
-      Om[e] = fma3(dt, al, o);
+      Om[e] = fma3(dts[e], al, o);
     }
-    if (g == 0) {
-      if (ghost) {
-        bv = {0.f, 0.f, 0.f};                                  // fixed halo-edge point
-      } else if (rd.clamp) {
-        bv = (1.0f / dt) * ((xc - bx) - bxl);
-        Om[0] = wc;
-      } else {
-        V3 Fb = V3{0.f, 0.f, 0.f} - fs0;
-        if (rd.has_ext) {
-          const float* pf = fext + 3 * rd.pt_off;
-          Fb = Fb + V3{pf[0], pf[1], pf[2]};
-        }
-        bv = fma3(dt, fma3(rd.winv0, Fb, fnma3(rd.damp_lin, bv, grav)), bv);
-      }
+    // the base point (only lane 0's copy is ever read): a fixed halo-edge point, clamped, or free
+    const V3 bc = (ghost ? 0.f : 1.0f / dt) * ((xc - bx) - bxl);
+    if (__builtin_expect(rd.clamp || ghost, 1)) {
+      bv = bc;
+    } else {
+      bv = fma3(dt, fma3(rd.winv0, Fb, fnma3(rd.damp_lin, bv, grav)), bv);
     }
+    Om[0] = sel(clamp0, wc, Om[0]);
   }
 
-  // One red-black half-sweep h of the distance impulses.  If dsnap is given, the segment
-  // vector d of the slot's segment in this half-sweep is saved (for the adjoint).
-  template <bool M>
-  __device__ __forceinline__ void half_sweep(const RodDev& rd, Mailbox<W, M>& mb, int& par, int h,
-                                             const V3 (&Ev)[E], V3 enext, V3* dsnap) {
-    const bool cross_lanes = (E % 2 == 1) || (h == 0);
-    V3 vlo = {0.f, 0.f, 0.f}, vhi = {0.f, 0.f, 0.f};
-    if (cross_lanes) {
-      float mh[3] = {Vv[E - 1].x, Vv[E - 1].y, Vv[E - 1].z};
-      float ml[3] = {Vv[0].x, Vv[0].y, Vv[0].z};
-      const float base[3] = {bv.x, bv.y, bv.z};
-      float lo[3], hi[3];
-      exchange<W, E, 3, 3, true, M>(mh, lo, ml, hi, base, mb, par);
-      vlo = {lo[0], lo[1], lo[2]};
-      vhi = {hi[0], hi[1], hi[2]};
-      if (!M && g == 0) vlo = bv;
-    }
-    V3 dvb = {0.f, 0.f, 0.f};
-    V3 nv[E];
+  // One red-black half-sweep H of the distance impulses (segments of parity H).  FREE: the base
+  // point may move (without it, the rod is clamped or the window starts inside the rod, and
+  // the base point's update drops out).  ODD: of an odd iteration.  If dsnap is given, the segment vector d of the slot's
+  // segment in this half-sweep is saved (for the adjoint).
+  template <int H, bool FREE, bool ODD>
+  __device__ __forceinline__ void half_sweep(Mailbox<W>& mb, const V3 (&Ev)[E], V3 enext,
+                                             V3* dsnap) {
     if constexpr (E % 2 == 0) {
       // Even E: slot e has the parity of e (lane and window starts are even).  Half-sweep 1
       // pairs slots (0, 1), (2, 3), ..., half-sweep 0 pairs (1, 2), (3, 4), ...: the two slots
@@ -864,6 +824,7 @@ struct RodLane {
       // operands both ends would use (slot a's next-segment coefficients are slot a + 1's own),
       // so the result is the same as computing it at each end.  In half-sweep 0 slots 0 and
       // E - 1 act on the segments that cross to the lanes below and above.
+      V3 nv[E];
       auto pair = [&](int a) {   // the segment between slots a and a + 1 (slot a + 1's)
         const V3 d = fma3(dt, Vv[a + 1] - Vv[a], Ev[a + 1]);
         const V3 im = impulse_d(d, P[P_CI][a + 1], P[P_CIL][a + 1]);
@@ -874,50 +835,139 @@ struct RodLane {
           dsnap[a + 1] = d;
         }
       };
-      if (h == 0) {
+      if constexpr (H == 0) {
+        V3 vlo, vhi;
+        exchange_v<FREE, ODD>(mb, vlo, vhi);
         const V3 d0 = fma3(dt, Vv[0] - vlo, Ev[0]);
         const V3 im0 = impulse_d(d0, P[P_CI][0], P[P_CIL][0]);
-        nv[0] = fnma3(P[P_WINV][0], im0, Vv[0]);
+        V3 iml;
+        if constexpr (W == 1) {
+          // one wavefront holds the rod: the segment above is the next lane's first, and its
+          // impulse is taken from there (three moves instead of evaluating it again)
+          iml = {from_upper_lane(im0.x), from_upper_lane(im0.y), from_upper_lane(im0.z)};
+          if (dsnap)
+            dsnap[E - 1] = {from_upper_lane(d0.x), from_upper_lane(d0.y), from_upper_lane(d0.z)};
+        } else {
+          const V3 dl = fma3(dt, vhi - Vv[E - 1], enext);
+          iml = impulse_d(dl, P[P_CI_NEXT][E - 1], P[P_CIL_NEXT][E - 1]);
+          if (dsnap) dsnap[E - 1] = dl;
+        }
         if (dsnap) dsnap[0] = d0;
-        dvb = P[P_WINV_PREV][0] * im0;   // base point: left end of segment 0
         imp0 = imp0 + im0;
 #pragma unroll
         for (int a = 1; a + 1 < E; a += 2) pair(a);
-        const V3 dl = fma3(dt, vhi - Vv[E - 1], enext);
-        const V3 iml = impulse_d(dl, P[P_CI_NEXT][E - 1], P[P_CIL_NEXT][E - 1]);
+        nv[0] = fnma3(P[P_WINV][0], im0, Vv[0]);
         nv[E - 1] = fma3(P[P_WINV][E - 1], iml, Vv[E - 1]);
-        if (dsnap) dsnap[E - 1] = dl;
+        if (FREE) bv = bv + P[P_WINV_PREV][0] * im0;   // base point: left end of segment 0
       } else {
 #pragma unroll
         for (int a = 0; a < E; a += 2) pair(a);
       }
 #pragma unroll
       for (int e = 0; e < E; ++e) Vv[e] = nv[e];
-      if (g == 0 && h == 0 && !rd.clamp && !ghost) bv = bv + dvb;
-      return;
+    } else {
+      static_assert(E == 1, "odd shapes hold one slot per lane");
+      // One slot per lane: the lane is the right end of its own segment (odd lanes in
+      // half-sweep 1, even ones in half-sweep 0) or the left end of the next lane's.  Only that
+      // segment is evaluated, with d = e + dt (v_hi - v_lo) written as e -+ dt (v_other - v).
+      // In half-sweep 1 the pairs (0, 1), (2, 3), ... lie inside a wavefront.
+      const bool is_hi = ((j0 & 1) == H);
+      V3 vo;
+      if constexpr (H == 0) {
+        V3 vlo, vhi;
+        exchange_v<FREE, ODD>(mb, vlo, vhi);
+        vo = sel(is_hi, vlo, vhi);
+      } else {
+        vo = {from_pair_lane(Vv[0].x), from_pair_lane(Vv[0].y), from_pair_lane(Vv[0].z)};
+      }
+      const V3 es = sel(is_hi, Ev[0], enext);
+      const float ci = is_hi ? P[P_CI][0] : P[P_CI_NEXT][0];
+      const float cil = is_hi ? P[P_CIL][0] : P[P_CIL_NEXT][0];
+      const V3 d = fma3(is_hi ? -dt : dt, vo - Vv[0], es);
+      const V3 im = impulse_d(d, ci, cil);
+      if (dsnap) dsnap[0] = d;
+      if (H == 0) imp0 = imp0 + im;
+      if (FREE && H == 0) bv = bv + P[P_WINV_PREV][0] * im;
+      Vv[0] = fma3(is_hi ? -P[P_WINV][0] : P[P_WINV][0], im, Vv[0]);
     }
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int j = j0 + e;
-      const bool is_hi = ((j & 1) == h);   // slot is the right end of segment j
-      const float w_me = P[P_WINV][e];
-      // as right end of segment j (partner: point j) or left end of segment j+1
-      // (partner: point j+2); only one of the two is live for even E
-      const V3 v_lo = (e == 0) ? vlo : Vv[e - 1];
-      const V3 v_hi = (e == E - 1) ? vhi : Vv[e + 1];
-      const V3 e_next = (e == E - 1) ? enext : Ev[e + 1];
-      const V3 d_hi = fma3(dt, Vv[e] - v_lo, Ev[e]);
-      const V3 d_lo = fma3(dt, v_hi - Vv[e], e_next);
-      const V3 im_hi = impulse_d(d_hi, P[P_CI][e], P[P_CIL][e]);
-      const V3 im_lo = impulse_d(d_lo, P[P_CI_NEXT][e], P[P_CIL_NEXT][e]);
-      nv[e] = sel(is_hi, fnma3(w_me, im_hi, Vv[e]), fma3(w_me, im_lo, Vv[e]));
-      if (dsnap) dsnap[e] = sel(is_hi, d_hi, d_lo);
-      if (e == 0) dvb = P[P_WINV_PREV][e] * im_hi;   // base point: left end of segment 0
-      if (e == 0 && h == 0) imp0 = imp0 + im_hi;
+  }
+
+  // The velocities that half-sweep 0 needs from the lanes below (its last slot's point; the base
+  // point for lane 0) and above (its first slot's point).  Between wavefronts: one LDS write and
+  // one read per lane, both edge lanes' words at once.  ODD: an odd iteration.  BASE: the base point's velocity changes
+  // between iterations and is published with them (else once per step, publish_base).
+  template <bool BASE, bool ODD>
+  __device__ __forceinline__ void exchange_v(Mailbox<W>& mb, V3& vlo, V3& vhi) const {
+    const V3 a = Vv[E - 1], b = Vv[0];
+    if constexpr (W == 1) {
+      vlo = {from_lower_lane(a.x), from_lower_lane(a.y), from_lower_lane(a.z)};
+      vlo = sel(first_lane(), bv, vlo);
+      vhi = {from_upper_lane(b.x), from_upper_lane(b.y), from_upper_lane(b.z)};
+    } else {
+      constexpr int R = kSecRow;
+      float* const at = mb.row[wave][0] + (ODD ? kSecVelOdd : kSecVel);
+      const bool top = last_lane();
+      if (__builtin_expect(edge_lane(), 1)) {
+        float* const p = at + (top ? 3 * R : 2 * R);
+        const V3 m = sel(top, a, b);
+        p[0] = m.x; p[1] = m.y; p[2] = m.z;
+        if (BASE && wave == 0 && !top) {
+          at[R] = bv.x; at[R + 1] = bv.y; at[R + 2] = bv.z;
+        }
+      }
+      __syncthreads();
+      const V3 t = {at[R], at[R + 1], at[R + 2]}, u = {at[4 * R], at[4 * R + 1], at[4 * R + 2]};
+      vlo = {from_lower_lane_or(t.x, a.x), from_lower_lane_or(t.y, a.y), from_lower_lane_or(t.z, a.z)};
+      vhi = {from_upper_lane_or(u.x, b.x), from_upper_lane_or(u.y, b.y), from_upper_lane_or(u.z, b.z)};
     }
-#pragma unroll
-    for (int e = 0; e < E; ++e) Vv[e] = nv[e];
-    if (g == 0 && h == 0 && !rd.clamp && !ghost) bv = bv + dvb;
+  }
+  // The base point's velocity for a step's iterations (both sections), before their first.
+  __device__ __forceinline__ void publish_base(Mailbox<W>& mb) const {
+    if constexpr (W > 1) {
+      if (wave == 0 && first_lane()) {
+        float* const at = mb.row[0][1];
+        at[kSecVel] = at[kSecVelOdd] = bv.x;
+        at[kSecVel + 1] = at[kSecVelOdd + 1] = bv.y;
+        at[kSecVel + 2] = at[kSecVelOdd + 2] = bv.z;
+      }
+    }
+  }
+
+  // The constraint iterations of a step: both half-sweeps, then after() (what else belongs to
+  // an iteration).
+  template <bool FREE, class After>
+  __device__ __forceinline__ void iterate_base(int n_iter, Mailbox<W>& mb, const V3 (&Ev)[E],
+                                               V3 enext, After&& after) {
+    auto one = [&](auto odd) {
+      half_sweep<0, FREE, odd.value>(mb, Ev, enext, nullptr);
+      half_sweep<1, FREE, false>(mb, Ev, enext, nullptr);
+      after();
+    };
+    int it = 0;
+    // four at a time: the loop's own taken branch costs 40 to 80 cycles, with an iteration at
+    // 220 (one wavefront) to 550 cycles
+    for (; it + 4 <= n_iter; it += 4) {
+      one(std::false_type{});
+      one(std::true_type{});
+      one(std::false_type{});
+      one(std::true_type{});
+    }
+    for (; it + 2 <= n_iter; it += 2) {
+      one(std::false_type{});
+      one(std::true_type{});
+    }
+    if (it < n_iter) one(std::false_type{});
+  }
+  template <class After>
+  __device__ __forceinline__ void iterate(const RodDev& rd, Mailbox<W>& mb, const V3 (&Ev)[E],
+                                          V3 enext, After&& after) {
+    if (rd.n_iter == 0) return;
+    if (rd.clamp || ghost) {
+      publish_base(mb);
+      iterate_base<false>(rd.n_iter, mb, Ev, enext, after);
+    } else {
+      iterate_base<true>(rd.n_iter, mb, Ev, enext, after);
+    }
   }
 
   // Candidate lists of the slots (see kEnvCand): where each was built and its length, in HBM
@@ -1033,33 +1083,47 @@ struct RodLane {
       advance_position(X[e], XL[e], Vv[e], dt);
       advance_quat(Qf[e], QL[e], Om[e], dt);
     }
-    if (g == 0 && !ghost) {
-      if (rd.clamp) {
-        bx = xc;
-        bxl = {0.f, 0.f, 0.f};
-        Qf[0] = qc;
-        QL[0] = {0.f, 0.f, 0.f, 0.f};
-      } else {
-        advance_position(bx, bxl, bv, dt);
-      }
+    Qf[0] = sel4(clamp0, qc, Qf[0]);
+    QL[0] = sel4(clamp0, Q4{0.f, 0.f, 0.f, 0.f}, QL[0]);
+    if (ghost) return;   // (the halo-edge point is held)
+    if (__builtin_expect(rd.clamp, 1)) {
+      bx = xc;
+      bxl = {0.f, 0.f, 0.f};
+    } else {
+      advance_position(bx, bxl, bv, dt);
     }
   }
 };
 
-// Prescribed clamp pose of step s (global step index steps_done + s), evaluated kClampChunk
-// steps at a time, one step per lane (g: the lane within the rod), into LDS.  Must be reached
-// by every thread; any_driven (uniform over the workgroup) says whether any rod in the
-// workgroup has a driven clamp, i.e. whether the chunk barriers are taken.
-template <int W>
-__device__ __forceinline__ void clamp_for_step(const RodDev& rd, float (*cbuf)[10], int s,
-                                               int n_steps, long long steps_done, V3& xc, Q4& qc,
-                                               V3& wc, bool any_driven, int g) {
-  if (!any_driven) return;
-  const bool mine = rd.driven && rd.clamp;
-  const int cs = s % kClampChunk;
-  if (cs == 0) {
+// Clamp poses of a workgroup's rod in LDS: x (3), q (4), body rate (3), padded to whole 16-byte
+// reads.  A driven clamp's are evaluated kClampChunk steps at a time, one step per lane; a
+// static one's are in the first row, so that a step reads its row without asking which it is.
+constexpr int kClampRow = 12;
+
+// Writes the static pose (needs a barrier before the first step reads it).
+__device__ __forceinline__ void clamp_init(const RodDev& rd, float (*cbuf)[kClampRow], int g) {
+  if (g == 0) {
+    float* c = cbuf[0];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      c[k] = rd.cx0[k];
+      c[7 + k] = 0.f;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) c[3 + k] = rd.cq0[k];
+  }
+}
+
+// Evaluates the poses of the next steps when step s (global step index steps_done + s) starts a
+// chunk (g: the lane within the rod).  Must be reached by every thread; any_driven (uniform over
+// the workgroup) says whether any rod in the workgroup has a driven clamp, i.e. whether the
+// chunk barriers are taken.
+__device__ __forceinline__ void clamp_chunk(const RodDev& rd, float (*cbuf)[kClampRow], int s,
+                                            int n_steps, long long steps_done, bool any_driven,
+                                            int g) {
+  if (__builtin_expect(any_driven && s % kClampChunk == 0, 0)) {
     __syncthreads();
-    if (mine && g < kClampChunk && s + g < n_steps) {
+    if (rd.driven && rd.clamp && g < kClampChunk && s + g < n_steps) {
       V3 pxc, pwc;
       Q4 pqc;
       clamp_pose(rd, rd.t0 + (double)(steps_done + s + g + 1) * rd.dt_d, pxc, pqc, pwc);
@@ -1070,8 +1134,12 @@ __device__ __forceinline__ void clamp_for_step(const RodDev& rd, float (*cbuf)[1
     }
     __syncthreads();
   }
-  if (!mine) return;
-  const float* c = cbuf[cs];
+}
+
+// The pose of step s.
+__device__ __forceinline__ void clamp_read(const RodDev& rd, const float (*cbuf)[kClampRow], int s,
+                                           V3& xc, Q4& qc, V3& wc) {
+  const float* c = cbuf[rd.driven ? s % kClampChunk : 0];
   xc = {c[0], c[1], c[2]};
   qc = {c[3], c[4], c[5], c[6]};
   wc = {c[7], c[8], c[9]};
@@ -1091,18 +1159,19 @@ __global__ __launch_bounds__(64 * W) void rod_resident_kernel(
     float* __restrict__ traj,
     long long traj_stride, int n_pts, int n_frames, float* __restrict__ tips, int tip_steps,
     long long tip_base, int traj_steps, int store_final) {
-  __shared__ Mailbox<W, kMergedExchange<W, E>> mb;
+  __shared__ Mailbox<W> mb;
   mailbox_init(mb);
-  __shared__ float cbuf[kClampChunk][10];
+  __shared__ alignas(16) float cbuf[kClampChunk][kClampRow];
   const int rod = rod_ids[blockIdx.x];
   const RodDev rd = rods[rod];
   RodLane<W, E> L;
   L.load_params(rd, prm, prm_stride);
+  clamp_init(rd, cbuf, L.g);
   L.load_state(rd, st);
+  __syncthreads();
   __shared__ float4 lcand[(F & kFeatEnv) ? 64 * W * E : 1];
   __shared__ float lrad[(F & kFeatEnv) ? 64 * W * E : 1];
   if (F & kFeatEnv) L.env_load(rd, lcand, lrad);
-  int par = 0;
   V3 xc = {rd.cx0[0], rd.cx0[1], rd.cx0[2]}, wc = {0.f, 0.f, 0.f};
   Q4 qc = {rd.cq0[0], rd.cq0[1], rd.cq0[2], rd.cq0[3]};
   const int tip_lane = (rd.n - 1) / E, tip_e = (rd.n - 1) % E;
@@ -1118,17 +1187,20 @@ __global__ __launch_bounds__(64 * W) void rod_resident_kernel(
     pw = mailbox_load(&hb->pose[L.g]);
 
   for (int s = 0; s < n_steps; ++s) {
-    if (traj && s < traj_steps) {
+    if ((F & kFeatTrace) && traj && s < traj_steps) {
       L.store_state(rd, state_at(traj + (long long)s * traj_stride, n_pts, n_frames));
+    }
+    if (!(F & kFeatHaptic)) {   // (a mailbox rod's pose is static or comes from its mailbox)
+      clamp_chunk(rd, cbuf, s, n_steps, steps_done, rd.driven && rd.clamp, L.g);
+      clamp_read(rd, cbuf, s, xc, qc, wc);
     }
     if (F & kFeatEnv) L.env_detect(rd, lcand, lrad);   // environment collisions (Fig. 5: detection first)
     V3 xl, xll, vl, wn;
     Q4 qn, qnl;
-    L.template exchange_a<(F & kFeatDamp) != 0>(mb, par, xl, xll, qn, qnl, vl, wn);
+    L.template exchange_a<(F & kFeatDamp) != 0>(mb, xl, xll, qn, qnl, vl, wn);
     V3 Fo[E], T[E], Ev[E], fs0, enext;
-    L.template forces<(F & kFeatDamp) != 0>(mb, par, xl, xll, qn, qnl, Fo, T, Ev, fs0, enext,
+    L.template forces<(F & kFeatDamp) != 0>(mb, xl, xll, qn, qnl, Fo, T, Ev, fs0, enext,
                                             rd.damp_int, vl, wn);
-    clamp_for_step<W>(rd, cbuf, s, n_steps, steps_done, xc, qc, wc, rd.driven && rd.clamp, L.g);
     const bool hfirst = hb && hn == 0;
     if (hfirst && L.g < 64) {   // wave 0, all lanes: take the pose if whole and new
       const uint32_t tag = (uint32_t)(pw >> 32);
@@ -1148,11 +1220,9 @@ __global__ __launch_bounds__(64 * W) void rod_resident_kernel(
     // momentum the base point receives over the window: internal force x dt, plus segment 0's
     // constraint impulses (accumulated by the sweeps)
     L.imp0 = fnma3(rd.dt, fs0, hn == 0 ? V3{0.f, 0.f, 0.f} : L.imp0);
-    for (int it = 0; it < rd.n_iter; ++it) {
-      L.half_sweep(rd, mb, par, 0, Ev, enext, nullptr);
-      L.half_sweep(rd, mb, par, 1, Ev, enext, nullptr);
+    L.iterate(rd, mb, Ev, enext, [&]() {
       if (F & kFeatEnv) L.env_impulses(rd);   // then the collision response (Fig. 5)
-    }
+    });
     if ((F & kFeatEnv) && rd.n_iter == 0) L.env_impulses(rd);   // without iterations: once
     L.integrate_velocities(rd, xc, qc);
     if (hb) {
@@ -1170,7 +1240,7 @@ __global__ __launch_bounds__(64 * W) void rod_resident_kernel(
         hn = 0;
       }
     }
-    if (tips && (int)threadIdx.x == tip_lane) {
+    if ((F & kFeatTrace) && tips && (int)threadIdx.x == tip_lane) {
 #pragma unroll
       for (int e = 0; e < E; ++e)
         if (e == tip_e) {
@@ -1180,7 +1250,7 @@ __global__ __launch_bounds__(64 * W) void rod_resident_kernel(
     }
   }
   if (F & kFeatEnv) L.env_store(rd, lcand);
-  if (store_final) {
+  if (!(F & kFeatTrace) || store_final) {
     const float chk = L.store_state(rd, st);
     if (!__builtin_isfinite(chk)) atomicOr(status, 1);
   }
@@ -1269,8 +1339,8 @@ __global__ __launch_bounds__(128 * W) void rod_group_kernel(
   constexpr int CC = CT ? CAP : 1;                                  // contact-list slots
   constexpr int SMAX = CT ? 2 * ((CAP + kSphereSize - 1) / kSphereSize) : 1;  // spheres
   constexpr int SW = (SMAX + 31) / 32;
-  __shared__ Mailbox<W, false> mb[2];   // two rods per workgroup: the plain exchange
-  __shared__ float cbuf[2][kClampChunk][10];
+  __shared__ Mailbox<W> mb[2];
+  __shared__ alignas(16) float cbuf[2][kClampChunk][kClampRow];
   // step-start position and sphere radius, and the low parts of the position (the positions
   // are pairs of floats; separations between points take both); rewritten at every step start
   // after a barrier, so that no wavefront still reads the previous step's
@@ -1293,7 +1363,8 @@ __global__ __launch_bounds__(128 * W) void rod_group_kernel(
   __shared__ int moved[2][2 * W];                         // per wavefront and step parity
   __shared__ int touching[2][2 * W];                      // ditto: some point has a contact
   const GroupDev gp = groups[blockIdx.x];
-  const int sub = threadIdx.x >= 64 * W ? 1 : 0;
+  const int sub = __builtin_amdgcn_readfirstlane(threadIdx.x >= 64 * W ? 1 : 0);
+  mailbox_init(mb[sub]);
   const bool active = gp.rod[sub] >= 0;
   RodDev rd = rods[active ? gp.rod[sub] : gp.rod[0]];
   if (!active) rd.n = 0;   // idle half: no slots, same barriers
@@ -1335,9 +1406,7 @@ __global__ __launch_bounds__(128 * W) void rod_group_kernel(
   const float reb2 = (0.45f * gp.margin) * (0.45f * gp.margin);
   const int s0 = (nrod[0] + kSphereSize - 1) / kSphereSize;
   const int ns = s0 + (nrod[1] + kSphereSize - 1) / kSphereSize;
-  int par = 0;
-  V3 xc = {rd.cx0[0], rd.cx0[1], rd.cx0[2]}, wc = {0.f, 0.f, 0.f};
-  Q4 qc = {rd.cq0[0], rd.cq0[1], rd.cq0[2], rd.cq0[3]};
+  clamp_init(rd, cbuf[sub], L.g);   // (the first step's barriers come before its read)
   const float dt = rd.dt;
   int bpar = 0;
   bool overflow = false;
@@ -1513,14 +1582,17 @@ __global__ __launch_bounds__(128 * W) void rod_group_kernel(
     // ---- the step
     V3 xl, xll;
     Q4 qn, qnl;
-    L.exchange_a(mb[sub], par, xl, xll, qn, qnl);
+    clamp_chunk(rd, cbuf[sub], s, n_steps, steps_done, any_driven, L.g);
+    V3 xc, wc;
+    Q4 qc;
+    clamp_read(rd, cbuf[sub], s, xc, qc, wc);
+    L.exchange_a(mb[sub], xl, xll, qn, qnl);
     V3 F[E], T[E], Ev[E], fs0, enext;
-    L.forces(mb[sub], par, xl, xll, qn, qnl, F, T, Ev, fs0, enext);
-    clamp_for_step<W>(rd, cbuf[sub], s, n_steps, steps_done, xc, qc, wc, any_driven, L.g);
+    L.forces(mb[sub], xl, xll, qn, qnl, F, T, Ev, fs0, enext);
     L.integrate_forces(rd, F, T, fs0, xc, wc, fext, text);
-    for (int it = 0; it < rd.n_iter; ++it) {
-      L.half_sweep(rd, mb[sub], par, 0, Ev, enext, nullptr);
-      L.half_sweep(rd, mb[sub], par, 1, Ev, enext, nullptr);
+    auto iteration = [&](auto odd) {
+      L.template half_sweep<0, true, odd.value>(mb[sub], Ev, enext, nullptr);
+      L.template half_sweep<1, true, odd.value>(mb[sub], Ev, enext, nullptr);
       if (gp.bind_mode) {
         publish();
 #pragma unroll
@@ -1605,7 +1677,13 @@ __global__ __launch_bounds__(128 * W) void rod_group_kernel(
         }
         bpar ^= 1;
       }
+    };
+    int it = 0;
+    for (; it + 2 <= rd.n_iter; it += 2) {
+      iteration(std::false_type{});
+      iteration(std::true_type{});
     }
+    if (it < rd.n_iter) iteration(std::false_type{});
     L.integrate_velocities(rd, xc, qc);
   }
   if (active) {
@@ -1667,8 +1745,9 @@ __global__ __launch_bounds__(64 * W) void rod_grid_kernel(
     StateArrays st, const float* __restrict__ fext, const float* __restrict__ text, int n_steps,
     long long steps_done, int* __restrict__ status, float* pub, int pub_slots, int n_chunks,
     int* flags, int spin_limit) {
-  __shared__ Mailbox<W, false> mb;   // the plain exchange (see kMergedExchange)
-  __shared__ float cbuf[kClampChunk][10];
+  __shared__ Mailbox<W> mb;
+  mailbox_init(mb);
+  __shared__ alignas(16) float cbuf[kClampChunk][kClampRow];
   __shared__ int abort_flag;
   const int ci = block_chunk[blockIdx.x];
   const GridChunk ck = chunks[ci];
@@ -1676,9 +1755,7 @@ __global__ __launch_bounds__(64 * W) void rod_grid_kernel(
   RodLane<W, E> L;
   L.load_params(rd, prm, prm_stride, ck.win0, ck.nwin);
   L.load_state(rd, st);
-  int par = 0;
-  V3 xc = {rd.cx0[0], rd.cx0[1], rd.cx0[2]}, wc = {0.f, 0.f, 0.f};
-  Q4 qc = {rd.cq0[0], rd.cq0[1], rd.cq0[2], rd.cq0[3]};
+  clamp_init(rd, cbuf, L.g);
   const int own_lo = ck.s0 - ck.win0, own_hi = own_lo + ck.c;
   const int H = ck.halo;
   int xk = 0;   // halo exchanges so far in this launch
@@ -1687,18 +1764,15 @@ __global__ __launch_bounds__(64 * W) void rod_grid_kernel(
 
   for (int s = 0; s < n_steps; ++s) {
     const long long gs = steps_done + s;
-    V3 xl, xll;
-    Q4 qn, qnl;
-    L.exchange_a(mb, par, xl, xll, qn, qnl);
+    V3 xl, xll, xc, wc;
+    Q4 qn, qnl, qc;
+    clamp_chunk(rd, cbuf, s, n_steps, steps_done, rd.driven && rd.clamp && ck.win0 == 0, L.g);
+    clamp_read(rd, cbuf, s, xc, qc, wc);
+    L.exchange_a(mb, xl, xll, qn, qnl);
     V3 F[E], T[E], Ev[E], fs0, enext;
-    L.forces(mb, par, xl, xll, qn, qnl, F, T, Ev, fs0, enext);
-    if (ck.win0 == 0)
-      clamp_for_step<W>(rd, cbuf, s, n_steps, steps_done, xc, qc, wc, rd.driven && rd.clamp, L.g);
+    L.forces(mb, xl, xll, qn, qnl, F, T, Ev, fs0, enext);
     L.integrate_forces(rd, F, T, fs0, xc, wc, fext, text);
-    for (int it = 0; it < rd.n_iter; ++it) {
-      L.half_sweep(rd, mb, par, 0, Ev, enext, nullptr);
-      L.half_sweep(rd, mb, par, 1, Ev, enext, nullptr);
-    }
+    L.iterate(rd, mb, Ev, enext, []() {});
     L.integrate_velocities(rd, xc, qc);
 
     if ((s + 1) % ck.every != 0 || s + 1 == n_steps) continue;   // (uniform over the chunk)

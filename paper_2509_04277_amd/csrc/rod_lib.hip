@@ -63,14 +63,16 @@ struct KernelEntry {
   int waves, elems;
   KernelFn fn[8];   // by feature bits (kFeatHaptic, kFeatEnv, kFeatDamp); the variants exist
                     // for the default shapes only, without environment + internal friction
+  KernelFn trace;   // the plain kernel with kFeatTrace
 };
 
 // Built kernel shapes: (waves per rod, elements per lane).  Capacity = 64 * waves * elems.
-#define ROD_SHAPE(w, e) {w, e, {corde::rod_resident_kernel<w, e, 0>}}
+#define ROD_SHAPE(w, e) {w, e, {corde::rod_resident_kernel<w, e, 0>}, corde::rod_resident_kernel<w, e, 8>}
 #define ROD_SHAPE_F(w, e)                                                                   \
   {w, e, {corde::rod_resident_kernel<w, e, 0>, corde::rod_resident_kernel<w, e, 1>,       \
           corde::rod_resident_kernel<w, e, 2>, corde::rod_resident_kernel<w, e, 3>,       \
-          corde::rod_resident_kernel<w, e, 4>, corde::rod_resident_kernel<w, e, 5>}}
+          corde::rod_resident_kernel<w, e, 4>, corde::rod_resident_kernel<w, e, 5>},      \
+   corde::rod_resident_kernel<w, e, 8>}
 const KernelEntry kKernels[] = {
     ROD_SHAPE_F(1, 1), ROD_SHAPE_F(1, 2), ROD_SHAPE(1, 4),    ROD_SHAPE(1, 8),
     ROD_SHAPE(2, 1),   ROD_SHAPE_F(2, 2), ROD_SHAPE(2, 4),    ROD_SHAPE(4, 1),
@@ -1010,7 +1012,7 @@ rod_status launch_forward_on(rod_ctx* c, StateArrays sa, int ks,
     const KernelEntry* k = find_kernel(b.waves, b.elems);
     if (!k) return fail(c, ROD_E_UNSUPPORTED, "kernel shape not built");
     if (b.feat) return fail(c, ROD_E_UNSUPPORTED, "the adjoint steps plain rods only");
-    hipLaunchKernelGGL(k->fn[0], dim3(b.count), dim3(64 * k->waves), 0, stream, c->d_rods,
+    hipLaunchKernelGGL(k->trace, dim3(b.count), dim3(64 * k->waves), 0, stream, c->d_rods,
                        c->d_rod_ids + b.first, c->d_prm, c->prm_stride, sa, c->d_fext,
                        c->d_text, ks, step, c->d_status, traj, S, c->total_pts, c->total_frames,
                        tips, c->adj_steps, tip_base, traj_steps, store_final);
