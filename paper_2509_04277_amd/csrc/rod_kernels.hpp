@@ -817,6 +817,13 @@ struct RodLane {
   template <int H, bool FREE, bool ODD>
   __device__ __forceinline__ void half_sweep(Mailbox<W>& mb, const V3 (&Ev)[E], V3 enext,
                                              V3* dsnap) {
+    V3 vlo = {0.f, 0.f, 0.f}, vhi = {0.f, 0.f, 0.f};
+    if constexpr (H == 0) exchange_v<FREE, ODD>(mb, vlo, vhi);
+    sweep<H, FREE>(vlo, vhi, Ev, enext, dsnap);
+  }
+  // The half-sweep given the velocities from the lanes below and above (half-sweep 0 only).
+  template <int H, bool FREE>
+  __device__ __forceinline__ void sweep(V3 vlo, V3 vhi, const V3 (&Ev)[E], V3 enext, V3* dsnap) {
     if constexpr (E % 2 == 0) {
       // Even E: slot e has the parity of e (lane and window starts are even).  Half-sweep 1
       // pairs slots (0, 1), (2, 3), ..., half-sweep 0 pairs (1, 2), (3, 4), ...: the two slots
@@ -836,8 +843,6 @@ struct RodLane {
         }
       };
       if constexpr (H == 0) {
-        V3 vlo, vhi;
-        exchange_v<FREE, ODD>(mb, vlo, vhi);
         const V3 d0 = fma3(dt, Vv[0] - vlo, Ev[0]);
         const V3 im0 = impulse_d(d0, P[P_CI][0], P[P_CIL][0]);
         V3 iml;
@@ -874,8 +879,6 @@ struct RodLane {
       const bool is_hi = ((j0 & 1) == H);
       V3 vo;
       if constexpr (H == 0) {
-        V3 vlo, vhi;
-        exchange_v<FREE, ODD>(mb, vlo, vhi);
         vo = sel(is_hi, vlo, vhi);
       } else {
         vo = {from_pair_lane(Vv[0].x), from_pair_lane(Vv[0].y), from_pair_lane(Vv[0].z)};
@@ -1376,16 +1379,37 @@ __global__ __launch_bounds__(128 * W) void rod_group_kernel(
     any_driven = any_driven || (r1.driven && r1.clamp);
     nrod[1] = r1.n;
   }
-  const bool moved_rod = !(gp.bind_mode == 1 && sub == 1);
   const bool contact = CT && gp.contact != 0;
   RodLane<W, E> L;
   L.load_params(rd, prm, prm_stride);
   L.load_state(rd, st);
-  int part[E], cnt[E], ncand[E];
+  int cnt[E], ncand[E];
   float rho[E];
+  // Binding of slot j of this thread's rod: the partner's slot and w / (dt (w + w_partner)) (one-way:
+  // 1 / dt), 0 where the slot is not bound, does not exist or is the master's.
+  const bool moved_rod = gp.bind_mode != 0 && !(gp.bind_mode == 1 && sub == 1);
+  const RodDev& ro = rods[gp.rod[1 - sub] >= 0 ? gp.rod[1 - sub] : gp.rod[0]];
+  auto binding = [&](int j, int& pt) {
+    pt = 0;
+    if (!moved_rod || j < 0 || j >= rd.n) return 0.f;
+    const int p = partner[rd.slot_off + j];
+    if (p < 0) return 0.f;
+    pt = p;
+    const float wm = prm[P_WINV * prm_stride + rd.slot_off + j];
+    const float ws = gp.bind_mode == 2 ? wm + prm[P_WINV * prm_stride + ro.slot_off + p] : wm;
+    return ws > 0.f ? wm / (rd.dt * ws) : 0.f;
+  };
+  int part[E];
+  float bfac[E];
+  // The slot next to this wavefront's, below its first lane or above its last (edge lanes only)
+  const int nslot = last_lane() ? L.j0 + E : L.j0 - 1;
+  const bool nvalid = nslot >= 0 && nslot < rd.n;
+  const int nown = nvalid ? nslot : 0;
+  int npart;
+  const float nfac = binding(nslot, npart);
 #pragma unroll
   for (int e = 0; e < E; ++e) {
-    part[e] = (L.ok[e] && gp.bind_mode) ? partner[rd.slot_off + L.j0 + e] : -1;
+    bfac[e] = binding(L.ok[e] ? L.j0 + e : -1, part[e]);
     rho[e] = L.ok[e] ? rho_slot[rd.slot_off + L.j0 + e] : 0.f;
     cnt[e] = 0;
     ncand[e] = 0;
@@ -1408,6 +1432,7 @@ __global__ __launch_bounds__(128 * W) void rod_group_kernel(
   const int ns = s0 + (nrod[1] + kSphereSize - 1) / kSphereSize;
   clamp_init(rd, cbuf[sub], L.g);   // (the first step's barriers come before its read)
   const float dt = rd.dt;
+  const int n_iter = r0.n_iter;   // (equal for both rods)
   int bpar = 0;
   bool overflow = false;
   bool touch = false;   // some point of the group has a contact this step
@@ -1590,25 +1615,56 @@ __global__ __launch_bounds__(128 * W) void rod_group_kernel(
     V3 F[E], T[E], Ev[E], fs0, enext;
     L.forces(mb[sub], xl, xll, qn, qnl, F, T, Ev, fs0, enext);
     L.integrate_forces(rd, F, T, fs0, xc, wc, fext, text);
-    auto iteration = [&](auto odd) {
-      L.template half_sweep<0, true, odd.value>(mb[sub], Ev, enext, nullptr);
+    // predicted separation of a bound pair at the step's start, (x - xo) + (l - lo), for the
+    // thread's slots and the neighbouring one; it and the factors stay for all iterations, so
+    // an iteration reads one velocity per slot from LDS (four 128-bit words before: 4 KB per
+    // wavefront and iteration, the LDS's own time) and divides nothing
+    V3 bd[E], nd = {0.f, 0.f, 0.f}, edge = {0.f, 0.f, 0.f};
+    const bool fused = W > 1 && gp.bind_mode != 0 && !(contact && touch);   // (uniform)
+    if (gp.bind_mode) {
+      auto apart = [&](V3 x, V3 l, int p) {
+        const float4 ox = xs[1 - sub][p], ol = xsl[1 - sub][p];
+        return (x - V3{ox.x, ox.y, ox.z}) + (l - V3{ol.x, ol.y, ol.z});
+      };
+#pragma unroll
+      for (int e = 0; e < E; ++e) bd[e] = apart(L.X[e], L.XL[e], part[e]);
+      if (W > 1) {
+        const float4 x = xs[sub][nown], l = xsl[sub][nown];
+        nd = apart({x.x, x.y, x.z}, {l.x, l.y, l.z}, npart);
+      }
+    }
+    // first: of the step.  With bindings a later iteration needs no exchange of its own before
+    // half-sweep 0: the velocities next to the wavefront's were published before the bindings
+    // were applied, and their bindings are applied here as by their owner (edge): one barrier per
+    // iteration instead of two.  With both: 2 x 512 rods bound both ways 13.0 -> 10.5 us per step
+    // (a loop of 10-step launches), 2 x 700 41 -> 26, 2 x 100 7.4 -> 4.3.
+    auto iteration = [&](auto odd, auto first) {
+      if (W > 1 && !first.value && fused) {
+        const V3 a = L.Vv[E - 1], b = L.Vv[0];
+        const V3 t = sel(L.g == 0, L.bv, edge);
+        const V3 vlo = {from_lower_lane_or(t.x, a.x), from_lower_lane_or(t.y, a.y),
+                        from_lower_lane_or(t.z, a.z)};
+        const V3 vhi = {from_upper_lane_or(t.x, b.x), from_upper_lane_or(t.y, b.y),
+                        from_upper_lane_or(t.z, b.z)};
+        L.template sweep<0, true>(vlo, vhi, Ev, enext, nullptr);
+      } else {
+        L.template half_sweep<0, true, odd.value>(mb[sub], Ev, enext, nullptr);
+      }
       L.template half_sweep<1, true, odd.value>(mb[sub], Ev, enext, nullptr);
       if (gp.bind_mode) {
         publish();
+        auto bound = [&](V3 v, V3 d0, float4 ov, float f) {   // predicted separation removed
+          const V3 d = fma3(dt, v - V3{ov.x, ov.y, ov.z}, d0);
+          return sel(f != 0.f, fnma3(f, d, v), v);
+        };
+        if (W > 1 && fused) {
+          const float4 v = vw[bpar][sub][nown], ov = vw[bpar][1 - sub][npart];
+          edge = sel(nvalid, bound({v.x, v.y, v.z}, nd, ov, nfac), V3{0.f, 0.f, 0.f});
+        }
+        if (moved_rod) {
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-          if (part[e] >= 0 && moved_rod) {
-            const float4 ox = xs[1 - sub][part[e]];
-            const float4 ov = vw[bpar][1 - sub][part[e]];
-            const float4 ol = xsl[1 - sub][part[e]];
-            const V3 lo = {ol.x, ol.y, ol.z};
-            // predicted separation: (x - xo) + (l - lo) + dt (v - vo)
-            const V3 d0 = (L.X[e] - V3{ox.x, ox.y, ox.z}) + (L.XL[e] - lo);
-            const V3 d = fma3(dt, L.Vv[e] - V3{ov.x, ov.y, ov.z}, d0);
-            const float wm = L.P[P_WINV][e];
-            const float ws = gp.bind_mode == 2 ? wm + ov.w : wm;
-            if (ws > 0.f) L.Vv[e] = fnma3(wm / (dt * ws), d, L.Vv[e]);
-          }
+          for (int e = 0; e < E; ++e)
+            L.Vv[e] = bound(L.Vv[e], bd[e], vw[bpar][1 - sub][part[e]], bfac[e]);
         }
         bpar ^= 1;
       }
@@ -1678,12 +1734,13 @@ __global__ __launch_bounds__(128 * W) void rod_group_kernel(
         bpar ^= 1;
       }
     };
-    int it = 0;
-    for (; it + 2 <= rd.n_iter; it += 2) {
-      iteration(std::false_type{});
-      iteration(std::true_type{});
+    iteration(std::false_type{}, std::true_type{});   // (n_iter >= 1)
+    int it = 1;
+    for (; it + 2 <= n_iter; it += 2) {
+      iteration(std::true_type{}, std::false_type{});
+      iteration(std::false_type{}, std::false_type{});
     }
-    if (it < rd.n_iter) iteration(std::false_type{});
+    if (it < n_iter) iteration(std::true_type{}, std::false_type{});
     L.integrate_velocities(rd, xc, qc);
   }
   if (active) {
