@@ -732,6 +732,94 @@ __global__ void zero_floats(float* __restrict__ p, long long n) {
     p[i] = 0.f;
 }
 
+// Up to kMoveJobs copies (src null: fills with 0) and the start time of every rod, in one launch:
+// separate copies and fills of a few kB cost 5 us each on the device and about as much to enqueue
+// (a device rod_set_state was six to eight of them, then an upload of the rod table and a wait
+// for it).  Measured, set + get of a 4096-element rod's state: 70 -> 15 us of stream time.
+constexpr int kMoveJobs = 8;
+struct MoveJobs {
+  const float* src[kMoveJobs];
+  float* dst[kMoveJobs];
+  long long n[kMoveJobs];   // floats
+  int count;
+  RodDev* rods;             // null: start times unchanged
+  int n_rods;
+  double t0;
+};
+__global__ __launch_bounds__(256) void move_floats(MoveJobs m) {
+  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  const long long stride = (long long)gridDim.x * blockDim.x;
+  for (int j = 0; j < m.count; ++j) {
+    const float* s = m.src[j];
+    float* d = m.dst[j];
+    // four floats per lane where both sides start at 16 bytes, the rest one by one
+    const bool wide = (((uintptr_t)s | (uintptr_t)d) & 15) == 0;
+    const long long quads = wide ? m.n[j] / 4 : 0;
+    for (long long i = t; i < quads; i += stride)
+      reinterpret_cast<float4*>(d)[i] =
+          s ? reinterpret_cast<const float4*>(s)[i] : make_float4(0.f, 0.f, 0.f, 0.f);
+    for (long long i = 4 * quads + t; i < m.n[j]; i += stride) d[i] = s ? s[i] : 0.f;
+  }
+  if (m.rods)
+    for (long long i = t; i < m.n_rods; i += stride) m.rods[i].t0 = m.t0;
+}
+
+// Collects the jobs of one launch.
+struct Mover {
+  MoveJobs m{};
+  long long most = 0;
+  void add(float* dst, const float* src, long long n) {
+    if (n <= 0) return;
+    m.src[m.count] = src;
+    m.dst[m.count] = dst;
+    m.n[m.count] = n;
+    ++m.count;
+    most = std::max(most, n);
+  }
+  rod_status run(rod_ctx* c) {
+    if (!m.count && !m.rods) return ROD_OK;
+    const long long items = std::max<long long>((most + 3) / 4, m.rods ? m.n_rods : 0);
+    const long long blocks = std::min<long long>(std::max<long long>((items + 255) / 256, 1), 2048);
+    hipLaunchKernelGGL(move_floats, dim3((unsigned)blocks), dim3(256), 0, c->stream, m);
+    HIP_TRY(c, hipGetLastError());
+    return ROD_OK;
+  }
+};
+
+// Whether [p, p + bytes) lies in one allocation of the handle's device, so that a kernel may
+// read or write it (a caller's pointer that does not goes through hipMemcpyAsync, which moves or
+// refuses it).
+bool on_this_device(const rod_ctx* c, const void* p, size_t bytes) {
+  hipPointerAttribute_t at{};
+  if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (at.type != hipMemoryTypeDevice || at.device != c->device) return false;
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if (hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)const_cast<void*>(p)) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  const uintptr_t b = (uintptr_t)base, q = (uintptr_t)p;
+  return q >= b && bytes <= size && q - b <= size - bytes && (q & 3) == 0;
+}
+
+// Adds the copy of n floats between the handle and a caller's array: to the mover where a kernel
+// can reach that array, else enqueued at once.
+rod_status move_or_copy(rod_ctx* c, Mover& mv, float* dst, const float* src, long long n,
+                        bool caller_is_src, bool on_device) {
+  if (on_device && on_this_device(c, caller_is_src ? (const void*)src : dst, sizeof(float) * n)) {
+    mv.add(dst, src, n);
+    return ROD_OK;
+  }
+  const hipMemcpyKind k = on_device ? hipMemcpyDeviceToDevice
+                                    : caller_is_src ? hipMemcpyHostToDevice : hipMemcpyDeviceToHost;
+  HIP_TRY(c, hipMemcpyAsync(dst, src, sizeof(float) * n, k, c->stream));
+  return ROD_OK;
+}
+
 // State arrays of a launch: the handle's own, or (rod_step_state_noalloc) the caller's with
 // the low parts in the device's scratch array.
 StateArrays handle_state(rod_ctx* c) { return {c->d_x, c->d_v, c->d_q, c->d_w, c->d_xl, c->d_ql}; }
@@ -1236,24 +1324,25 @@ rod_status rod_set_state(rod_ctx* c, const float* x, const float* v, const float
   if (!c) return fail(nullptr, ROD_E_INVALID, "null handle");
   if (!x || !v || !q || !w) return fail(c, ROD_E_INVALID, "null state pointer");
   if (!std::isfinite(t0)) return fail(c, ROD_E_INVALID, "t0 must be finite");
-  const hipMemcpyKind k = on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
-  HIP_TRY(c, hipMemcpyAsync(c->d_x, x, sizeof(float) * 3 * c->total_pts, k, c->stream));
-  HIP_TRY(c, hipMemsetAsync(c->d_xl, 0, sizeof(float) * 3 * c->total_pts, c->stream));
-  HIP_TRY(c, hipMemcpyAsync(c->d_v, v, sizeof(float) * 3 * c->total_pts, k, c->stream));
-  HIP_TRY(c, hipMemcpyAsync(c->d_q, q, sizeof(float) * 4 * c->total_frames, k, c->stream));
-  HIP_TRY(c, hipMemsetAsync(c->d_ql, 0, sizeof(float) * 4 * c->total_frames, c->stream));
-  HIP_TRY(c, hipMemcpyAsync(c->d_w, w, sizeof(float) * 3 * c->total_frames, k, c->stream));
-  if (!on_device) HIP_TRY(c, hipStreamSynchronize(c->stream));
+  const long long P3 = 3LL * c->total_pts, F4 = 4LL * c->total_frames, F3 = 3LL * c->total_frames;
+  Mover mv;
+  rod_status st = move_or_copy(c, mv, c->d_x, x, P3, true, on_device);
+  if (st == ROD_OK) st = move_or_copy(c, mv, c->d_v, v, P3, true, on_device);
+  if (st == ROD_OK) st = move_or_copy(c, mv, c->d_q, q, F4, true, on_device);
+  if (st == ROD_OK) st = move_or_copy(c, mv, c->d_w, w, F3, true, on_device);
+  if (st != ROD_OK) return st;
+  mv.add(c->d_xl, nullptr, P3);
+  mv.add(c->d_ql, nullptr, F4);
+  if (c->d_flags) mv.add(reinterpret_cast<float*>(c->d_flags), nullptr, c->n_chunks);
+  mv.m.rods = c->d_rods;
+  mv.m.n_rods = c->n_rods;
+  mv.m.t0 = t0;
+  st = mv.run(c);
+  if (st != ROD_OK) return st;
   c->t0 = t0;
   c->steps_done = 0;
-  {
-    rod_status st = reset_flags(c);
-    if (st != ROD_OK) return st;
-  }
   for (auto& r : c->rods) r.t0 = t0;
-  HIP_TRY(c, hipMemcpyAsync(c->d_rods, c->rods.data(), sizeof(RodDev) * c->n_rods,
-                            hipMemcpyHostToDevice, c->stream));
-  HIP_TRY(c, hipStreamSynchronize(c->stream));  // c->rods is host memory read by the copy
+  if (!on_device) HIP_TRY(c, hipStreamSynchronize(c->stream));
   c->have_state = true;
   return ROD_OK;
 }
@@ -1261,11 +1350,24 @@ rod_status rod_set_state(rod_ctx* c, const float* x, const float* v, const float
 rod_status rod_get_state(rod_ctx* c, float* x, float* v, float* q, float* w, int32_t on_device) {
   if (!c) return fail(nullptr, ROD_E_INVALID, "null handle");
   if (!c->have_state) return fail(c, ROD_E_ORDER, "rod_get_state before rod_set_state");
-  const hipMemcpyKind k = on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-  if (x) HIP_TRY(c, hipMemcpyAsync(x, c->d_x, sizeof(float) * 3 * c->total_pts, k, c->stream));
-  if (v) HIP_TRY(c, hipMemcpyAsync(v, c->d_v, sizeof(float) * 3 * c->total_pts, k, c->stream));
-  if (q) HIP_TRY(c, hipMemcpyAsync(q, c->d_q, sizeof(float) * 4 * c->total_frames, k, c->stream));
-  if (w) HIP_TRY(c, hipMemcpyAsync(w, c->d_w, sizeof(float) * 3 * c->total_frames, k, c->stream));
+  const long long P3 = 3LL * c->total_pts, F4 = 4LL * c->total_frames, F3 = 3LL * c->total_frames;
+  if ((x != nullptr) + (v != nullptr) + (q != nullptr) + (w != nullptr) == 1) {
+    // one array: a plain copy (1 us less to enqueue than the pointer checks and a launch)
+    const hipMemcpyKind k = on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
+    if (x) HIP_TRY(c, hipMemcpyAsync(x, c->d_x, sizeof(float) * P3, k, c->stream));
+    if (v) HIP_TRY(c, hipMemcpyAsync(v, c->d_v, sizeof(float) * P3, k, c->stream));
+    if (q) HIP_TRY(c, hipMemcpyAsync(q, c->d_q, sizeof(float) * F4, k, c->stream));
+    if (w) HIP_TRY(c, hipMemcpyAsync(w, c->d_w, sizeof(float) * F3, k, c->stream));
+    return on_device ? ROD_OK : rod_sync(c);
+  }
+  Mover mv;
+  rod_status st = ROD_OK;
+  if (x) st = move_or_copy(c, mv, x, c->d_x, P3, false, on_device);
+  if (v && st == ROD_OK) st = move_or_copy(c, mv, v, c->d_v, P3, false, on_device);
+  if (q && st == ROD_OK) st = move_or_copy(c, mv, q, c->d_q, F4, false, on_device);
+  if (w && st == ROD_OK) st = move_or_copy(c, mv, w, c->d_w, F3, false, on_device);
+  if (st == ROD_OK) st = mv.run(c);
+  if (st != ROD_OK) return st;
   if (!on_device) return rod_sync(c);
   return ROD_OK;
 }
@@ -2017,11 +2119,15 @@ rod_status rod_adjoint_backward(rod_ctx* c, int64_t rollout, const float* dl_dti
   if (!dl_dtips) return fail(c, ROD_E_INVALID, "null dL/dtip");
   const size_t S = state_floats(c);
   const size_t P3 = (size_t)3 * c->total_pts, F4 = (size_t)4 * c->total_frames;
-  const hipMemcpyKind kin = on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
-  HIP_TRY(c, hipMemcpyAsync(c->d_dtips, dl_dtips, sizeof(float) * 3 * c->n_rods * c->adj_steps, kin, c->stream));
-  HIP_TRY(c, hipMemsetAsync(c->d_adj, 0, sizeof(float) * S, c->stream));
-  HIP_TRY(c, hipMemsetAsync(c->d_gacc, 0, sizeof(double) * 2 * corde::kAdjointMaxLanes * c->n_rods,
-                            c->stream));
+  {
+    Mover mv;
+    rod_status st = move_or_copy(c, mv, c->d_dtips, dl_dtips, 3LL * c->n_rods * c->adj_steps, true, on_device);
+    if (st != ROD_OK) return st;
+    mv.add(c->d_adj, nullptr, (long long)S);
+    mv.add(reinterpret_cast<float*>(c->d_gacc), nullptr, 4LL * corde::kAdjointMaxLanes * c->n_rods);
+    st = mv.run(c);
+    if (st != ROD_OK) return st;
+  }
   const long long Sl = (long long)S;
   const int nck = c->adj_nckpt, ck = c->adj_ckpt;
   auto reverse = [&](int seg, const float* traj) -> rod_status {
@@ -2076,21 +2182,27 @@ rod_status rod_adjoint_backward(rod_ctx* c, int64_t rollout, const float* dl_dti
       }
     }
   }
-  const hipMemcpyKind kout = on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-  if (dl_dx) HIP_TRY(c, hipMemcpyAsync(dl_dx, c->d_adj, sizeof(float) * P3, kout, c->stream));
-  if (dl_dv) HIP_TRY(c, hipMemcpyAsync(dl_dv, c->d_adj + P3, sizeof(float) * P3, kout, c->stream));
-  if (dl_dq) HIP_TRY(c, hipMemcpyAsync(dl_dq, c->d_adj + 2 * P3, sizeof(float) * F4, kout, c->stream));
-  if (dl_dw) HIP_TRY(c, hipMemcpyAsync(dl_dw, c->d_adj + 2 * P3 + F4, sizeof(float) * 3 * c->total_frames, kout, c->stream));
   if (dl_dbend || dl_dtwist) {
     // fixed-order FP64 sums over the steps, into the first 2 n_rods floats of d_dtips (the
     // loss gradient is no longer needed) and from there to the caller
-    float* gb = c->d_dtips;
-    float* gt = c->d_dtips + c->n_rods;
-    hipLaunchKernelGGL(corde::sum_multiplier_grads, dim3((c->n_rods + 63) / 64), dim3(64), 0,
-                       c->stream, c->d_gacc, c->n_rods, gb, gt);
+    hipLaunchKernelGGL(corde::sum_multiplier_grads, dim3(c->n_rods), dim3(64), 0, c->stream,
+                       c->d_gacc, c->d_dtips, c->d_dtips + c->n_rods);
     HIP_TRY(c, hipGetLastError());
-    if (dl_dbend) HIP_TRY(c, hipMemcpyAsync(dl_dbend, gb, sizeof(float) * c->n_rods, kout, c->stream));
-    if (dl_dtwist) HIP_TRY(c, hipMemcpyAsync(dl_dtwist, gt, sizeof(float) * c->n_rods, kout, c->stream));
+  }
+  {
+    Mover mv;
+    rod_status st = ROD_OK;
+    auto give = [&](float* dst, const float* src, long long n) {
+      if (dst && st == ROD_OK) st = move_or_copy(c, mv, dst, src, n, false, on_device);
+    };
+    give(dl_dx, c->d_adj, (long long)P3);
+    give(dl_dv, c->d_adj + P3, (long long)P3);
+    give(dl_dq, c->d_adj + 2 * P3, (long long)F4);
+    give(dl_dw, c->d_adj + 2 * P3 + F4, 3LL * c->total_frames);
+    give(dl_dbend, c->d_dtips, c->n_rods);
+    give(dl_dtwist, c->d_dtips + c->n_rods, c->n_rods);
+    if (st == ROD_OK) st = mv.run(c);
+    if (st != ROD_OK) return st;
   }
   int stt = 0;
   HIP_TRY(c, hipMemcpyAsync(&stt, c->d_status, sizeof(int), hipMemcpyDeviceToHost, c->stream));

@@ -204,6 +204,13 @@ class RodBatch:
         h = C.c_void_p()
         _check(lib().rod_create(arr, len(specs), C.c_void_p(stream), C.byref(h)))
         self.h = h
+        self.stream = int(stream or 0)
+
+    def _foreign_stream(self, device):
+        """True if torch's current stream on ``device`` is not the handle's: memory that torch
+        frees is then reused without regard to the handle's pending work."""
+        import torch
+        return torch.cuda.current_stream(device).cuda_stream != self.stream
 
     def close(self):
         if getattr(self, "h", None) is not None and self.h.value:
@@ -226,8 +233,13 @@ class RodBatch:
         for a, s in zip((x, v, q, w), sizes):
             if (a.size if isinstance(a, np.ndarray) else a.numel()) != s:
                 raise ValueError("state array of %d values expected" % s)
-        _check(lib().rod_set_state(self.h, *[C.c_void_p(p) for p, _ in ptrs], dev.pop(),
+        on_device = dev.pop()
+        _check(lib().rod_set_state(self.h, *[C.c_void_p(p) for p, _ in ptrs], on_device,
                                    float(t0)), self.h)
+        if on_device and self._foreign_stream(x.device):
+            # the caller may free the arrays on its own stream when this returns
+            import torch
+            torch.cuda.ExternalStream(self.stream, device=x.device).synchronize()
 
     def set_state_rods(self, states, t0: float = 0.0):
         """Set from a list of ``RodState`` (any float dtype), concatenated in rod order."""
@@ -437,12 +449,14 @@ def rollout_function():
     class RodRollout(torch.autograd.Function):
         @staticmethod
         def forward(ctx, batch, bend, twist, x0, v0, q0, w0, n_steps, ckpt_every):
-            batch.set_stiffness_mult(bend.detach().cpu().numpy(), twist.detach().cpu().numpy())
+            mult = torch.stack((bend.detach(), twist.detach())).cpu().numpy()   # one copy, one wait
+            batch.set_stiffness_mult(mult[0], mult[1])
             batch.set_state(x0.detach().contiguous(), v0.detach().contiguous(),
                             q0.detach().contiguous(), w0.detach().contiguous())
             tips = torch.empty((len(batch.n), int(n_steps), 3), dtype=torch.float32, device=x0.device)
             batch.adjoint_forward(int(n_steps), int(ckpt_every), tips)
-            torch.cuda.synchronize(x0.device)
+            if batch._foreign_stream(x0.device):   # else the tips are ready in stream order
+                torch.cuda.synchronize(x0.device)
             ctx.batch = batch
             ctx.rollout = batch.rollout   # a later forward on the handle makes backward refuse
             return tips
@@ -454,8 +468,8 @@ def rollout_function():
             out = dict(bend=torch.empty(len(b.n), device=dev), twist=torch.empty(len(b.n), device=dev),
                        x=torch.empty(3 * b.n_points, device=dev), v=torch.empty(3 * b.n_points, device=dev),
                        q=torch.empty(4 * b.n_frames, device=dev), w=torch.empty(3 * b.n_frames, device=dev))
+            # (waits for the handle's stream before it returns)
             b.adjoint_backward(grad_tips.contiguous().float(), out, rollout=ctx.rollout)
-            torch.cuda.synchronize(dev)
             return (None, out["bend"], out["twist"], out["x"], out["v"], out["q"], out["w"], None, None)
 
     return RodRollout
