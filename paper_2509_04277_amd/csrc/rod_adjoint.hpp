@@ -102,6 +102,12 @@ __global__ __launch_bounds__(64 * W) void rod_adjoint_kernel(
     p = av + 3 * rd.pt_off;
     abv = {p[0], p[1], p[2]};
   }
+  // One slot per lane, several wavefronts: slots pair up across lanes 2 i and 2 i + 1 in the sums
+  // that two slots per lane add up in one lane (the multiplier gradients of a pair, a frame's
+  // adjoint from its two joints), in the same order, so that the gradients of a rod are the
+  // same bits in 2 x 2 and 4 x 1.
+  constexpr bool kPaired = E == 1 && W > 1;
+  const bool odd = (j0 & 1) != 0;
   const int tip_lane = (rd.n - 1) / E, tip_e = (rd.n - 1) % E;
   const bool clamp0 = rd.clamp && g == 0;   // this lane holds the kinematic frame 0 / point 0
   // this lane's multiplier gradients, accumulated in FP64 over all steps newest first (the
@@ -337,6 +343,7 @@ __global__ __launch_bounds__(64 * W) void rod_adjoint_kernel(
       V3 dneg_first = {0.f, 0.f, 0.f};
       Q4 qb_last = {0.f, 0.f, 0.f, 0.f};
       Q4 qb_prev = {0.f, 0.f, 0.f, 0.f};
+      Q4 qs_own = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         const V3 d = Ev[e];                                   // the forward's segment vector
@@ -399,8 +406,16 @@ __global__ __launch_bounds__(64 * W) void rod_adjoint_kernel(
         const V3 mb_ = fma3(rw, tjb - tnb, cross(cb, rv));
         const V3 rvb = {m.y * cb.z - m.z * cb.y + C1 * mb_.x, m.z * cb.x - m.x * cb.z + C1 * mb_.y,
                         m.x * cb.y - m.y * cb.x + C3 * mb_.z};
-        gb += mb_.x * (C1b[e] * rv.x - D0b[e]) + mb_.y * (C1b[e] * rv.y - D1b[e]);
-        gt += mb_.z * (C3b[e] * rv.z - D2b[e]);
+        if constexpr (kPaired) {   // the odd lane adds the pair
+          const float xb = mb_.x * (C1b[e] * rv.x - D0b[e]) + mb_.y * (C1b[e] * rv.y - D1b[e]);
+          const float tt = C3b[e] * rv.z - D2b[e];
+          const float lb = from_pair_lane(xb), lt = from_pair_lane(mb_.z * tt);
+          gb = odd ? lb + xb : 0.f;
+          gt = odd ? __builtin_fmaf(mb_.z, tt, lt) : 0.f;
+        } else {
+          gb += mb_.x * (C1b[e] * rv.x - D0b[e]) + mb_.y * (C1b[e] * rv.y - D1b[e]);
+          gt += mb_.z * (C3b[e] * rv.z - D2b[e]);
+        }
         // rw = qa . qb ; rv = qa_w qb_v - qb_w qa_v - qa_v x qb_v
         const V3 qav = fnma3(qb.w, rvb, cross(rvb, vb));
         const V3 qbv = fma3(q.w, rvb, cross(va, rvb));
@@ -410,7 +425,8 @@ __global__ __launch_bounds__(64 * W) void rod_adjoint_kernel(
                          rwb * q.z + qbv.z};
         qs = q_add(qs, qa_b);
         if (e > 0) qs = q_add(qs, qb_prev);
-        AQn[e] = sel4(L.ok[e], q_add(AQn[e], qs), AQn[e]);
+        if constexpr (kPaired) qs_own = qs;
+        else AQn[e] = sel4(L.ok[e], q_add(AQn[e], qs), AQn[e]);
         qb_prev = qb_b;
         if (e == E - 1) qb_last = qb_b;
       }
@@ -423,7 +439,12 @@ __global__ __launch_bounds__(64 * W) void rod_adjoint_kernel(
         // joint j-1's adjoint for frame j (from below); segment j+1's -d for point j+1 (above)
         const Q4 qfrom = {lo[0], lo[1], lo[2], lo[3]};
         const V3 dfrom = {hi[0], hi[1], hi[2]};
-        if (g != 0) AQn[0] = sel4(L.ok[0], q_add(AQn[0], qfrom), AQn[0]);
+        if constexpr (kPaired) {
+          const Q4 two = odd ? q_add(AQn[0], q_add(qs_own, qfrom)) : q_add(q_add(AQn[0], qs_own), qfrom);
+          AQn[0] = sel4(L.ok[0], g != 0 ? two : q_add(AQn[0], qs_own), AQn[0]);
+        } else if (g != 0) {
+          AQn[0] = sel4(L.ok[0], q_add(AQn[0], qfrom), AQn[0]);
+        }
         AXn[E - 1] = sel(L.ok[E - 1], AXn[E - 1] - dfrom, AXn[E - 1]);
       }
       if (g == 0) abxn = abxn - dneg_first;                  // point 0 is segment 0's left end

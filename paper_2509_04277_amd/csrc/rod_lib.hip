@@ -158,6 +158,7 @@ struct rod_ctx {
   float* d_pub = nullptr;
   int* d_flags = nullptr;
   std::vector<Bucket> buckets;
+  bool crowded = false;   // the default shapes share every SIMD between several wavefronts
   // rod groups (bindings, contact): one or two rods per workgroup, grouped by kernel shape
   std::vector<std::array<int, 2>> bind_pairs;   // as set: bound rod pairs (second = master)
   int bind_mode = 0;
@@ -418,6 +419,20 @@ void default_shape(int n, int* w, int* e) {
   *e = 8;
 }
 
+// Default shape of rod r without kernel features (the variants with features exist in
+// default_shape's only).  Rods of 129 to 256 elements: four wavefronts of one element per lane
+// step one rod fastest (3.1 us inextensible, 0.90 extensible; 2 x 2: 3.5 and 1.17, and the
+// wavefronts of several 2 x 2 workgroups on a compute unit share two of its SIMDs: 4.8), while
+// one wavefront of four elements (3.4 and 1.64) issues half the instructions per element and
+// wins once the SIMDs are shared: 12 rods per compute unit take 9.2 us that way and 15.5 as 4 x 1.
+// Calls of 60 steps, 2 x 2 / 4 x 1 / 1 x 4: 300 rods 232 / 207 / - us, 1200 rods 309 / 299 / 259.
+// (One wavefront of eight elements for 257 to 512 was slower than 4 x 2 at every load: 1000 rods
+// 614 against 327.)
+void plain_shape(const rod_ctx* c, int r, int* w, int* e) {
+  default_shape(c->n[r], w, e);
+  if (c->n[r] > 128 && c->n[r] <= 256) *w = c->crowded ? 1 : 4, *e = c->crowded ? 4 : 1;
+}
+
 // Groups the rods into buckets of equal kernel shape (shape(r) gives it), longest rod first
 // within a bucket, and uploads the resulting rod order.
 template <class ShapeFn>
@@ -459,6 +474,17 @@ rod_status make_buckets(rod_ctx* c, ShapeFn shape) {
                             hipMemcpyHostToDevice, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   return ROD_OK;
+}
+
+// Buckets of the default shapes, for the load that the handle's rods make together.
+rod_status make_plain_buckets(rod_ctx* c) {
+  int cus = 0;
+  HIP_TRY(c, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
+  long long waves = 0;   // in the shapes of shortest step
+  for (int r = 0; r < c->n_rods; ++r)
+    if (c->n[r] <= c->chunk_above) waves += c->n[r] <= 128 ? 1 : c->n[r] <= 1024 ? 4 : 8;
+  c->crowded = waves > 8LL * cus;   // more than two wavefronts per SIMD
+  return make_buckets(c, [&](int r, int* w, int* e) { plain_shape(c, r, w, e); });
 }
 
 // AABB tree of a triangle mesh by volume partitioning: the triangles of a node are split at
@@ -957,7 +983,7 @@ rod_status rebuild_groups(rod_ctx* c) {
       HIP_TRY(c, hipMemsetAsync(c->d_cbuild, 0xff, sizeof(float4) * slots, c->stream));
     }
   }
-  return make_buckets(c, [&](int r, int* w, int* e) { default_shape(c->n[r], w, e); });
+  return make_plain_buckets(c);
 }
 
 // n_steps steps of every rod, spl steps per launch; bucket < 0: all buckets, else that one.
@@ -1272,7 +1298,7 @@ rod_status rod_create(const rod_params* params, int32_t n_rods, void* hip_stream
   {
     rod_status st = setup_long_rods(c);
     if (st != ROD_OK) return cleanup(st);
-    st = make_buckets(c, [&](int r, int* w, int* e) { default_shape(c->n[r], w, e); });
+    st = make_plain_buckets(c);
     if (st != ROD_OK) return cleanup(st);
   }
   {
@@ -1548,7 +1574,7 @@ rod_status rod_set_chunking(rod_ctx* c, int32_t min_elements, int32_t chunk_elem
   c->chunk_above = min_elements;
   c->chunk_target = chunk_elements;
   rod_status st = setup_long_rods(c);
-  if (st == ROD_OK) st = make_buckets(c, [&](int r, int* w, int* e) { default_shape(c->n[r], w, e); });
+  if (st == ROD_OK) st = make_plain_buckets(c);
   if (st != ROD_OK) {   // back to the default split, which rod_create accepted
     for (void** p : {(void**)&c->d_chunks, (void**)&c->d_block_chunk, (void**)&c->d_pub,
                      (void**)&c->d_flags}) {
@@ -1561,7 +1587,7 @@ rod_status rod_set_chunking(rod_ctx* c, int32_t min_elements, int32_t chunk_elem
     c->chunk_target = 0;
     const std::string err = c->err;
     if (setup_long_rods(c) == ROD_OK)
-      (void)make_buckets(c, [&](int r, int* w, int* e) { default_shape(c->n[r], w, e); });
+      (void)make_plain_buckets(c);
     return fail(c, st, err);
   }
   if (c->n_chunks) c->adj_ready = false;   // the adjoint does not step chunked rods
