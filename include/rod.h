@@ -178,11 +178,14 @@ rod_status rod_bucket_info(const rod_ctx* ctx, int32_t bucket, rod_tuning* t, in
 /* Step every rod longer than min_elements (1..2048; default 2048) with the chunked long-rod
  * kernel: one workgroup per chunk, neighbouring chunks trading H = T (2 n_constraint_iters + 2)
  * + 2 (rounded up to even) halo elements per side once every T steps, so a rod of up to 2048
- * elements can also be spread over several compute units.  T (1..16) is the largest for which
- * each halo takes at most a quarter of a 512-element window, 2 H + 2 <= chunk_elements (if
- * set) and the rod needs at most one chunk per compute unit.  chunk_elements sets the owned
- * elements per chunk (0 = the most a 512-element window holds, 512 - 2 H; otherwise clamped to
- * [2 H + 2, 512 - 2 H]; chunk sizes are even and about equal).  The other rods return to their
+ * elements can also be spread over several compute units.  A chunk holds up to 368 elements at 10
+ * constraint iterations (404 for extensible rods) as four overlapping windows of 128, or, where
+ * that would take more than one chunk per compute unit or needs more than 19 iterations, one
+ * window of 512.  T (1..16) is the largest that keeps the rod within one chunk per compute unit,
+ * 2 H + 2 <= chunk_elements (if set), and lets a chunk own H + 2 elements (a window of 512: each
+ * halo a quarter of it at most).  chunk_elements sets the owned elements per chunk (0 = the most
+ * a chunk holds less 2 H; otherwise at least 2 H + 2); chunk sizes are even and about equal.  The
+ * other rods return to their
  * default shapes (as after rod_create).  A held adjoint rollout is dropped if any rod ends up
  * chunked.  All chunks of a handle must be resident on the device together: the handle's
  * chunked steps run after those of any other handle of the process on the same device (stream

@@ -1139,10 +1139,10 @@ __device__ __forceinline__ void clamp_chunk(const RodDev& rd, float (*cbuf)[kCla
   }
 }
 
-// The pose of step s.
-__device__ __forceinline__ void clamp_read(const RodDev& rd, const float (*cbuf)[kClampRow], int s,
+// The pose of step s (driven: clamp_chunk evaluates the rod's poses here; the first row otherwise).
+__device__ __forceinline__ void clamp_read(bool driven, const float (*cbuf)[kClampRow], int s,
                                            V3& xc, Q4& qc, V3& wc) {
-  const float* c = cbuf[rd.driven ? s % kClampChunk : 0];
+  const float* c = cbuf[driven ? s % kClampChunk : 0];
   xc = {c[0], c[1], c[2]};
   qc = {c[3], c[4], c[5], c[6]};
   wc = {c[7], c[8], c[9]};
@@ -1195,7 +1195,7 @@ __global__ __launch_bounds__(64 * W) void rod_resident_kernel(
     }
     if (!(F & kFeatHaptic)) {   // (a mailbox rod's pose is static or comes from its mailbox)
       clamp_chunk(rd, cbuf, s, n_steps, steps_done, rd.driven && rd.clamp, L.g);
-      clamp_read(rd, cbuf, s, xc, qc, wc);
+      clamp_read(rd.driven, cbuf, s, xc, qc, wc);
     }
     if (F & kFeatEnv) L.env_detect(rd, lcand, lrad);   // environment collisions (Fig. 5: detection first)
     V3 xl, xll, vl, wn;
@@ -1610,7 +1610,7 @@ __global__ __launch_bounds__(128 * W) void rod_group_kernel(
     clamp_chunk(rd, cbuf[sub], s, n_steps, steps_done, any_driven, L.g);
     V3 xc, wc;
     Q4 qc;
-    clamp_read(rd, cbuf[sub], s, xc, qc, wc);
+    clamp_read(rd.driven, cbuf[sub], s, xc, qc, wc);
     L.exchange_a(mb[sub], xl, xll, qn, qnl);
     V3 F[E], T[E], Ev[E], fs0, enext;
     L.forces(mb[sub], xl, xll, qn, qnl, F, T, Ev, fs0, enext);
@@ -1779,20 +1779,53 @@ struct GridChunk {
   int32_t left, right;     // neighbour chunk indices (-1 at the rod's ends)
   int32_t halo;            // H
   int32_t every;           // T: steps between halo exchanges (H >= T (2 n_iter + 2))
+  int32_t halo_in;         // rod_window_kernel: halo slots of its wavefronts' windows
+  int32_t every_in;        //   and the steps between their exchanges (divides every)
 };
 
 // Mailbox part: the 20 words (x, v of point j+1; q, w of frame j; the low parts of x and q) of
-// up to pub_slots slots, word-major (word k of slot i at k pub_slots + i), so that a
-// wavefront's store or load of one word covers consecutive addresses.
+// up to pub_slots slots, as ten 64-bit words, word-major (word i of slot o at i pub_slots + o),
+// so that a wavefront's store or load of one word covers consecutive addresses.
 constexpr int kPubSlotFloats = 20;
 
 // Mailbox words are read and written as device-scope relaxed atomics (coherent across the
 // XCDs' L2 caches without writing back or invalidating them); the step flags order them.
-__device__ __forceinline__ void put_coherent(float* p, float v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+template <int W, int E>
+__device__ __forceinline__ void put_slot(float* part, int o, int pub_slots, const RodLane<W, E>& L,
+                                         int e) {
+  const float v[kPubSlotFloats] = {L.X[e].x,  L.X[e].y,  L.X[e].z,  L.XL[e].x, L.XL[e].y,
+                                   L.XL[e].z, L.Vv[e].x, L.Vv[e].y, L.Vv[e].z, L.Om[e].x,
+                                   L.Om[e].y, L.Om[e].z, L.Qf[e].w, L.Qf[e].x, L.Qf[e].y,
+                                   L.Qf[e].z, L.QL[e].w, L.QL[e].x, L.QL[e].y, L.QL[e].z};
+  uint64_t* const d = reinterpret_cast<uint64_t*>(part) + o;
+#pragma unroll
+  for (int i = 0; i < kPubSlotFloats / 2; ++i)
+    __hip_atomic_store(d + i * pub_slots,
+                       (uint64_t)__float_as_uint(v[2 * i + 1]) << 32 | __float_as_uint(v[2 * i]),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ float get_coherent(const float* p) {
-  return __hip_atomic_load(const_cast<float*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+template <int N>   // the first N words
+__device__ __forceinline__ void get_words(const float* part, int o, int pub_slots, float (&v)[N]) {
+  const uint64_t* const d = reinterpret_cast<const uint64_t*>(part) + o;
+#pragma unroll
+  for (int i = 0; i < N / 2; ++i) {
+    const uint64_t w = __hip_atomic_load(const_cast<uint64_t*>(d) + i * pub_slots, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+    v[2 * i] = __uint_as_float((uint32_t)w);
+    v[2 * i + 1] = __uint_as_float((uint32_t)(w >> 32));
+  }
+}
+template <int W, int E>
+__device__ __forceinline__ void get_slot(const float* part, int o, int pub_slots, RodLane<W, E>& L,
+                                         int e) {
+  float v[kPubSlotFloats];
+  get_words(part, o, pub_slots, v);
+  L.X[e] = {v[0], v[1], v[2]};
+  L.XL[e] = {v[3], v[4], v[5]};
+  L.Vv[e] = {v[6], v[7], v[8]};
+  L.Om[e] = {v[9], v[10], v[11]};
+  L.Qf[e] = {v[12], v[13], v[14], v[15]};
+  L.QL[e] = {v[16], v[17], v[18], v[19]};
 }
 
 template <int W, int E>
@@ -1816,6 +1849,7 @@ __global__ __launch_bounds__(64 * W) void rod_grid_kernel(
   const int own_lo = ck.s0 - ck.win0, own_hi = own_lo + ck.c;
   const int H = ck.halo;
   int xk = 0;   // halo exchanges so far in this launch
+  int until = ck.every;
   if (threadIdx.x == 0) abort_flag = 0;
   __syncthreads();
 
@@ -1823,8 +1857,9 @@ __global__ __launch_bounds__(64 * W) void rod_grid_kernel(
     const long long gs = steps_done + s;
     V3 xl, xll, xc, wc;
     Q4 qn, qnl, qc;
-    clamp_chunk(rd, cbuf, s, n_steps, steps_done, rd.driven && rd.clamp && ck.win0 == 0, L.g);
-    clamp_read(rd, cbuf, s, xc, qc, wc);
+    const bool driven = rd.driven && rd.clamp && ck.win0 == 0;
+    clamp_chunk(rd, cbuf, s, n_steps, steps_done, driven, L.g);
+    clamp_read(driven, cbuf, s, xc, qc, wc);
     L.exchange_a(mb, xl, xll, qn, qnl);
     V3 F[E], T[E], Ev[E], fs0, enext;
     L.forces(mb, xl, xll, qn, qnl, F, T, Ev, fs0, enext);
@@ -1832,7 +1867,8 @@ __global__ __launch_bounds__(64 * W) void rod_grid_kernel(
     L.iterate(rd, mb, Ev, enext, []() {});
     L.integrate_velocities(rd, xc, qc);
 
-    if ((s + 1) % ck.every != 0 || s + 1 == n_steps) continue;   // (uniform over the chunk)
+    if (--until > 0 || s + 1 == n_steps) continue;   // (uniform over the chunk)
+    until = ck.every;
     // ---- publish boundary slots: part 0 = owned [0, H), part 1 = owned [c - H - 1, c), into
     // the mailbox buffer of this launch's exchange count parity
     const int pp = xk & 1;
@@ -1844,16 +1880,8 @@ __global__ __launch_bounds__(64 * W) void rod_grid_kernel(
       // (with several chunks c >= 2 H + 2, so no slot is in both parts)
       const bool p0 = L.ok[e] && o >= 0 && o < H && ck.left >= 0;
       const bool p1 = L.ok[e] && o >= ck.c - H - 1 && o < ck.c && ck.right >= 0;
-      if (p0 || p1) {
-        float* d = p0 ? mine + o : mine + pub_slots * kPubSlotFloats + (o - (ck.c - H - 1));
-        const float v[kPubSlotFloats] = {L.X[e].x,  L.X[e].y,  L.X[e].z,  L.Vv[e].x,
-                                         L.Vv[e].y, L.Vv[e].z, L.Qf[e].w, L.Qf[e].x,
-                                         L.Qf[e].y, L.Qf[e].z, L.Om[e].x, L.Om[e].y,
-                                         L.Om[e].z, L.XL[e].x, L.XL[e].y, L.XL[e].z,
-                                         L.QL[e].w, L.QL[e].x, L.QL[e].y, L.QL[e].z};
-#pragma unroll
-        for (int k = 0; k < kPubSlotFloats; ++k) put_coherent(d + k * pub_slots, v[k]);
-      }
+      if (p0) put_slot(mine, o, pub_slots, L, e);
+      if (p1) put_slot(mine + pub_slots * kPubSlotFloats, o - (ck.c - H - 1), pub_slots, L, e);
     }
     // this thread's mailbox stores are complete (device-visible) before the barrier, and the
     // flag is raised after it
@@ -1890,30 +1918,262 @@ __global__ __launch_bounds__(64 * W) void rod_grid_kernel(
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const int o = L.j0 + e - own_lo;
-      const float* src = nullptr;
-      if (L.ok[e] && o < 0 && lp) src = lp + (o + H + 1);   // slot s0 + o
-      if (L.ok[e] && o >= ck.c && rp) src = rp + (o - ck.c);
-      if (src) {
-        float v[kPubSlotFloats];
-#pragma unroll
-        for (int k = 0; k < kPubSlotFloats; ++k) v[k] = get_coherent(src + k * pub_slots);
-        L.X[e] = {v[0], v[1], v[2]};
-        L.Vv[e] = {v[3], v[4], v[5]};
-        L.Qf[e] = {v[6], v[7], v[8], v[9]};
-        L.Om[e] = {v[10], v[11], v[12]};
-        L.XL[e] = {v[13], v[14], v[15]};
-        L.QL[e] = {v[16], v[17], v[18], v[19]};
-      }
+      if (L.ok[e] && o < 0 && lp) get_slot(lp, o + H + 1, pub_slots, L, e);   // slot s0 + o
+      if (L.ok[e] && o >= ck.c && rp) get_slot(rp, o - ck.c, pub_slots, L, e);
     }
     if (L.g == 0 && L.ghost && lp) {   // halo-edge point: point win0 = point of slot win0 - 1
-      const int ps = pub_slots;
-      L.bx = {get_coherent(lp), get_coherent(lp + ps), get_coherent(lp + 2 * ps)};
-      L.bxl = {get_coherent(lp + 13 * ps), get_coherent(lp + 14 * ps), get_coherent(lp + 15 * ps)};
-      L.bv = {get_coherent(lp + 3 * ps), get_coherent(lp + 4 * ps), get_coherent(lp + 5 * ps)};
+      float v[10];
+      get_words(lp, 0, pub_slots, v);
+      L.bx = {v[0], v[1], v[2]};
+      L.bxl = {v[3], v[4], v[5]};
+      L.bv = {v[6], v[7], v[8]};
     }
   }
   const float chk = L.store_state(rd, st, own_lo, own_hi);
   if (!__builtin_isfinite(chk)) atomicOr(status, 1);
+}
+
+// ---------------------------------------------------------------------------------------
+// Long rods, the wavefronts of a workgroup apart: a chunk as above, stepped by kWinWaves
+// wavefronts that each hold a window of 128 slots (two per lane) of their own and step it alone,
+// with lane moves only.  Neighbouring windows overlap by 2 h slots, h = t (2 n_iter + 2) + 2
+// rounded up to even, and every t steps each refills its outer h slots from its neighbours'
+// windows through LDS (one barrier); every T steps (a multiple of t) the chunk's outer H slots
+// come from the neighbouring chunks through memory as in rod_grid_kernel.  The same reasoning
+// holds for both: what a window's edge perturbs moves inwards by 2 n_iter + 2 slots per step.
+// rod_grid_kernel spreads one window over four wavefronts and exchanges edge velocities between
+// them in every constraint iteration, each a barrier with an LDS write and read (330 cycles, an
+// iteration's arithmetic taking 265); a wavefront alone takes 230 cycles per iteration and 0.9
+// instead of 1.3 us for the rest.  The overlap costs capacity (368 slots per workgroup instead
+// of 512 at 10 iterations), which a rod with spare compute units has.
+// Measured (us per step, 1000 per launch): 4096 elements 4.4 -> 3.0 (inextensible), 1.53 ->
+// 1.19 (extensible); 65536 elements 4.54 -> 4.1, 1.56 -> 1.24.
+constexpr int kWinWaves = 4;
+constexpr int kWinSlots = 128;
+constexpr int kWinHaloMax = 42;   // both published ranges lie inside the exact slots
+
+// One slot pair's 40 words as quads, and back.
+__device__ __forceinline__ void pack_pair(const RodLane<1, 2>& L, float4 (&q)[10]) {
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    q[5 * e] = make_float4(L.X[e].x, L.X[e].y, L.X[e].z, L.XL[e].x);
+    q[5 * e + 1] = make_float4(L.XL[e].y, L.XL[e].z, L.Vv[e].x, L.Vv[e].y);
+    q[5 * e + 2] = make_float4(L.Vv[e].z, L.Om[e].x, L.Om[e].y, L.Om[e].z);
+    q[5 * e + 3] = make_float4(L.Qf[e].w, L.Qf[e].x, L.Qf[e].y, L.Qf[e].z);
+    q[5 * e + 4] = make_float4(L.QL[e].w, L.QL[e].x, L.QL[e].y, L.QL[e].z);
+  }
+}
+__device__ __forceinline__ void unpack_pair(RodLane<1, 2>& L, const float4 (&q)[10]) {
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const float4 a = q[5 * e], b = q[5 * e + 1], c = q[5 * e + 2], d = q[5 * e + 3], f = q[5 * e + 4];
+    L.X[e] = {a.x, a.y, a.z};
+    L.XL[e] = {a.w, b.x, b.y};
+    L.Vv[e] = {b.z, b.w, c.x};
+    L.Om[e] = {c.y, c.z, c.w};
+    L.Qf[e] = {d.x, d.y, d.z, d.w};
+    L.QL[e] = {f.x, f.y, f.z, f.w};
+  }
+}
+
+// VEL: every chunk of the launch exchanges between its wavefronts every step, velocities only.
+template <bool VEL>
+__global__ __launch_bounds__(64 * kWinWaves) void rod_window_kernel(
+    const RodDev* __restrict__ rods, const GridChunk* __restrict__ chunks,
+    const int* __restrict__ block_chunk, const float* __restrict__ prm, int prm_stride,
+    StateArrays st, const float* __restrict__ fext, const float* __restrict__ text, int n_steps,
+    long long steps_done, int* __restrict__ status, float* pub, int pub_slots, int n_chunks,
+    int* flags, int spin_limit) {
+  // per exchange parity and wavefront: the slot pairs its lower ([0]) and upper neighbour ([1])
+  // refill from it, quad-major (consecutive lanes' quads are consecutive), and the point below
+  // the upper neighbour's window
+  __shared__ float4 halo[2][kWinWaves][2][10][kWinHaloMax / 2];
+  __shared__ alignas(16) float edge[2][kWinWaves][8];
+  __shared__ alignas(16) float cbuf[kClampChunk][kClampRow];
+  __shared__ Mailbox<1> mb;   // (one wavefront per window: never used)
+  __shared__ int abort_flag;
+  const int ci = block_chunk[blockIdx.x];
+  const GridChunk ck = chunks[ci];
+  const RodDev rd = rods[ck.rod];
+  const int k = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int h = ck.halo_in, stride = kWinSlots - 2 * h;
+  const int nk = ck.nwin <= kWinSlots ? 1 : 1 + (ck.nwin - kWinSlots + stride - 1) / stride;
+  const int wa = k < nk ? k * stride : 0;   // this window's first slot in the chunk's
+  const int nw = k < nk ? min(kWinSlots, ck.nwin - wa) : 0;   // (0: an idle wavefront, same barriers)
+  RodLane<1, 2> L;
+  L.load_params(rd, prm, prm_stride, ck.win0 + wa, nw);
+  L.load_state(rd, st);
+  if (k == 0) clamp_init(rd, cbuf, L.g);
+  if (threadIdx.x == 0) abort_flag = 0;
+  const int own_lo = ck.s0 - ck.win0;   // the chunk's owned slots start here in its window
+  const int H = ck.halo;
+  // slots of this window that no other wavefront answers for
+  const int mine_lo = k == 0 ? 0 : h, mine_hi = k + 1 < nk ? kWinSlots - h : nw;
+  const bool driven = rd.driven && rd.clamp && ck.win0 == 0;
+  int par = 0, xk = 0, until = ck.every, until_in = ck.every_in;
+  // the slot pair this lane publishes (0: to the wavefront below, 1: to the one above), and the
+  // one it refills, in the wavefronts' halo rows; -1: none
+  const int plo = L.g - h / 2, pup = L.g - (kWinSlots - 2 * h) / 2;
+  const bool put_lo = k > 0 && k < nk && plo >= 0 && plo < h / 2;
+  const bool put_up = k + 1 < nk && pup >= 0 && pup < h / 2;
+  const bool get_lo = k > 0 && k < nk && L.g < h / 2;
+  const bool get_up = k + 1 < nk && L.g >= 64 - h / 2;
+  float4* const put = &halo[0][k][put_lo ? 0 : 1][0][put_lo ? plo : put_up ? pup : 0];
+  const float4* const get = get_lo ? &halo[0][k - 1][1][0][L.g]
+                            : get_up ? &halo[0][k + 1][0][0][L.g - (64 - h / 2)] : &halo[0][0][0][0][0];
+  constexpr int kParity = kWinWaves * 2 * 10 * (kWinHaloMax / 2), kQuad = kWinHaloMax / 2;
+  __syncthreads();
+
+  for (int s = 0; s < n_steps; ++s) {
+    const long long gs = steps_done + s;
+    V3 xl, xll, xc, wc;
+    Q4 qn, qnl, qc;
+    clamp_chunk(rd, cbuf, s, n_steps, steps_done, driven, threadIdx.x);
+    clamp_read(driven, cbuf, s, xc, qc, wc);
+    L.exchange_a(mb, xl, xll, qn, qnl);
+    V3 F[2], T[2], Ev[2], fs0, enext;
+    L.forces(mb, xl, xll, qn, qnl, F, T, Ev, fs0, enext);
+    L.integrate_forces(rd, F, T, fs0, xc, wc, fext, text);
+    L.iterate(rd, mb, Ev, enext, []() {});
+    if (VEL && nk > 1) {
+      // ---- the windows' outer velocities, through LDS.  Exchanging every step, the outer slots'
+      // positions and frames were exact when the step began: with the owners' velocities they
+      // are advanced to the owners' values (a third of the words; the exchange is LDS time)
+      if (put_lo || put_up) {
+        const V3 a = L.Vv[0], b = L.Vv[1], c = L.Om[0], d = L.Om[1];
+        const float4 q[3] = {make_float4(a.x, a.y, a.z, b.x), make_float4(b.y, b.z, c.x, c.y),
+                             make_float4(c.z, d.x, d.y, d.z)};
+#pragma unroll
+        for (int i = 0; i < 3; ++i) put[par * kParity + i * kQuad] = q[i];
+        if (h > kWinSlots / 4 && put_lo && put_up) {   // (only then can a pair go both ways)
+#pragma unroll
+          for (int i = 0; i < 3; ++i) halo[par][k][1][i][pup] = q[i];
+        }
+      }
+      if (k + 1 < nk && pup == -1) {
+        float* p = edge[par][k];
+        p[0] = L.Vv[1].x; p[1] = L.Vv[1].y; p[2] = L.Vv[1].z;
+      }
+      __syncthreads();
+      if (get_lo || get_up) {
+        const float4* const g = get + par * kParity;
+        const float4 q0 = g[0], q1 = g[kQuad], q2 = g[2 * kQuad];
+        L.Vv[0] = {q0.x, q0.y, q0.z};
+        L.Vv[1] = {q0.w, q1.x, q1.y};
+        L.Om[0] = {q1.z, q1.w, q2.x};
+        L.Om[1] = {q2.y, q2.z, q2.w};
+      }
+      if (k > 0 && k < nk) {   // the point below the window (lane 0's copy counts)
+        const float* p = edge[par][k - 1];
+        advance_position(L.bx, L.bxl, V3{p[0], p[1], p[2]}, L.dt);
+      }
+      par ^= 1;
+    }
+    L.integrate_velocities(rd, xc, qc);
+    --until;
+    if (--until_in > 0 || s + 1 == n_steps) continue;   // (uniform over the chunk)
+    until_in = ck.every_in;
+
+    // ---- the windows' outer slots, through LDS
+    if (!VEL && nk > 1) {
+      float4 q[10];
+      if (put_lo || put_up) {
+        pack_pair(L, q);
+#pragma unroll
+        for (int i = 0; i < 10; ++i) put[par * kParity + i * kQuad] = q[i];
+        if (h > kWinSlots / 4 && put_lo && put_up) {   // (only then can a pair go both ways)
+#pragma unroll
+          for (int i = 0; i < 10; ++i) halo[par][k][1][i][pup] = q[i];
+        }
+      }
+      if (k + 1 < nk && pup == -1) {
+        float* p = edge[par][k];
+        p[0] = L.X[1].x; p[1] = L.X[1].y; p[2] = L.X[1].z;
+        p[3] = L.XL[1].x; p[4] = L.XL[1].y; p[5] = L.XL[1].z;
+      }
+      __syncthreads();
+      if (get_lo || get_up) {
+#pragma unroll
+        for (int i = 0; i < 10; ++i) q[i] = get[par * kParity + i * kQuad];
+        unpack_pair(L, q);
+      }
+      if (k > 0 && k < nk && L.g == 0) {
+        const float* p = edge[par][k - 1];
+        L.bx = {p[0], p[1], p[2]};
+        L.bxl = {p[3], p[4], p[5]};
+      }
+      par ^= 1;
+    }
+    if (until > 0) continue;
+    until = ck.every;
+    if (ck.left < 0 && ck.right < 0) continue;
+
+    // ---- the chunk's outer slots, through memory (see rod_grid_kernel)
+    const int pp = xk & 1;
+    ++xk;
+    float* mine = pub + ((long long)(pp * n_chunks + ci) * 2) * pub_slots * kPubSlotFloats;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int jl = L.j0 + e;
+      if (!L.ok[e] || jl < mine_lo || jl >= mine_hi) continue;
+      const int o = wa + jl - own_lo;   // owned index
+      if (o >= 0 && o < H && ck.left >= 0) put_slot(mine, o, pub_slots, L, e);
+      if (o >= ck.c - H - 1 && o < ck.c && ck.right >= 0)   // (a short chunk's may be both)
+        put_slot(mine + pub_slots * kPubSlotFloats, o - (ck.c - H - 1), pub_slots, L, e);
+    }
+    // this thread's mailbox stores are complete (device-visible) before the barrier, and the
+    // flag is raised after it
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      __hip_atomic_store(&flags[ci], (int)(gs + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      // wait for both neighbours to have published this step (bounded spin)
+      int spins = 0;
+      for (int side = 0; side < 2; ++side) {
+        const int nb = side == 0 ? ck.left : ck.right;
+        if (nb < 0) continue;
+        while (__hip_atomic_load(&flags[nb], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (int)(gs + 1)) {
+          __builtin_amdgcn_s_sleep(1);
+          if (++spins > spin_limit) {
+            abort_flag = 1;
+            break;
+          }
+        }
+      }
+    }
+    __syncthreads();   // the neighbours' words are read (device-coherent) only after this
+    if (abort_flag) {
+      if (threadIdx.x == 0) atomicOr(status, 4);
+      break;
+    }
+    const float* lp = ck.left >= 0
+        ? pub + ((long long)(pp * n_chunks + ck.left) * 2 + 1) * pub_slots * kPubSlotFloats
+        : nullptr;
+    const float* rp = ck.right >= 0
+        ? pub + ((long long)(pp * n_chunks + ck.right) * 2) * pub_slots * kPubSlotFloats
+        : nullptr;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int o = wa + L.j0 + e - own_lo;
+      const bool below = o < 0 && lp, above = o >= ck.c && rp;
+      if (L.ok[e] && (below || above))
+        get_slot(below ? lp : rp, below ? o + H + 1 : o - ck.c, pub_slots, L, e);
+    }
+    {   // the point below this window, where it lies outside the owned slots
+      const int o = wa - 1 - own_lo;
+      const bool below = o < 0 && lp, above = o >= ck.c && rp;
+      if (L.g == 0 && L.ghost && k < nk && (below || above)) {
+        float v[6];
+        get_words(below ? lp : rp, below ? o + H + 1 : o - ck.c, pub_slots, v);
+        L.bx = {v[0], v[1], v[2]};
+        L.bxl = {v[3], v[4], v[5]};
+      }
+    }
+  }
+  if (nw > 0) {
+    const float chk = L.store_state(rd, st, max(mine_lo, own_lo - wa), min(mine_hi, own_lo + ck.c - wa));
+    if (!__builtin_isfinite(chk)) atomicOr(status, 1);
+  }
 }
 
 }  // namespace corde

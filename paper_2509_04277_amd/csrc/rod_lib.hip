@@ -35,6 +35,7 @@ using GridFn = void (*)(const RodDev*, const corde::GridChunk*, const int*, cons
                         int, int*, int);
 // Long-rod kernel shape: 4 wavefronts (one per SIMD) x 2 elements per lane = 512-slot windows.
 constexpr int kGridWaves = 4, kGridElems = 2;
+static_assert(kGridWaves == corde::kWinWaves, "both long-rod kernels launch the same workgroup");
 constexpr int kResidentMax = 2048;   // longest rod stepped by a single workgroup
 constexpr int kChunkTry = 512;       // rods longer than this may be chunked by rod_autotune
 constexpr int kMaxDevices = 64;       // devices of one process the library keeps state for
@@ -88,7 +89,12 @@ const KernelEntry* find_kernel(int w, int e) {
   return nullptr;
 }
 
-GridFn grid_kernel() { return corde::rod_grid_kernel<kGridWaves, kGridElems>; }
+enum LongKernel { kLongGrid, kLongWindows, kLongWindowsVel };
+GridFn grid_kernel(LongKernel k) {
+  return k == kLongWindowsVel ? corde::rod_window_kernel<true>
+         : k == kLongWindows  ? corde::rod_window_kernel<false>
+                              : corde::rod_grid_kernel<kGridWaves, kGridElems>;
+}
 
 using GroupFn = void (*)(const RodDev*, const corde::GroupDev*, const int*, const float*,
                          float4*, uint16_t*,
@@ -152,6 +158,7 @@ struct rod_ctx {
   int chunk_above = kResidentMax;
   int chunk_target = 0;   // owned elements per chunk (0: as many as a window holds)
   std::vector<int> long_rods;
+  LongKernel long_kernel = kLongGrid;
   int n_chunks = 0, pub_slots = 0;
   corde::GridChunk* d_chunks = nullptr;
   int* d_block_chunk = nullptr;
@@ -571,68 +578,111 @@ rod_status rebucket(rod_ctx* c) {
   });
 }
 
-// Splits every rod longer than chunk_above into chunks owning c slots (even, at least 2 H + 2
-// when there are several, about chunk_target if set) with windows of at most
-// 64 kGridWaves kGridElems slots and H = T (2 n_iter + 2) + 2 (rounded up to even) halo slots
-// per side, enough for T steps between halo exchanges; T (at most kMaxExchangeEvery) is the
-// largest whose halos take at most a quarter of a window each, fit chunk_target if set, and
-// keep the rod within one chunk per compute unit (or 1).  Maps chunks to blocks so that
-// neighbours share an XCD.
+// Appends the chunks of rod r: c owned slots each (even, about chunk_target if set) with windows
+// that add H = T (2 n_iter + 2) + 2 (rounded up to even) halo slots per side, enough for T steps
+// between halo exchanges.  T (at most kMaxExchangeEvery) is the largest whose halos fit
+// chunk_target if set and keep the rod within one chunk per compute unit (or 1).
+// win: windows of rod_window_kernel, four of 128 slots that overlap by 2 h; a chunk then owns at
+// least H + 1 slots, so that halos reach into the next chunk only.  Else one window of
+// 512 slots of rod_grid_kernel, of which the halos take at most a quarter each.
+// Returns false if the rod cannot be split this way.
+bool chunk_rod(const rod_ctx* c, int r, bool win, int cus, std::vector<corde::GridChunk>& ch, int& hmax) {
+  const int n = c->n[r];
+  const int rad = 2 * c->rods[r].n_iter + 2;   // one step's dependency radius in slots
+  auto halo_of = [&](int t) { const int h = t * rad + 2; return h + (h & 1); };
+  // wavefronts exchange every t steps: often enough that the overlaps stay small (the exchange
+  // costs about 500 cycles of LDS time, an overlap slot 1/128 of a wavefront)
+  auto t_in = [&](int T) { return std::min(T, std::max(1, 16 / rad)); };
+  auto slots = [&](int T) {
+    return win ? corde::kWinSlots + (corde::kWinWaves - 1) * (corde::kWinSlots - 2 * halo_of(t_in(T)))
+               : 64 * kGridWaves * kGridElems;
+  };
+  auto least = [&](int h) { return win ? h + 2 : 2 * h + 2; };   // owned slots of a split rod's chunk
+  auto chunks_of = [&](int T) {
+    const int h = halo_of(T);
+    int cm = (slots(T) - 2 * h) & ~1;
+    if (c->chunk_target > 0) cm = std::min(cm, std::max(c->chunk_target, 2 * h + 2) & ~1);
+    if (cm < 2) return INT32_MAX;
+    int g = (n + cm - 1) / cm;
+    while (g > 1 && ((n / g) & ~1) < least(h)) --g;
+    return g;
+  };
+  auto fits = [&](int T) {
+    const int h = halo_of(T);
+    if (!win) return 4 * h <= slots(T);
+    if (halo_of(t_in(T)) > corde::kWinHaloMax || slots(T) - 2 * h < least(h)) return false;
+    // the longest chunk of an even split, with its halos
+    const int g = chunks_of(T), even = (n / g) & ~1;
+    if (g == 1) return n <= slots(T);
+    return even >= least(h) && even + std::min(2, n - even * g) + (g == 2 ? h : 2 * h) <= slots(T);
+  };
+  int T = win ? (fits(1) ? 1 : 0) : 1;
+  for (int t = 2; t <= kMaxExchangeEvery; ++t) {
+    const int h = halo_of(t);
+    if ((c->chunk_target > 0 && 2 * h + 2 > c->chunk_target) || chunks_of(t) > cus) break;
+    if (!fits(t)) {
+      if (!win) break;
+      continue;
+    }
+    if (!win || t % t_in(t) == 0) T = t;
+  }
+  if (T == 0) return false;
+  const int H = halo_of(T), G = chunks_of(T);
+  int base = (n / G) & ~1;
+  int rem = n - base * G;   // distributed two slots at a time
+  int s0 = 0;
+  const int first = (int)ch.size();
+  for (int k = 0; k < G; ++k) {
+    int cc = base;
+    if (rem >= 2) { cc += 2; rem -= 2; }
+    if (k == G - 1) cc = n - s0;
+    corde::GridChunk g{};
+    g.rod = r;
+    g.s0 = s0;
+    g.c = cc;
+    g.win0 = std::max(0, s0 - H);
+    g.nwin = std::min(n, s0 + cc + H) - g.win0;
+    g.left = k > 0 ? first + k - 1 : -1;
+    g.right = k < G - 1 ? first + k + 1 : -1;
+    g.halo = H;
+    g.every = T;
+    g.every_in = t_in(T);
+    g.halo_in = halo_of(g.every_in);
+    if (g.nwin > slots(T) || (G > 1 && cc < least(H))) return false;
+    ch.push_back(g);
+    s0 += cc;
+  }
+  hmax = std::max(hmax, H);
+  return true;
+}
+
+// Splits every rod longer than chunk_above and maps the chunks to blocks so that neighbours share
+// an XCD.  rod_window_kernel steps them where it can hold every rod with at most one chunk per
+// compute unit (beyond that its wavefronts would share SIMDs, and its chunks are the smaller
+// ones); rod_grid_kernel otherwise: more than 19 constraint iterations, or longer rods.
 rod_status setup_long_rods(rod_ctx* c) {
-  std::vector<corde::GridChunk> ch;
-  int hmax = 0;
-  const int K = 64 * kGridWaves * kGridElems;
   int cus = 0;
   HIP_TRY(c, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
   for (int r = 0; r < c->n_rods; ++r) {
-    const int n = c->n[r];
-    if (n <= c->chunk_above) continue;
+    if (c->n[r] <= c->chunk_above) continue;
     if (c->rods[r].damp_int > 0.f)
       return fail(c, ROD_E_UNSUPPORTED, "rods with internal friction cannot be chunked");
     c->long_rods.push_back(r);
-    const int rad = 2 * c->rods[r].n_iter + 2;   // one step's dependency radius in slots
-    auto halo_of = [&](int t) { const int h = t * rad + 2; return h + (h & 1); };
-    auto chunks_of = [&](int h) {
-      int cm = (K - 2 * h) & ~1;
-      if (c->chunk_target > 0) cm = std::min(cm, std::max(c->chunk_target, 2 * h + 2) & ~1);
-      int g = (n + cm - 1) / cm;
-      while (g > 1 && ((n / g) & ~1) < 2 * h + 2) --g;
-      return g;
-    };
-    int T = 1;
-    for (int t = 2; t <= kMaxExchangeEvery; ++t) {
-      const int h = halo_of(t);
-      if (4 * h > K || (c->chunk_target > 0 && 2 * h + 2 > c->chunk_target) || chunks_of(h) > cus)
-        break;
-      T = t;
-    }
-    const int H = halo_of(T);
-    hmax = std::max(hmax, H);
-    const int G = chunks_of(H);
-    int base = (n / G) & ~1;
-    int rem = n - base * G;   // distributed two slots at a time
-    int s0 = 0;
-    const int first = (int)ch.size();
-    for (int k = 0; k < G; ++k) {
-      int cc = base;
-      if (rem >= 2) { cc += 2; rem -= 2; }
-      if (k == G - 1) cc = n - s0;
-      corde::GridChunk g{};
-      g.rod = r;
-      g.s0 = s0;
-      g.c = cc;
-      g.win0 = std::max(0, s0 - H);
-      g.nwin = std::min(n, s0 + cc + H) - g.win0;
-      g.left = k > 0 ? first + k - 1 : -1;
-      g.right = k < G - 1 ? first + k + 1 : -1;
-      g.halo = H;
-      g.every = T;
-      if (g.nwin > K || (G > 1 && cc < 2 * H + 2))
+  }
+  std::vector<corde::GridChunk> ch;
+  int hmax = 0;
+  bool windows = true, vel = true;
+  for (int r : c->long_rods) windows = windows && chunk_rod(c, r, true, cus, ch, hmax);
+  windows = windows && (int)ch.size() <= cus;
+  for (const auto& g : ch) vel = vel && g.every_in == 1;
+  c->long_kernel = !windows ? kLongGrid : vel ? kLongWindowsVel : kLongWindows;
+  if (!windows) {
+    ch.clear();
+    hmax = 0;
+    for (int r : c->long_rods)
+      if (!chunk_rod(c, r, false, cus, ch, hmax))
         return fail(c, ROD_E_UNSUPPORTED, "rod " + std::to_string(r) +
                     ": too many constraint iterations to split it into chunks");
-      ch.push_back(g);
-      s0 += cc;
-    }
   }
   c->n_chunks = (int)ch.size();
   if (!c->n_chunks) return ROD_OK;
@@ -662,7 +712,8 @@ rod_status setup_long_rods(rod_ctx* c) {
   HIP_TRY(c, hipMemset(c->d_flags, 0, sizeof(int) * G));
   // every chunk must be resident at once (the chunks wait on each other)
   int per_cu = 0;
-  HIP_TRY(c, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, grid_kernel(), 64 * kGridWaves, 0));
+  HIP_TRY(c, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, grid_kernel(c->long_kernel),
+                                                          64 * kGridWaves, 0));
   if ((long long)per_cu * cus < G)
     return fail(c, ROD_E_UNSUPPORTED, "long rods need " + std::to_string(G) +
                 " resident workgroups, the device holds " + std::to_string(per_cu * cus));
@@ -691,7 +742,7 @@ rod_status launch_long(rod_ctx* c, StateArrays sa, int ks, long long done, hipSt
   int* fl = c->d_flags;
   void* args[] = {&rods, &chunks, &bc, &prm, &stride, &sa, &fe, &te, &ks, &done,
                   &st, &pub, &ps, &nc, &fl, &spin};
-  HIP_TRY(c, hipLaunchKernel((const void*)grid_kernel(), dim3(c->n_chunks), dim3(64 * kGridWaves),
+  HIP_TRY(c, hipLaunchKernel((const void*)grid_kernel(c->long_kernel), dim3(c->n_chunks), dim3(64 * kGridWaves),
                              args, 0, stream));
   return ROD_OK;
 }
