@@ -115,7 +115,9 @@ typedef struct rod_tuning {
  * coefficients (masses, inertias, stiffnesses of eqs. (2), (3), (8)) in FP64 on the host.
  * Rods of up to 2048 elements are stepped by one workgroup each; longer rods are split into
  * chunks of up to about 500 elements, one workgroup per chunk, that exchange halos once every
- * few steps (see rod_set_chunking)
+ * few steps (see rod_set_chunking); so are shorter rods of a handle (more than 128 elements, or 256
+ * with fewer than five constraint iterations) while it holds few plain rods and neither
+ * rod_set_tuning, rod_set_chunking nor rod_autotune was called: the states are the same bits
  * (all chunks of a handle must be resident on the device at once: ROD_E_UNSUPPORTED if not,
  * and for any rod longer than 131072 elements).
  * The state is zero until rod_set_state().  Errors: INVALID (bad sizes/values), NOMEM,
@@ -163,6 +165,7 @@ rod_status rod_get_time(const rod_ctx* ctx, double* t, int64_t* steps);
  * smallest shape that holds each rod); rod_step() launches every bucket per chunk of steps.
  * Rods longer than 2048 elements form one last bucket stepped by the chunked kernel (shape
  * 4 waves x 2 elements per lane per chunk), which tuning does not change.
+ * (A handle whose shapes were never set may step its rods as chunks all the same, see rod_create.)
  * rod_set_tuning() puts all other rods into one bucket of the given shape (waves in
  * {1,2,4,8,16}, elems_per_lane in {1,2,4,8} as built; ROD_E_UNSUPPORTED if not built or too
  * small for the longest of them).  rod_get_tuning() reports the first bucket's shape and the
@@ -187,10 +190,11 @@ rod_status rod_bucket_info(const rod_ctx* ctx, int32_t bucket, rod_tuning* t, in
  * a chunk holds less 2 H; otherwise at least 2 H + 2); chunk sizes are even and about equal.  The
  * other rods return to their
  * default shapes (as after rod_create).  A held adjoint rollout is dropped if any rod ends up
- * chunked.  All chunks of a handle must be resident on the device together: the handle's
- * chunked steps run after those of any other handle of the process on the same device (stream
- * order through one event per device), and a chunk whose neighbour does not arrive gives up
- * after a bounded wait (rod_sync then reports ROD_E_TIMEOUT), for instance when another
+ * chunked.  All chunks of a handle must be resident on the device together: chunked steps of the
+ * process's handles run side by side on a device while their chunks together are at most its
+ * compute units, else after each other (stream order through the handles' events), and a chunk
+ * whose neighbour does not arrive gives up after a bounded wait of several seconds (rod_sync
+ * then reports ROD_E_TIMEOUT), for instance when another
  * process holds the compute units.  Errors: INVALID, UNSUPPORTED (too many constraint
  * iterations to split a rod, or more chunks than the device holds at once; the default split
  * is then restored), DEVICE. */

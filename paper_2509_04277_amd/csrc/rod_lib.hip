@@ -129,6 +129,7 @@ thread_local std::string g_last_error;
 
 struct rod_ctx {
   int device = 0;
+  int cus = 0;   // the device's compute units
   hipStream_t stream = nullptr;
   int n_rods = 0;
   int max_n = 0;
@@ -157,13 +158,21 @@ struct rod_ctx {
   // long rods (more than chunk_above elements): chunked, one workgroup per chunk
   int chunk_above = kResidentMax;
   int chunk_target = 0;   // owned elements per chunk (0: as many as a window holds)
-  std::vector<int> long_rods;
-  LongKernel long_kernel = kLongGrid;
-  int n_chunks = 0, pub_slots = 0;
-  corde::GridChunk* d_chunks = nullptr;
-  int* d_block_chunk = nullptr;
-  float* d_pub = nullptr;
-  int* d_flags = nullptr;
+  struct LongSet {   // rods that step as chunks, one launch
+    std::vector<int> rods;
+    LongKernel kernel = kLongGrid;
+    int n_chunks = 0, pub_slots = 0;
+    bool coupled = false;   // some rod has several chunks (they wait on each other)
+    corde::GridChunk* d_chunks = nullptr;
+    int* d_block_chunk = nullptr;
+    float* d_pub = nullptr;
+    int* d_flags = nullptr;
+  };
+  LongSet lng;      // the rods above the chunking threshold
+  // All rods of the handle as window chunks, for steps whose shapes the caller left to the library
+  // (see spread_rods); empty where that is not the faster way.
+  LongSet spread;
+  bool own_shapes = true;   // neither rod_set_tuning, rod_set_chunking nor rod_autotune was called
   std::vector<Bucket> buckets;
   bool crowded = false;   // the default shapes share every SIMD between several wavefronts
   // rod groups (bindings, contact): one or two rods per workgroup, grouped by kernel shape
@@ -485,12 +494,10 @@ rod_status make_buckets(rod_ctx* c, ShapeFn shape) {
 
 // Buckets of the default shapes, for the load that the handle's rods make together.
 rod_status make_plain_buckets(rod_ctx* c) {
-  int cus = 0;
-  HIP_TRY(c, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
   long long waves = 0;   // in the shapes of shortest step
   for (int r = 0; r < c->n_rods; ++r)
     if (c->n[r] <= c->chunk_above) waves += c->n[r] <= 128 ? 1 : c->n[r] <= 1024 ? 4 : 8;
-  c->crowded = waves > 8LL * cus;   // more than two wavefronts per SIMD
+  c->crowded = waves > 8LL * c->cus;   // more than two wavefronts per SIMD
   return make_buckets(c, [&](int r, int* w, int* e) { plain_shape(c, r, w, e); });
 }
 
@@ -626,8 +633,12 @@ bool chunk_rod(const rod_ctx* c, int r, bool win, int cus, std::vector<corde::Gr
     }
     if (!win || t % t_in(t) == 0) T = t;
   }
+  if (win && c->chunk_target == 0 && halo_of(t_in(kMaxExchangeEvery)) <= corde::kWinHaloMax &&
+      n <= slots(kMaxExchangeEvery))
+    T = kMaxExchangeEvery;   // one chunk, whose halos do not matter
   if (T == 0) return false;
-  const int H = halo_of(T), G = chunks_of(T);
+  const bool one = win && c->chunk_target == 0 && n <= slots(T);
+  const int H = halo_of(T), G = one ? 1 : chunks_of(T);
   int base = (n / G) & ~1;
   int rem = n - base * G;   // distributed two slots at a time
   int s0 = 0;
@@ -645,7 +656,7 @@ bool chunk_rod(const rod_ctx* c, int r, bool win, int cus, std::vector<corde::Gr
     g.left = k > 0 ? first + k - 1 : -1;
     g.right = k < G - 1 ? first + k + 1 : -1;
     g.halo = H;
-    g.every = T;
+    g.every = T;   // (a multiple of every_in unless the rod is one chunk)
     g.every_in = t_in(T);
     g.halo_in = halo_of(g.every_in);
     if (g.nwin > slots(T) || (G > 1 && cc < least(H))) return false;
@@ -656,39 +667,22 @@ bool chunk_rod(const rod_ctx* c, int r, bool win, int cus, std::vector<corde::Gr
   return true;
 }
 
-// Splits every rod longer than chunk_above and maps the chunks to blocks so that neighbours share
-// an XCD.  rod_window_kernel steps them where it can hold every rod with at most one chunk per
-// compute unit (beyond that its wavefronts would share SIMDs, and its chunks are the smaller
-// ones); rod_grid_kernel otherwise: more than 19 constraint iterations, or longer rods.
-rod_status setup_long_rods(rod_ctx* c) {
-  int cus = 0;
-  HIP_TRY(c, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
-  for (int r = 0; r < c->n_rods; ++r) {
-    if (c->n[r] <= c->chunk_above) continue;
-    if (c->rods[r].damp_int > 0.f)
-      return fail(c, ROD_E_UNSUPPORTED, "rods with internal friction cannot be chunked");
-    c->long_rods.push_back(r);
-  }
-  std::vector<corde::GridChunk> ch;
-  int hmax = 0;
-  bool windows = true, vel = true;
-  for (int r : c->long_rods) windows = windows && chunk_rod(c, r, true, cus, ch, hmax);
-  windows = windows && (int)ch.size() <= cus;
-  for (const auto& g : ch) vel = vel && g.every_in == 1;
-  c->long_kernel = !windows ? kLongGrid : vel ? kLongWindowsVel : kLongWindows;
-  if (!windows) {
-    ch.clear();
-    hmax = 0;
-    for (int r : c->long_rods)
-      if (!chunk_rod(c, r, false, cus, ch, hmax))
-        return fail(c, ROD_E_UNSUPPORTED, "rod " + std::to_string(r) +
-                    ": too many constraint iterations to split it into chunks");
-  }
-  c->n_chunks = (int)ch.size();
-  if (!c->n_chunks) return ROD_OK;
-  c->pub_slots = hmax + 1;
+void free_long_set(rod_ctx::LongSet& l) {
+  for (void* p : {(void*)l.d_chunks, (void*)l.d_block_chunk, (void*)l.d_pub, (void*)l.d_flags})
+    if (p) (void)hipFree(p);
+  l = rod_ctx::LongSet{};
+}
+
+// Uploads the chunks ch of l.rods (halos of at most hmax slots), mapped to blocks so that
+// neighbours share an XCD, and checks that the device holds all of them at once.
+rod_status place_chunks(rod_ctx* c, rod_ctx::LongSet& l, const std::vector<corde::GridChunk>& ch,
+                        int hmax, int cus) {
+  l.n_chunks = (int)ch.size();
+  if (!l.n_chunks) return ROD_OK;
+  l.pub_slots = hmax + 1;
+  for (const auto& g : ch) l.coupled = l.coupled || g.left >= 0 || g.right >= 0;
   // blocks are dealt to the 8 XCDs round-robin: give XCD x the chunks [x G / 8, (x+1) G / 8)
-  const int G = c->n_chunks;
+  const int G = l.n_chunks;
   std::vector<int> block_chunk(G);
   {
     std::vector<int> per_xcd(8, 0), start(9, 0);
@@ -702,22 +696,96 @@ rod_status setup_long_rods(rod_ctx* c) {
     }
   }
   auto dm = [&](void** p, size_t n) { return hipMalloc(p, std::max<size_t>(n, 4)) == hipSuccess; };
-  if (!dm((void**)&c->d_chunks, sizeof(corde::GridChunk) * G) ||
-      !dm((void**)&c->d_block_chunk, sizeof(int) * G) ||
-      !dm((void**)&c->d_pub, sizeof(float) * 2 * (size_t)G * 2 * c->pub_slots * corde::kPubSlotFloats) ||
-      !dm((void**)&c->d_flags, sizeof(int) * G))
+  if (!dm((void**)&l.d_chunks, sizeof(corde::GridChunk) * G) ||
+      !dm((void**)&l.d_block_chunk, sizeof(int) * G) ||
+      !dm((void**)&l.d_pub, sizeof(float) * 2 * (size_t)G * 2 * l.pub_slots * corde::kPubSlotFloats) ||
+      !dm((void**)&l.d_flags, sizeof(int) * G))
     return fail(c, ROD_E_NOMEM, "long-rod buffers");
-  HIP_TRY(c, hipMemcpy(c->d_chunks, ch.data(), sizeof(corde::GridChunk) * G, hipMemcpyHostToDevice));
-  HIP_TRY(c, hipMemcpy(c->d_block_chunk, block_chunk.data(), sizeof(int) * G, hipMemcpyHostToDevice));
-  HIP_TRY(c, hipMemset(c->d_flags, 0, sizeof(int) * G));
+  HIP_TRY(c, hipMemcpy(l.d_chunks, ch.data(), sizeof(corde::GridChunk) * G, hipMemcpyHostToDevice));
+  HIP_TRY(c, hipMemcpy(l.d_block_chunk, block_chunk.data(), sizeof(int) * G, hipMemcpyHostToDevice));
+  HIP_TRY(c, hipMemset(l.d_flags, 0, sizeof(int) * G));
   // every chunk must be resident at once (the chunks wait on each other)
   int per_cu = 0;
-  HIP_TRY(c, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, grid_kernel(c->long_kernel),
+  HIP_TRY(c, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, grid_kernel(l.kernel),
                                                           64 * kGridWaves, 0));
   if ((long long)per_cu * cus < G)
     return fail(c, ROD_E_UNSUPPORTED, "long rods need " + std::to_string(G) +
                 " resident workgroups, the device holds " + std::to_string(per_cu * cus));
   return ROD_OK;
+}
+
+// The window kernel for chunks ch, or kLongGrid if they are more than the compute units (beyond
+// that their wavefronts would share SIMDs, and the windows' chunks are the smaller ones).
+LongKernel window_kernel(const std::vector<corde::GridChunk>& ch, int cus) {
+  if ((int)ch.size() > cus) return kLongGrid;
+  for (const auto& g : ch)
+    if (g.every_in != 1) return kLongWindows;
+  return kLongWindowsVel;
+}
+
+// Splits every rod longer than chunk_above.  rod_window_kernel steps them where it can hold every
+// rod with at most one chunk per compute unit; rod_grid_kernel otherwise: more than 19
+// constraint iterations, or longer rods.
+rod_status setup_long_rods(rod_ctx* c) {
+  const int cus = c->cus;
+  rod_ctx::LongSet& l = c->lng;
+  for (int r = 0; r < c->n_rods; ++r) {
+    if (c->n[r] <= c->chunk_above) continue;
+    if (c->rods[r].damp_int > 0.f)
+      return fail(c, ROD_E_UNSUPPORTED, "rods with internal friction cannot be chunked");
+    l.rods.push_back(r);
+  }
+  std::vector<corde::GridChunk> ch;
+  int hmax = 0;
+  bool windows = true;
+  for (int r : l.rods) windows = windows && chunk_rod(c, r, true, cus, ch, hmax);
+  l.kernel = windows ? window_kernel(ch, cus) : kLongGrid;
+  if (l.kernel == kLongGrid) {
+    ch.clear();
+    hmax = 0;
+    for (int r : l.rods)
+      if (!chunk_rod(c, r, false, cus, ch, hmax))
+        return fail(c, ROD_E_UNSUPPORTED, "rod " + std::to_string(r) +
+                    ": too many constraint iterations to split it into chunks");
+  }
+  return place_chunks(c, l, ch, hmax, cus);
+}
+
+// Plans the handle's rods as window chunks (c->spread) where that steps them faster than one
+// workgroup of a resident shape each: plain rods, few enough for one chunk per compute unit, of
+// more than 128 elements with five or more constraint iterations (the windows exchange once per
+// step, the resident shapes once per iteration), else of more than 256.  Calls of 10 steps,
+// resident -> spread: inextensible 200 elements 43 -> 37 us, 300 50 -> 38, 512 50 -> 42, 700 66 -> 42;
+// extensible 260 25.8 -> 25.1, 400 26.1 -> 25.8, 700 36 -> 26; of 100 steps: inextensible 256 322 ->
+// 243, 1000 520 -> 308, 2048 840 -> 316, extensible 300 145 -> 122, 1000 222 -> 134, 2048 346 -> 137;
+// 30 rods of 300 to 512, 60 steps: 242 -> 213.
+rod_status spread_rods(rod_ctx* c) {
+  std::vector<corde::GridChunk> ch;
+  int hmax = 0;
+  for (int r = 0; r < c->n_rods; ++r) {
+    const int n = c->n[r];
+    if (n > kResidentMax || n <= (c->rods[r].n_iter >= 5 ? 128 : 256) || c->rods[r].damp_int > 0.f ||
+        !chunk_rod(c, r, true, c->cus, ch, hmax) || (int)ch.size() > c->cus)
+      return ROD_OK;
+  }
+  for (int r = 0; r < c->n_rods; ++r) c->spread.rods.push_back(r);
+  c->spread.kernel = window_kernel(ch, c->cus);
+  if (place_chunks(c, c->spread, ch, hmax, c->cus) != ROD_OK) free_long_set(c->spread);
+  return ROD_OK;
+}
+
+// Whether the next step runs on c->spread: nothing set that its kernel does not do, and no stream
+// capture (the order among chunked runs is kept by events of other streams).
+bool spread_now(const rod_ctx* c) {
+  if (!c->spread.n_chunks || !c->own_shapes || c->lng.n_chunks || !c->groups.empty() || c->n_haptic ||
+      c->env_nodes)
+    return false;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return cap == hipStreamCaptureStatusNone;
 }
 
 // Chunked long rods: one ordinary launch of ks steps.  The chunks wait on their neighbours, so
@@ -726,44 +794,97 @@ rod_status setup_long_rods(rod_ctx* c) {
 // one on the same device (LongGate), so two such grids never hold the compute units against
 // each other.  A workgroup whose neighbour still does not arrive gives up after a bounded wait
 // (status 4) instead of hanging.
-rod_status launch_long(rod_ctx* c, StateArrays sa, int ks, long long done, hipStream_t stream) {
-  if (!c->n_chunks) return ROD_OK;
-  int spin = 1 << 22;
-  const RodDev* rods = c->d_rods;
-  const corde::GridChunk* chunks = c->d_chunks;
-  const int* bc = c->d_block_chunk;
-  const float* prm = c->d_prm;
-  int stride = c->prm_stride;
-  const float* fe = c->d_fext;
-  const float* te = c->d_text;
-  int* st = c->d_status;
-  float* pub = c->d_pub;
-  int ps = c->pub_slots, nc = c->n_chunks;
-  int* fl = c->d_flags;
-  void* args[] = {&rods, &chunks, &bc, &prm, &stride, &sa, &fe, &te, &ks, &done,
-                  &st, &pub, &ps, &nc, &fl, &spin};
-  HIP_TRY(c, hipLaunchKernel((const void*)grid_kernel(c->long_kernel), dim3(c->n_chunks), dim3(64 * kGridWaves),
-                             args, 0, stream));
+rod_status launch_long(rod_ctx* c, const rod_ctx::LongSet& l, StateArrays sa, int ks, long long done,
+                       hipStream_t stream) {
+  if (!l.n_chunks) return ROD_OK;
+  // polls of about a microsecond (rods that the library spread by itself wait longer before they
+  // give up: one workgroup would not have had to)
+  const int spin = &l == &c->spread ? 1 << 25 : 1 << 22;
+  hipLaunchKernelGGL(grid_kernel(l.kernel), dim3(l.n_chunks), dim3(64 * kGridWaves), 0, stream,
+                     c->d_rods, l.d_chunks, l.d_block_chunk, c->d_prm, c->prm_stride, sa, c->d_fext,
+                     c->d_text, ks, done, c->d_status, l.d_pub, l.pub_slots, l.n_chunks, l.d_flags,
+                     spin);
+  HIP_TRY(c, hipGetLastError());
   return ROD_OK;
 }
 
-// Orders the chunked runs of all handles of the process, per device: a run waits for the
-// event recorded after the previous one (if another stream recorded it) and records it anew.
-// The events live until the process ends.
+// Keeps the chunked runs of all handles of the process that may be in flight together, per device,
+// within one workgroup per compute unit, so that no two grids hold the compute units against
+// each other: a run whose chunks do not fit beside those of other streams' unfinished runs waits
+// for them (their events; runs on one stream follow each other anyway).  Runs that fit go on
+// side by side.  rod_destroy takes the handle's event out.
 struct LongGate {
+  struct Run {
+    hipStream_t stream = nullptr;
+    hipEvent_t done = nullptr;   // the end event of the stream's last chunked run (a handle's ev1)
+    int chunks = 0;              // the largest of its unfinished runs; 0: finished
+  };
   std::mutex m;
-  hipEvent_t ev[kMaxDevices] = {};
-  hipStream_t last[kMaxDevices] = {};   // stream of the last record (valid where rec)
-  bool rec[kMaxDevices] = {};
+  std::vector<Run> runs[kMaxDevices];
 };
 LongGate& long_gate() {
   static LongGate* g = new LongGate;   // never destroyed: handles may outlive static teardown
   return *g;
 }
 
+// State arrays of a launch on the handle's own state.
+StateArrays handle_state(rod_ctx* c) { return {c->d_x, c->d_v, c->d_q, c->d_w, c->d_xl, c->d_ql}; }
+
+// Steps the chunks of l on the handle's stream, spl steps per launch, and records ev1 after
+// them if they are coupled.
+rod_status step_long(rod_ctx* c, const rod_ctx::LongSet& l, int n_steps, int spl, int* launches) {
+  auto run = [&]() -> rod_status {
+    for (int done = 0; done < n_steps; done += spl) {
+      const int ks = std::min(spl, n_steps - done);
+      rod_status rs = launch_long(c, l, handle_state(c), ks, c->steps_done + done, c->stream);
+      if (rs != ROD_OK) return rs;
+      ++*launches;
+    }
+    return ROD_OK;
+  };
+  if (!l.coupled) return run();   // chunks that wait for nothing need no company
+  const int dev = c->device;
+  if (dev < 0 || dev >= kMaxDevices) return fail(c, ROD_E_DEVICE, "device index out of range");
+  LongGate& g = long_gate();
+  std::lock_guard<std::mutex> lock(g.m);
+  auto& runs = g.runs[dev];
+  for (size_t i = runs.size(); i-- > 0;) {   // finished runs of other streams leave
+    if (runs[i].stream == c->stream || hipEventQuery(runs[i].done) != hipSuccess) continue;
+    runs[i] = runs.back();
+    runs.pop_back();
+  }
+  (void)hipGetLastError();   // (hipErrorNotReady of the unfinished ones)
+  LongGate::Run* mine = nullptr;
+  int others = 0;
+  for (LongGate::Run& o : runs) {
+    if (o.stream == c->stream) mine = &o;
+    else others += o.chunks;
+  }
+  if (others + l.n_chunks > c->cus)
+    for (const LongGate::Run& o : runs)
+      if (o.stream != c->stream) HIP_TRY(c, hipStreamWaitEvent(c->stream, o.done, 0));
+  const rod_status st = run();
+  HIP_TRY(c, hipEventRecord(c->ev1, c->stream));
+  // (of several handles on one stream the last one's event stands for all)
+  if (mine) *mine = {c->stream, c->ev1, std::max(mine->chunks, l.n_chunks)};
+  else runs.push_back({c->stream, c->ev1, l.n_chunks});
+  return st;
+}
+
+// Takes a handle's event out of the gate (its stream's work is done).
+void leave_long_gate(rod_ctx* c) {
+  if (c->device < 0 || c->device >= kMaxDevices) return;
+  LongGate& g = long_gate();
+  std::lock_guard<std::mutex> lock(g.m);
+  auto& runs = g.runs[c->device];
+  for (size_t i = runs.size(); i-- > 0;)
+    if (runs[i].done == c->ev1) runs.erase(runs.begin() + i);
+}
+
 // Zeroes the long-rod step flags (whenever the step counter restarts).
 rod_status reset_flags(rod_ctx* c) {
-  if (c->d_flags) HIP_TRY(c, hipMemsetAsync(c->d_flags, 0, sizeof(int) * c->n_chunks, c->stream));
+  for (const rod_ctx::LongSet* l : {&c->lng, &c->spread})
+    if (l->d_flags) HIP_TRY(c, hipMemsetAsync(l->d_flags, 0, sizeof(int) * l->n_chunks, c->stream));
   return ROD_OK;
 }
 
@@ -896,10 +1017,6 @@ rod_status move_or_copy(rod_ctx* c, Mover& mv, float* dst, const float* src, lon
   HIP_TRY(c, hipMemcpyAsync(dst, src, sizeof(float) * n, k, c->stream));
   return ROD_OK;
 }
-
-// State arrays of a launch: the handle's own, or (rod_step_state_noalloc) the caller's with
-// the low parts in the device's scratch array.
-StateArrays handle_state(rod_ctx* c) { return {c->d_x, c->d_v, c->d_q, c->d_w, c->d_xl, c->d_ql}; }
 
 rod_status launch_bucket(rod_ctx* c, const rod_ctx::Bucket& b, int ks, long long done,
                          hipStream_t stream, const StateArrays& sp) {
@@ -1039,6 +1156,17 @@ rod_status rebuild_groups(rod_ctx* c) {
 
 // n_steps steps of every rod, spl steps per launch; bucket < 0: all buckets, else that one.
 rod_status launch_steps(rod_ctx* c, int n_steps, int spl, bool time_it, int bucket = -1) {
+  if (bucket < 0 && spread_now(c)) {
+    if (time_it) HIP_TRY(c, hipEventRecord(c->ev0, c->stream));
+    int launches = 0;
+    const rod_status rs = step_long(c, c->spread, n_steps, spl, &launches);
+    if (rs != ROD_OK) return rs;
+    if (time_it && !c->spread.coupled) HIP_TRY(c, hipEventRecord(c->ev1, c->stream));
+    c->timed = time_it;
+    c->last_launches = launches;
+    c->steps_done += n_steps;
+    return ROD_OK;
+  }
   // the buckets (and the bound-pair buckets) are independent: with several, each steps on its
   // own stream (forked from and joined back to the handle's stream)
   const int nb = bucket >= 0 ? 1 : (int)c->buckets.size();
@@ -1080,26 +1208,13 @@ rod_status launch_steps(rod_ctx* c, int n_steps, int spl, bool time_it, int buck
     }
   }
   // chunked long rods on the handle's stream, after the buckets (all of a chunked grid's
-  // workgroups must be resident together), and after any other handle's chunked run
-  if (bucket < 0 && c->n_chunks) {
-    const int dev = c->device;
-    if (dev < 0 || dev >= kMaxDevices) return fail(c, ROD_E_DEVICE, "device index out of range");
-    LongGate& g = long_gate();
-    std::lock_guard<std::mutex> lock(g.m);
-    if (!g.ev[dev]) HIP_TRY(c, hipEventCreateWithFlags(&g.ev[dev], hipEventDisableTiming));
-    if (g.rec[dev] && g.last[dev] != c->stream) HIP_TRY(c, hipStreamWaitEvent(c->stream, g.ev[dev], 0));
-    for (int done = 0; done < n_steps; done += spl) {
-      const int ks = std::min(spl, n_steps - done);
-      rod_status rs = launch_long(c, handle_state(c), ks, c->steps_done + done,
-                                  c->stream);
-      if (rs != ROD_OK) return rs;
-      ++launches;
-    }
-    HIP_TRY(c, hipEventRecord(g.ev[dev], c->stream));
-    g.last[dev] = c->stream;
-    g.rec[dev] = true;
+  // workgroups must be resident together)
+  if (bucket < 0 && c->lng.n_chunks) {
+    rod_status rs = step_long(c, c->lng, n_steps, spl, &launches);
+    if (rs != ROD_OK) return rs;
   }
-  if (time_it) HIP_TRY(c, hipEventRecord(c->ev1, c->stream));
+  const bool recorded = bucket < 0 && c->lng.n_chunks && c->lng.coupled;   // by step_long
+  if (time_it && !recorded) HIP_TRY(c, hipEventRecord(c->ev1, c->stream));
   c->timed = time_it;
   c->last_launches = launches;
   c->steps_done += n_steps;
@@ -1271,6 +1386,8 @@ rod_status rod_create(const rod_params* params, int32_t n_rods, void* hip_stream
   };
   hipError_t e = hipGetDevice(&c->device);
   if (e != hipSuccess) return cleanup(hip_fail(nullptr, e, "hipGetDevice"));
+  e = hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, c->device);
+  if (e != hipSuccess) return cleanup(hip_fail(nullptr, e, "hipDeviceGetAttribute"));
   c->stream = (hipStream_t)hip_stream;
   c->n_rods = n_rods;
   c->max_n = max_n;
@@ -1351,6 +1468,8 @@ rod_status rod_create(const rod_params* params, int32_t n_rods, void* hip_stream
     if (st != ROD_OK) return cleanup(st);
     st = make_plain_buckets(c);
     if (st != ROD_OK) return cleanup(st);
+    st = spread_rods(c);
+    if (st != ROD_OK) return cleanup(st);
   }
   {
     // set-up of rod_step_state_noalloc on this device (a failure is reported by that call)
@@ -1371,11 +1490,13 @@ rod_status rod_destroy(rod_ctx* c) {
                   (void*)c->d_status, (void*)c->d_rod_ids, (void*)c->d_ckpt, (void*)c->d_traj,
                   (void*)c->d_tips, (void*)c->d_dtips, (void*)c->d_adj,
                   (void*)c->d_gacc, (void*)c->d_groups, (void*)c->d_partner, (void*)c->d_rho,
-                  (void*)c->d_chunks, (void*)c->d_block_chunk, (void*)c->d_pub,
-                  (void*)c->d_flags, (void*)c->d_env_nodes, (void*)c->d_env_tris,
+                  (void*)c->d_env_nodes, (void*)c->d_env_tris,
                   (void*)c->d_env_cache, (void*)c->d_env_cand, (void*)c->d_cbuild,
                   (void*)c->d_ccand})
     if (p) (void)hipFree(p);
+  leave_long_gate(c);
+  free_long_set(c->lng);
+  free_long_set(c->spread);
   if (c->ev0) (void)hipEventDestroy(c->ev0);
   if (c->ev1) (void)hipEventDestroy(c->ev1);
   if (c->aux) {
@@ -1410,7 +1531,8 @@ rod_status rod_set_state(rod_ctx* c, const float* x, const float* v, const float
   if (st != ROD_OK) return st;
   mv.add(c->d_xl, nullptr, P3);
   mv.add(c->d_ql, nullptr, F4);
-  if (c->d_flags) mv.add(reinterpret_cast<float*>(c->d_flags), nullptr, c->n_chunks);
+  for (const rod_ctx::LongSet* l : {&c->lng, &c->spread})
+    if (l->d_flags) mv.add(reinterpret_cast<float*>(l->d_flags), nullptr, l->n_chunks);
   mv.m.rods = c->d_rods;
   mv.m.n_rods = c->n_rods;
   mv.m.t0 = t0;
@@ -1487,7 +1609,7 @@ rod_status rod_step_state_noalloc(rod_ctx* c, float* x, float* v, float* q, floa
   if (!x || !v || !q || !w) return fail(c, ROD_E_INVALID, "null state pointer");
   if (n_steps < 0 || steps_per_launch < 0 || first_step < 0)
     return fail(c, ROD_E_INVALID, "n_steps, steps_per_launch and first_step must be >= 0");
-  if (c->n_chunks || !c->pair_buckets.empty() || c->n_haptic || c->env_nodes)
+  if (c->lng.n_chunks || !c->pair_buckets.empty() || c->n_haptic || c->env_nodes)
     return fail(c, ROD_E_UNSUPPORTED, "rod_step_state_noalloc steps handles without chunked rods, "
                                       "bindings, contact, haptic mailboxes or an environment");
   if ((long long)c->total_pts > kNoAllocMaxPoints)
@@ -1549,6 +1671,7 @@ rod_status rod_set_tuning(rod_ctx* c, const rod_tuning* t) {
   if (64 * k->waves * k->elems < max_res) return fail(c, ROD_E_UNSUPPORTED, "shape cannot hold the longest rod");
   rod_status st = make_buckets(c, [&](int, int* w, int* e) { *w = t->waves; *e = t->elems_per_lane; });
   if (st != ROD_OK) return st;
+  c->own_shapes = false;
   c->steps_per_launch = t->steps_per_launch;
   return ROD_OK;
 }
@@ -1579,12 +1702,12 @@ rod_status rod_bucket_info(const rod_ctx* c, int32_t bucket, rod_tuning* t, int3
     return ROD_OK;
   }
   const int nb = nb0 + (int)c->pair_buckets.size();
-  if (bucket == nb && c->n_chunks) {
+  if (bucket == nb && c->lng.n_chunks) {
     t->waves = kGridWaves;
     t->elems_per_lane = kGridElems;
     t->steps_per_launch = c->steps_per_launch;
     t->us_per_step = 0.f;
-    *n_rods = (int)c->long_rods.size();
+    *n_rods = (int)c->lng.rods.size();
     return ROD_OK;
   }
   if (bucket < 0 || bucket >= nb0)
@@ -1614,26 +1737,13 @@ rod_status rod_set_chunking(rod_ctx* c, int32_t min_elements, int32_t chunk_elem
       return fail(c, ROD_E_UNSUPPORTED, "rods with internal friction cannot be chunked");
   }
   HIP_TRY(c, hipStreamSynchronize(c->stream));
-  for (void** p : {(void**)&c->d_chunks, (void**)&c->d_block_chunk, (void**)&c->d_pub,
-                   (void**)&c->d_flags}) {
-    if (*p) (void)hipFree(*p);
-    *p = nullptr;
-  }
-  c->long_rods.clear();
-  c->n_chunks = 0;
-  c->pub_slots = 0;
+  free_long_set(c->lng);
   c->chunk_above = min_elements;
   c->chunk_target = chunk_elements;
   rod_status st = setup_long_rods(c);
   if (st == ROD_OK) st = make_plain_buckets(c);
   if (st != ROD_OK) {   // back to the default split, which rod_create accepted
-    for (void** p : {(void**)&c->d_chunks, (void**)&c->d_block_chunk, (void**)&c->d_pub,
-                     (void**)&c->d_flags}) {
-      if (*p) (void)hipFree(*p);
-      *p = nullptr;
-    }
-    c->long_rods.clear();
-    c->n_chunks = 0;
+    free_long_set(c->lng);
     c->chunk_above = kResidentMax;
     c->chunk_target = 0;
     const std::string err = c->err;
@@ -1641,7 +1751,8 @@ rod_status rod_set_chunking(rod_ctx* c, int32_t min_elements, int32_t chunk_elem
       (void)make_plain_buckets(c);
     return fail(c, st, err);
   }
-  if (c->n_chunks) c->adj_ready = false;   // the adjoint does not step chunked rods
+  c->own_shapes = false;
+  if (c->lng.n_chunks) c->adj_ready = false;   // the adjoint does not step chunked rods
   return ROD_OK;
 }
 
@@ -1879,7 +1990,7 @@ rod_status rod_set_environment(rod_ctx* c, int32_t n_tris, const double* tris, d
     for (const auto& d : c->rods)
       if (d.damp_int > 0.f)
         return fail(c, ROD_E_UNSUPPORTED, "rods with internal friction do not collide with the environment");
-    if (c->n_chunks) return fail(c, ROD_E_UNSUPPORTED, "chunked rods do not collide with the environment");
+    if (c->lng.n_chunks) return fail(c, ROD_E_UNSUPPORTED, "chunked rods do not collide with the environment");
   }
   std::vector<corde::EnvNode> nodes;
   std::vector<corde::EnvTri> out;
@@ -1949,6 +2060,7 @@ rod_status rod_autotune(rod_ctx* c, int32_t probe_steps, int32_t steps_per_launc
   if (!c) return fail(nullptr, ROD_E_INVALID, "null handle");
   if (!c->have_state) return fail(c, ROD_E_ORDER, "rod_autotune before rod_set_state");
   if (probe_steps < 1 || steps_per_launch < 0) return fail(c, ROD_E_INVALID, "bad probe sizes");
+  c->own_shapes = false;   // the shapes picked here are the ones stepped
   const bool pick_k = steps_per_launch == 0;   // also choose the steps per launch
   if (pick_k) steps_per_launch = std::min(10, probe_steps);
   // save the state, probe the candidate shapes of every bucket, restore
@@ -2142,7 +2254,7 @@ rod_status rod_adjoint_forward(rod_ctx* c, int32_t n_steps, int32_t ckpt_every, 
       return fail(c, ROD_E_UNSUPPORTED, "adjoint supports at most 10 constraint iterations");
   for (const auto& b : c->buckets)
     if (!adjoint_shape(b.max_n)) return fail(c, ROD_E_UNSUPPORTED, "rod too long for the adjoint kernel");
-  if (c->n_chunks)
+  if (c->lng.n_chunks)
     return fail(c, ROD_E_UNSUPPORTED,
                 "chunked rods are not differentiated (rod_set_chunking(ctx, 2048, 0) restores the default split)");
   if (!c->groups.empty()) return fail(c, ROD_E_UNSUPPORTED, "the adjoint does not step grouped rods");
@@ -2190,7 +2302,7 @@ rod_status rod_adjoint_backward(rod_ctx* c, int64_t rollout, const float* dl_dti
   if (rollout != 0 && rollout != c->adj_serial)
     return fail(c, ROD_E_ORDER, "rollout " + std::to_string(rollout) +
                 " is no longer held (the handle holds rollout " + std::to_string(c->adj_serial) + ")");
-  if (c->n_chunks)
+  if (c->lng.n_chunks)
     return fail(c, ROD_E_UNSUPPORTED,
                 "chunked rods are not differentiated (rod_set_chunking(ctx, 2048, 0) restores the default split)");
   if (!dl_dtips) return fail(c, ROD_E_INVALID, "null dL/dtip");

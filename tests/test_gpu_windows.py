@@ -34,10 +34,12 @@ def _rod(n, n_iter, base):
             W.RodState(x, 0.1 * rng.normal(size=(n + 1, 3)), q, 0.5 * rng.normal(size=(n, 3))))
 
 
-def _run(rods, splits, chunk=None):
-    b = R.RodBatch([s for s, _ in rods])
+def _run(rods, splits, chunk=None, shape=None, stream=None):
+    b = R.RodBatch([s for s, _ in rods], stream)
     if chunk is not None:
         b.set_chunking(32, chunk)
+    if shape is not None:
+        b.set_tuning(*shape, 10)
     b.set_state_rods([st for _, st in rods])
     for k in splits:
         b.step(k, k)
@@ -57,7 +59,7 @@ def _run(rods, splits, chunk=None):
 ])
 def test_windows_are_bitwise_one_workgroup(n, n_iter, base, chunk):
     rods = [_rod(n, n_iter, base)]
-    ref = _run(rods, [97])
+    ref = _run(rods, [97], shape=(8, 4))
     for splits in ([97], [1, 16, 5, 33, 42]):
         got = _run(rods, splits, chunk)
         assert all(np.array_equal(a, b) for a, b in zip(ref, got)), splits
@@ -66,5 +68,58 @@ def test_windows_are_bitwise_one_workgroup(n, n_iter, base, chunk):
 def test_windows_of_rods_with_different_exchanges():
     """Extensible and inextensible long rods in one handle share a launch (whole-state exchanges)."""
     rods = [_rod(1200, 0, "clamped"), _rod(1300, 10, "driven"), _rod(60, 10, "free"), _rod(700, 3, "free")]
-    ref, got = _run(rods, [60]), _run(rods, [7, 53], 0)
+    ref, got = _run(rods, [60], shape=(8, 4)), _run(rods, [7, 53], 0)
     assert all(np.array_equal(a, b) for a, b in zip(ref, got))
+
+
+@pytest.mark.parametrize("sizes", [
+    [(129, 10)], [(256, 10), (257, 10)], [(368, 5)], [(369, 10), (512, 10)], [(1023, 10)],
+    [(2048, 10), (513, 12), (130, 7)], [(257, 0)], [(404, 0), (300, 2)], [(405, 0)], [(513, 0), (2047, 1)],
+    [(128, 10), (700, 10)], [(600, 20)],
+])
+def test_untuned_handles_are_bitwise_one_workgroup(sizes):
+    """Handles whose shapes are left to the library, around the sizes where it spreads their rods
+    over windows, against an explicit shape."""
+    rods = [_rod(n, it, base) for (n, it), base in zip(sizes, ("driven", "free", "clamped"))]
+    ref = _run(rods, [50], shape=(8, 4))
+    for splits in ([50], [1] * 9 + [41]):
+        got = _run(rods, splits)
+        assert all(np.array_equal(a, b) for a, b in zip(ref, got))
+
+
+def test_untuned_handles_on_many_streams():
+    """Several spread handles in flight together, more chunks than compute units in all, from two
+    host threads; then one of them changes over to another kernel and back."""
+    import threading
+    import torch
+    cases = [[_rod(2048 - 8 * i, 10, "clamped")] for i in range(14)]
+    refs = [_run(r, [40], shape=(8, 4)) for r in cases]
+    streams = [torch.cuda.Stream() for _ in cases]
+    hs = [R.RodBatch([s for s, _ in r], st.cuda_stream) for r, st in zip(cases, streams)]
+    for h, r in zip(hs, cases):
+        h.set_state_rods([st for _, st in r])
+
+    def drive(part):
+        for _ in range(8):
+            for h in part:
+                h.step(5, 5)
+
+    ts = [threading.Thread(target=drive, args=(p,)) for p in (hs[::2], hs[1::2])]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    for h, ref in zip(hs, refs):
+        h.sync()
+        assert all(np.array_equal(a, b) for a, b in zip(ref, h.get_state()))
+    h, r = hs[0], cases[0]
+    h.set_state_rods([st for _, st in r])
+    h.step(15, 15)
+    far = np.array([[[0, 0, -90], [1, 0, -90], [0, 1, -90]]], float)
+    h.set_environment(far, 0.1)      # a mesh out of reach: the resident kernel with its code
+    h.step(10, 10)
+    h.set_environment(np.zeros((0, 3, 3)), 0.0)
+    h.step(15, 5)
+    assert all(np.array_equal(a, b) for a, b in zip(refs[0], h.get_state()))
+    for h in hs:
+        h.close()
