@@ -161,6 +161,15 @@ __device__ __forceinline__ Q4 sel4(bool c, Q4 a, Q4 b) {
 // segment below 1e-19 m or a vanished quaternion).
 __device__ __forceinline__ float rsq(float x) { return __builtin_amdgcn_rsqf(x); }
 
+// a / b with rb = 1 / b (rounded to nearest): the product refined twice by the remainder.  The
+// second refinement of a quotient that is already faithful rounds as the division does
+// (Markstein): the same bits in five dependent instructions instead of a dozen.
+__device__ __forceinline__ float div_by(float a, float b, float rb) {
+  const float q = a * rb;
+  const float q1 = __builtin_fmaf(__builtin_fmaf(-q, b, a), rb, q);
+  return __builtin_fmaf(__builtin_fmaf(-q1, b, a), rb, q1);
+}
+
 // DPP whole-wavefront shifts.  from_lower_lane / from_upper_lane: the lane without a source
 // (lane 0 / lane 63) receives 0 (bound_ctrl).  The `_or` forms leave that lane's destination
 // unwritten, so it keeps `edge`: one instruction moves the neighbour's value and merges what the
@@ -1157,12 +1166,9 @@ struct RodLane {
   // Collision response impulses (after a constraint iteration's distance sweeps): a point whose
   // predicted motion along n falls short of its depth is pushed out, with Coulomb friction
   // against its tangential velocity, at most mu times the normal impulse.
-  // Without branches, so that a lane's slots overlap; the division by dt as a product with
-  // rdt = 1 / dt (rounded to nearest), refined twice by the remainder: the second refinement of
-  // a quotient that is already faithful rounds as the division does (Markstein), in five
-  // dependent instructions instead of a dozen.  This runs in every iteration while the
-  // wavefront touches the mesh; a chain of dependent instructions bounds it (50 steps of a rod of
-  // 48 points, touching: 266.5 -> 260.5 us by this alone).
+  // Without branches, so that a lane's slots overlap, and with rdt = 1 / dt.  This runs in
+  // every iteration while the wavefront touches the mesh; a chain of dependent instructions bounds
+  // it (50 steps of a rod of 48 points, touching: 266.5 -> 260.5 us by this alone).
   __device__ __forceinline__ void env_impulses(const RodDev& rd, float rdt) {
     if (!env_any) return;   // nothing of this wavefront touches the mesh (a uniform branch)
 #pragma unroll
@@ -1171,10 +1177,7 @@ struct RodLane {
       const V3 v = Vv[e];
       const float vn = dot(v, n);
       const float sep = fmaf(dt, vn, -ed[e]);
-      // w lambda: the normal velocity change, -sep / dt
-      const float d0 = -sep * rdt;
-      const float d1 = fmaf(fmaf(-d0, dt, -sep), rdt, d0);
-      const float dvn = fmaf(fmaf(-d1, dt, -sep), rdt, d1);
+      const float dvn = div_by(-sep, dt, rdt);   // w lambda: the normal velocity change
       const V3 vt = fnma3(vn, n, v);
       const float vtl2 = dot(vt, vt);
       const float il = rsqrtf(vtl2);
@@ -1421,21 +1424,25 @@ __device__ __forceinline__ void quad_put(uint2& q, int k, uint32_t v) {
 }
 
 // Gap |d| - D between two spheres whose radii sum to D (ri + rj) and whose centres are the
-// compensated positions xi + li and xj + lj; d returns the centre difference (rounded, for
-// the normal).  Resting contact keeps |d| within a step's sinking (g dt^2, often below
+// compensated positions xi + li and xj + lj; d is the centre difference, rounded.  Resting contact keeps |d| within a step's sinking (g dt^2, often below
 // 1e-8 m) of D, where the difference of two FP32 lengths would carry an error of ulp(D):
 // instead the centre difference is formed in FP64 (exact for these float operands), |d|^2 -
 // D^2 in FP64, and the gap is that over |d| + D, to FP32 precision of the gap itself.  (FP64
 // fused multiply-adds issue at the rate of the unpacked FP32 ones this library uses.)
-__device__ __forceinline__ float sphere_gap(V3 xi, V3 li, V3 xj, V3 lj, float ri, float rj,
-                                            V3& d) {
+// The gap is num / (sqrt(S) + D): a contact is told by num < 0, without the root and the division.
+struct SphereGap {
+  V3 d;
+  float num, S, D;
+  __device__ __forceinline__ bool touch() const { return num < 0.f && dot(d, d) > 0.f; }
+  __device__ __forceinline__ float gap() const { return num / (sqrtf(S) + D); }
+};
+__device__ __forceinline__ SphereGap sphere_gap(V3 xi, V3 li, V3 xj, V3 lj, float ri, float rj) {
   const double dx = ((double)xi.x - (double)xj.x) + ((double)li.x - (double)lj.x);
   const double dy = ((double)xi.y - (double)xj.y) + ((double)li.y - (double)lj.y);
   const double dz = ((double)xi.z - (double)xj.z) + ((double)li.z - (double)lj.z);
-  d = {(float)dx, (float)dy, (float)dz};
   const double S = __builtin_fma(dx, dx, __builtin_fma(dy, dy, dz * dz));
   const double D = (double)ri + (double)rj;
-  return (float)__builtin_fma(-D, D, S) / (sqrtf((float)S) + (float)D);
+  return {{(float)dx, (float)dy, (float)dz}, (float)__builtin_fma(-D, D, S), (float)S, (float)D};
 }
 
 template <int W, int E, bool CT>
@@ -1452,8 +1459,8 @@ __global__ __launch_bounds__(128 * W) void rod_group_kernel(
   constexpr int SW = (SMAX + 31) / 32;
   __shared__ Mailbox<W> mb[2];
   __shared__ alignas(16) float cbuf[2][kClampChunk][kClampRow];
-  // step-start position and sphere radius, and the low parts of the position (the positions
-  // are pairs of floats; separations between points take both); rewritten at every step start
+  // step-start position and sphere radius, and the low parts of the position with the inverse
+  // mass (the positions are pairs of floats; separations between points take both); rewritten at every step start
   // after a barrier, so that no wavefront still reads the previous step's
   __shared__ float4 xs[2][CAP];
   __shared__ float4 xsl[2][CAP];
@@ -1544,6 +1551,20 @@ __global__ __launch_bounds__(128 * W) void rod_group_kernel(
   int bpar = 0;
   bool overflow = false;
   bool touch = false;   // some point of the group has a contact this step
+  // What a slot's first kOwn contacts keep for a step's iterations: partner, step-start normal,
+  // gap (infinite: no such contact), sum of the inverse masses, that times dt, and the reciprocals
+  // of the two.  An iteration reads the partner's velocity alone and, but for the friction's
+  // direction, divides nothing.  A dependent chain of one wavefront bounds it: with the listing's test
+  // before its root and division, 50 steps of two crossing rods of 128 elements 291 -> 257 us, of
+  // 300 795 -> 685.
+  constexpr int kOwn = 2;
+  struct Touch {
+    int g;
+    V3 nrm;
+    float gap, wsum, dtw, rw, rdtw;
+  };
+  Touch own[E][kOwn];
+  bool wave_has[3] = {false, false, false};   // a point of the wavefront has > 0, 1, 2 contacts
   auto publish = [&]() {
 #pragma unroll
     for (int e = 0; e < E; ++e)
@@ -1587,7 +1608,7 @@ __global__ __launch_bounds__(128 * W) void rod_group_kernel(
     for (int e = 0; e < E; ++e) {
       if (!L.ok[e]) continue;
       xs[sub][L.j0 + e] = make_float4(L.X[e].x, L.X[e].y, L.X[e].z, rho[e]);
-      xsl[sub][L.j0 + e] = make_float4(L.XL[e].x, L.XL[e].y, L.XL[e].z, 0.f);
+      xsl[sub][L.j0 + e] = make_float4(L.XL[e].x, L.XL[e].y, L.XL[e].z, L.P[P_WINV][e]);
     }
     if (contact) {
       bool mv = false;
@@ -1682,16 +1703,21 @@ __global__ __launch_bounds__(128 * W) void rod_group_kernel(
             p[k] = xsp[g[k]];
             pl[k] = xlp[g[k]];
           }
+          SphereGap sg[4];
+          bool hit[4];
 #pragma unroll
           for (int k = 0; k < 4; ++k) {
-            if (q + k >= ncand[e]) break;
-            const V3 lj = {pl[k].x, pl[k].y, pl[k].z};
-            V3 d;
-            const float gap = sphere_gap(xi, li, V3{p[k].x, p[k].y, p[k].z}, lj, rho[e], p[k].w, d);
-            if (!(gap < 0.f) || !(dot(d, d) > 0.f)) continue;
+            sg[k] = sphere_gap(xi, li, V3{p[k].x, p[k].y, p[k].z}, V3{pl[k].x, pl[k].y, pl[k].z},
+                               rho[e], p[k].w);
+            hit[k] = q + k < ncand[e] && sg[k].touch();
+          }
+          if (!(hit[0] | hit[1] | hit[2] | hit[3])) continue;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            if (!hit[k]) continue;
             if (cnt[e] < kMaxContacts) {
               quad_put(lst[sub][cnt[e] >> 2][i], cnt[e] & 3, (uint32_t)g[k]);
-              if constexpr (GC) gapc[sub][cnt[e]][i] = gap;
+              if constexpr (GC) gapc[sub][cnt[e]][i] = sg[k].gap();
               ++cnt[e];
             } else {
               overflow = true;
@@ -1701,15 +1727,43 @@ __global__ __launch_bounds__(128 * W) void rod_group_kernel(
       }
       // the iterations' contact rounds (a publication and its barrier each) are skipped in
       // steps where no point of the group touches anything
-      bool mine = false;
 #pragma unroll
-      for (int e = 0; e < E; ++e) mine = mine || cnt[e] > 0;
-      const bool wt = __ballot(mine) != 0ull;
+      for (int c = 0; c < 3; ++c) {
+        bool mine = false;
+#pragma unroll
+        for (int e = 0; e < E; ++e) mine = mine || cnt[e] > c;
+        wave_has[c] = __ballot(mine) != 0ull;
+      }
+      const bool wt = wave_has[0];
       if ((threadIdx.x & 63) == 0) touching[s & 1][threadIdx.x >> 6] = wt ? 1 : 0;
       __syncthreads();
       touch = false;
 #pragma unroll
       for (int k = 0; k < 2 * W; ++k) touch = touch || touching[s & 1][k] != 0;
+      if (wt) {
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+#pragma unroll
+          for (int c = 0; c < kOwn; ++c) {
+            const int i = L.j0 + e;
+            const bool has = c < cnt[e];
+            Touch& t = own[e][c];
+            t.g = has ? quad_get(lst[sub][0][i], c) : sub * CAP + i;
+            const float4 p = (&xs[0][0])[t.g], pl = (&xsl[0][0])[t.g];
+            const V3 xj = {p.x, p.y, p.z}, lj = {pl.x, pl.y, pl.z};
+            if constexpr (GC) t.gap = gapc[sub][c][i];
+            else t.gap = sphere_gap(L.X[e], L.XL[e], xj, lj, rho[e], p.w).gap();
+            // the normal from the centre difference in FP32, the same in every shape and exactly
+            // opposite for the partner
+            const V3 d0 = (L.X[e] - xj) + (L.XL[e] - lj);
+            t.nrm = rsqrtf(dot(d0, d0)) * d0;
+            t.wsum = L.P[P_WINV][e] + pl.w;
+            t.gap = has && t.wsum > 0.f ? t.gap : __builtin_inff();
+            t.dtw = dt * t.wsum;
+            t.rw = 1.0f / t.wsum;
+            t.rdtw = 1.0f / t.dtw;
+          }
+      }
     }
 
     // ---- the step
@@ -1778,66 +1832,69 @@ __global__ __launch_bounds__(128 * W) void rod_group_kernel(
       }
       if (contact && touch) {   // (uniform over the workgroup)
         publish();
+        if (wave_has[0]) {
+          const float4* vwp = &vw[bpar][0][0];   // indexed by sub * CAP + slot
+          V3 acc[E];
+          int act[E];
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-          if (!cnt[e]) continue;
-          const int i = L.j0 + e;
-          const V3 xi = L.X[e], vi = L.Vv[e], li = L.XL[e];
-          const float wi = L.P[P_WINV][e];
-          const float4* xsp = &xs[0][0];     // indexed by sub * CAP + slot
-          const float4* xlp = &xsl[0][0];
-          const float4* vwp = &vw[bpar][0][0];
-          // the impulse on this point from partner (ox + its low parts oxl, ov); false if that
-          // contact is inactive
-          auto impulse = [&](float4 ox, float4 oxl, float4 ov, int c, V3& imp) {
-            const V3 xj = {ox.x, ox.y, ox.z}, vj = {ov.x, ov.y, ov.z};
-            const float wsum = wi + ov.w;
-            if (!(wsum > 0.f)) return false;
-            const V3 lj = {oxl.x, oxl.y, oxl.z};
-            // the listing's gap (stored, or formed again alike); the normal from the centre
-            // difference in FP32, the same in every shape and exactly opposite for the partner
-            float gap;
-            if constexpr (GC) {
-              gap = gapc[sub][c][i];
-            } else {
-              V3 dd;
-              gap = sphere_gap(xi, li, xj, lj, rho[e], ox.w, dd);
-            }
-            const V3 d0 = (xi - xj) + (li - lj);
-            const V3 nrm = rsqrtf(dot(d0, d0)) * d0;        // step-start normal, towards i
-            const V3 vr = vi - vj;
-            // predicted separation along the normal: |d0| - D + dt (vi - vj).n
-            const float sep = __builtin_fmaf(dt, dot(vr, nrm), gap);
-            if (!(sep < 0.f)) return false;
-            const float lam = -sep / (dt * wsum);
-            const V3 vt = fnma3(dot(vr, nrm), nrm, vr);
+          for (int e = 0; e < E; ++e) {
+            acc[e] = {0.f, 0.f, 0.f};
+            act[e] = 0;
+          }
+          // the impulse on slot e's point along one contact, added to its sum if the contact acts
+          // (predicted separation along the normal, gap + dt (vi - vj).n, below zero)
+          auto impulse = [&](int e, const Touch& t, float4 ov) {
+            const float wi = L.P[P_WINV][e];
+            const V3 vr = L.Vv[e] - V3{ov.x, ov.y, ov.z};
+            const float vn = dot(vr, t.nrm);
+            const float sep = __builtin_fmaf(dt, vn, t.gap);
+            const float lam = div_by(-sep, t.dtw, t.rdtw);
+            const V3 vt = fnma3(vn, t.nrm, vr);
             const float vtl = sqrtf(dot(vt, vt));
-            imp = (wi * lam) * nrm;
-            if (vtl > 0.f) imp = fnma3(wi * fminf(vtl / wsum, gp.mu * lam) / vtl, vt, imp);
-            return true;
+            const V3 push = (wi * lam) * t.nrm;
+            const float f = wi * fminf(div_by(vtl, t.wsum, t.rw), gp.mu * lam) / vtl;
+            const V3 imp = sel(vtl > 0.f, fnma3(f, vt, push), push);
+            const bool on = sep < 0.f;
+            acc[e] = sel(on, acc[e] + imp, acc[e]);
+            act[e] += on ? 1 : 0;
           };
-          V3 acc = {0.f, 0.f, 0.f};
-          int act = 0;
-          // two contacts at a time (their four reads together), summed in list order
 #pragma unroll
-          for (int c = 0; c < kMaxContacts; c += 2) {
-            if (c >= cnt[e]) break;
-            const uint2 w = lst[sub][c >> 2][i];
-            const int ga = quad_get(w, c & 3);
-            const int gb = c + 1 < cnt[e] ? quad_get(w, (c & 3) + 1) : ga;
-            const float4 oxa = xsp[ga], ova = vwp[ga], oxb = xsp[gb], ovb = vwp[gb];
-            const float4 la = xlp[ga], lb = xlp[gb];
-            V3 imp;
-            if (impulse(oxa, la, ova, c, imp)) {
-              acc = acc + imp;
-              ++act;
-            }
-            if (c + 1 < cnt[e] && impulse(oxb, lb, ovb, c + 1, imp)) {
-              acc = acc + imp;
-              ++act;
+          for (int c = 0; c < kOwn; ++c) {   // the slots' side by side
+            if (c > 0 && !wave_has[c]) break;   // (uniform)
+            float4 ov[E];
+#pragma unroll
+            for (int e = 0; e < E; ++e) ov[e] = vwp[own[e][c].g];
+#pragma unroll
+            for (int e = 0; e < E; ++e) impulse(e, own[e][c], ov[e]);
+          }
+          if (wave_has[2]) {   // the others, from their lists
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+              const int i = L.j0 + e;
+              for (int c = kOwn; c < cnt[e]; ++c) {
+                const int g = quad_get(lst[sub][c >> 2][i], c & 3);
+                const float4 p = (&xs[0][0])[g], pl = (&xsl[0][0])[g], ov = vwp[g];
+                const V3 xj = {p.x, p.y, p.z}, lj = {pl.x, pl.y, pl.z};
+                Touch t;
+                t.wsum = L.P[P_WINV][e] + ov.w;
+                if (!(t.wsum > 0.f)) continue;
+                if constexpr (GC) t.gap = gapc[sub][c][i];
+                else t.gap = sphere_gap(L.X[e], L.XL[e], xj, lj, rho[e], p.w).gap();
+                const V3 d0 = (L.X[e] - xj) + (L.XL[e] - lj);
+                t.nrm = rsqrtf(dot(d0, d0)) * d0;
+                t.dtw = dt * t.wsum;
+                t.rw = 1.0f / t.wsum;
+                t.rdtw = 1.0f / t.dtw;
+                impulse(e, t, ov);
+              }
             }
           }
-          if (act) L.Vv[e] = fma3(1.0f / (float)act, acc, L.Vv[e]);
+#pragma unroll
+          for (int e = 0; e < E; ++e) {
+            float share = act[e] == 2 ? 0.5f : 1.0f;
+            if (wave_has[2]) share = 1.0f / (float)max(act[e], 1);
+            L.Vv[e] = sel(act[e] > 0, fma3(share, acc[e], L.Vv[e]), L.Vv[e]);
+          }
         }
         bpar ^= 1;
       }
