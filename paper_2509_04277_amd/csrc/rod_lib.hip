@@ -117,9 +117,18 @@ const GroupEntry kGroups[] = {
     {2, 2, true, corde::rod_group_kernel<2, 2, true>},
     {4, 2, true, corde::rod_group_kernel<4, 2, true>},
 };
-// contact candidate lists: pairs within contact distance + this fraction of the largest
-// sphere radius of the group's rods
-constexpr float kContactMarginRel = 0.5f;
+// Contact candidate lists: pairs within contact distance + this margin, of spheres up to rmax with
+// self_skip elements to the largest sphere's diameter.  Points move by a fraction of an element per
+// step and a list holds until one has moved 0.45 of the margin, while the candidates of a point
+// grow with the elements within reach, and more than a list holds (kContactCand) have it built
+// in every step: half the radius where elements are as long as it, less as the square of their
+// length below.  50 steps of two crossing rods, radius 10 mm on 1 m, us, at 1/2 / this / 1/16 of
+// the radius: 2 x 16 195 / 194 / 254; 2 x 128 257 / 252 / 225; 2 x 300 683 / 545 / 548; 2 x 512
+// 3935 / 624 / 649.  (Not below 20 um: movements are told from positions of one float each.)
+static float contact_margin(float rmax, int self_skip) {
+  const float rel = std::min(0.5f, std::max(0.05f, 2.f / ((float)self_skip * (float)self_skip)));
+  return std::max(rel * rmax, std::min(0.5f * rmax, 2e-5f));
+}
 constexpr int kGroupMax = 1024;     // longest rod a group may hold
 constexpr int kContactMax = 512;    // longest rod of a group with contact
 
@@ -1070,8 +1079,14 @@ rod_status rebuild_groups(rod_ctx* c) {
     }
     gs[g].contact = 1;
     gs[g].mu = c->contact_mu;
-    gs[g].margin = kContactMarginRel * std::max(c->rmax[gs[g].rod[0]],
-                                                gs[g].rod[1] >= 0 ? c->rmax[gs[g].rod[1]] : 0.f);
+    float rmax = 0.f;
+    int skip = 1;
+    for (int r : gs[g].rod)
+      if (r >= 0) {
+        rmax = std::max(rmax, c->rmax[r]);
+        skip = std::max(skip, c->rods[r].self_skip);
+      }
+    gs[g].margin = contact_margin(rmax, skip);
   }
   if (!gs.empty() && c->env_nodes)
     return fail(c, ROD_E_UNSUPPORTED, "rods in groups do not collide with the environment");
