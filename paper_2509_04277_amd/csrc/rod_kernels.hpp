@@ -1122,21 +1122,37 @@ struct RodLane {
               if (k0 + 2 * u + 1 < have) keep(two[u].z, __int_as_float(two[u].w), moved);
             }
           }
-          if (near_n[e] <= kEnvNear) {
-            todo[e] = near_n[e];
-          } else {
-            for (int k = 0; k < have; ++k) {
-              const int2 one = list[k];
-              if (touches(__int_as_float(one.y), moved))
-                env_hit(env_tri(rd, one.x), c, cl, r, acc[e], dmax[e]);
-            }
-          }
+          todo[e] = near_n[e];
         } else {
           env_walk(rd, c, r, [&](int k) { env_hit(env_tri(rd, k), c, cl, r, acc[e], dmax[e]); });
         }
-        const bool fits = have <= kEnvCand && near_n[e] <= kEnvNear;
-        near_by2[e] = fits ? by * by * (1.f - 1e-6f) : -1.f;
-        near_n[e] = fits ? near_n[e] : 0;
+        near_by2[e] = have <= kEnvCand ? by * by * (1.f - 1e-6f) : -1.f;
+        near_n[e] = have <= kEnvCand ? near_n[e] : 0;
+      }
+      if (todo[e] > kEnvNear) {
+        // more than are kept: the whole list, four entries at a time (one load of the entries,
+        // then the triangles that can touch together)
+        const int slot = rd.slot_off + off + j0 + e;
+        const float r = lr[j0 + e], moved = sqrtf(moved2[e]);
+        const int have = __float_as_int(lc[j0 + e].w);
+        const GlobalI4* const quad = (const GlobalI4*)(uintptr_t)(rd.env_cand + (size_t)slot * kEnvCand);
+        for (int k0 = 0; k0 < have; k0 += 4) {
+          const Vec4i lo = quad[k0 / 2], hi = quad[k0 / 2 + 1];
+          const int id[4] = {lo.x, lo.z, hi.x, hi.z};
+          const float db[4] = {__int_as_float(lo.y), __int_as_float(lo.w), __int_as_float(hi.y),
+                               __int_as_float(hi.w)};
+          bool near[4];
+          EnvTri t[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            near[u] = k0 + u < have && db[u] - moved < r * (1.f + 1e-5f) + 1e-5f * db[u];
+            if (near[u]) t[u] = env_tri(rd, id[u]);
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (near[u]) env_hit(t[u], X[e], XL[e], r, acc[e], dmax[e]);
+        }
+        todo[e] = 0;
       }
       most = max(most, todo[e]);
     }
