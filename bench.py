@@ -348,7 +348,7 @@ def binding_extras(R, W):
         ms, launches = b.last_step_time()
         b.close()
         out[name] = {"us_per_step": 1e3 * ms / 5000,
-                     "kernel": ("rod_resident_kernel<4,2>, one workgroup per rod" if one_way is None
+                     "kernel": ("rod_window_kernel, each rod as window chunks" if one_way is None
                                 else "rod_group_kernel<4,2>, both rods in one workgroup")}
     for v in ("v1", "v2"):
         out[v]["overhead_vs_v0"] = out[v]["us_per_step"] / out["v0"]["us_per_step"] - 1.0
