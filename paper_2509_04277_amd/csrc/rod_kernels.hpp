@@ -1951,8 +1951,8 @@ __global__ __launch_bounds__(128 * W) void rod_group_kernel(
 // next launch loads from the neighbours' stored slots) the chunk publishes its first H owned
 // slots (for the left neighbour's right halo) and its last H + 1 owned slots (for the right
 // neighbour's left halo and halo-edge point) to a double-buffered mailbox in global memory,
-// raises its flag to the step count, waits for both neighbours' flags and refills its halos:
-// one exchange per T steps instead of one per phase.
+// raises its flag, waits for both neighbours' flags and refills its halos: one exchange per T
+// steps instead of one per phase.
 struct GridChunk {
   int32_t rod;             // rod index
   int32_t s0, c;           // owned slots
@@ -2009,6 +2009,37 @@ __device__ __forceinline__ void get_slot(const float* part, int o, int pub_slots
   L.QL[e] = {v[16], v[17], v[18], v[19]};
 }
 
+// A chunk's flag: steps done + 1 once it has loaded its window, + 1 more with each step after which
+// it has published its boundary slots.
+__device__ __forceinline__ void raise_flag(int* flags, int chunk, int value) {
+  __hip_atomic_store(flags + chunk, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Waits (one thread) until both neighbours' flags reach value; false after spin_limit polls.
+__device__ __forceinline__ bool await_neighbours(const int* flags, const GridChunk& ck, int value,
+                                                 int spin_limit) {
+  int spins = 0;
+  for (int side = 0; side < 2; ++side) {
+    const int nb = side == 0 ? ck.left : ck.right;
+    if (nb < 0) continue;
+    while (__hip_atomic_load(const_cast<int*>(flags) + nb, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT) < value) {
+      __builtin_amdgcn_s_sleep(1);
+      if (++spins > spin_limit) return false;
+    }
+  }
+  return true;
+}
+// Before a chunk stores its slots where its neighbours load theirs from: waits (the whole
+// workgroup) until both have loaded their windows.  A launch with a halo exchange has waited for
+// that there; one of at most ck.every steps has none, and a neighbour may start later than this
+// chunk ends, behind other work on its compute unit.
+__device__ __forceinline__ void await_loads(const int* flags, const GridChunk& ck, int loaded,
+                                            int exchanges, int spin_limit, int* status) {
+  if (exchanges > 0 || (ck.left < 0 && ck.right < 0)) return;   // (uniform)
+  if (threadIdx.x == 0 && !await_neighbours(flags, ck, loaded, spin_limit)) atomicOr(status, 4);
+  __syncthreads();
+}
+
 template <int W, int E>
 __global__ __launch_bounds__(64 * W) void rod_grid_kernel(
     const RodDev* __restrict__ rods, const GridChunk* __restrict__ chunks,
@@ -2032,7 +2063,9 @@ __global__ __launch_bounds__(64 * W) void rod_grid_kernel(
   int xk = 0;   // halo exchanges so far in this launch
   int until = ck.every;
   if (threadIdx.x == 0) abort_flag = 0;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the state's words have arrived)
   __syncthreads();
+  if (threadIdx.x == 0) raise_flag(flags, ci, (int)(steps_done + 1));
 
   for (int s = 0; s < n_steps; ++s) {
     const long long gs = steps_done + s;
@@ -2069,20 +2102,8 @@ __global__ __launch_bounds__(64 * W) void rod_grid_kernel(
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) {
-      __hip_atomic_store(&flags[ci], (int)(gs + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      // wait for both neighbours to have published this step (bounded spin)
-      int spins = 0;
-      for (int side = 0; side < 2; ++side) {
-        const int nb = side == 0 ? ck.left : ck.right;
-        if (nb < 0) continue;
-        while (__hip_atomic_load(&flags[nb], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (int)(gs + 1)) {
-          __builtin_amdgcn_s_sleep(1);
-          if (++spins > spin_limit) {
-            abort_flag = 1;
-            break;
-          }
-        }
-      }
+      raise_flag(flags, ci, (int)(gs + 2));
+      if (!await_neighbours(flags, ck, (int)(gs + 2), spin_limit)) abort_flag = 1;
     }
     __syncthreads();   // the neighbours' words are read (device-coherent) only after this
     if (abort_flag) {
@@ -2110,6 +2131,7 @@ __global__ __launch_bounds__(64 * W) void rod_grid_kernel(
       L.bv = {v[6], v[7], v[8]};
     }
   }
+  await_loads(flags, ck, (int)(steps_done + 1), xk, spin_limit, status);
   const float chk = L.store_state(rd, st, own_lo, own_hi);
   if (!__builtin_isfinite(chk)) atomicOr(status, 1);
 }
@@ -2203,7 +2225,9 @@ __global__ __launch_bounds__(64 * kWinWaves) void rod_window_kernel(
   const float4* const get = get_lo ? &halo[0][k - 1][1][0][L.g]
                             : get_up ? &halo[0][k + 1][0][0][L.g - (64 - h / 2)] : &halo[0][0][0][0][0];
   constexpr int kParity = kWinWaves * 2 * 10 * (kWinHaloMax / 2), kQuad = kWinHaloMax / 2;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the state's words have arrived)
   __syncthreads();
+  if (threadIdx.x == 0) raise_flag(flags, ci, (int)(steps_done + 1));
 
   for (int s = 0; s < n_steps; ++s) {
     const long long gs = steps_done + s;
@@ -2307,20 +2331,8 @@ __global__ __launch_bounds__(64 * kWinWaves) void rod_window_kernel(
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) {
-      __hip_atomic_store(&flags[ci], (int)(gs + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      // wait for both neighbours to have published this step (bounded spin)
-      int spins = 0;
-      for (int side = 0; side < 2; ++side) {
-        const int nb = side == 0 ? ck.left : ck.right;
-        if (nb < 0) continue;
-        while (__hip_atomic_load(&flags[nb], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (int)(gs + 1)) {
-          __builtin_amdgcn_s_sleep(1);
-          if (++spins > spin_limit) {
-            abort_flag = 1;
-            break;
-          }
-        }
-      }
+      raise_flag(flags, ci, (int)(gs + 2));
+      if (!await_neighbours(flags, ck, (int)(gs + 2), spin_limit)) abort_flag = 1;
     }
     __syncthreads();   // the neighbours' words are read (device-coherent) only after this
     if (abort_flag) {
@@ -2351,6 +2363,7 @@ __global__ __launch_bounds__(64 * kWinWaves) void rod_window_kernel(
       }
     }
   }
+  await_loads(flags, ck, (int)(steps_done + 1), xk, spin_limit, status);
   if (nw > 0) {
     const float chk = L.store_state(rd, st, max(mine_lo, own_lo - wa), min(mine_hi, own_lo + ck.c - wa));
     if (!__builtin_isfinite(chk)) atomicOr(status, 1);
