@@ -1951,7 +1951,7 @@ __global__ __launch_bounds__(128 * W) void rod_group_kernel(
 // next launch loads from the neighbours' stored slots) the chunk publishes its first H owned
 // slots (for the left neighbour's right halo) and its last H + 1 owned slots (for the right
 // neighbour's left halo and halo-edge point) to a double-buffered mailbox in global memory,
-// raises its flag, waits for both neighbours' flags and refills its halos: one exchange per T
+// raises its counter, waits for both neighbours' and refills its halos: one exchange per T
 // steps instead of one per phase.
 struct GridChunk {
   int32_t rod;             // rod index
@@ -1970,7 +1970,7 @@ struct GridChunk {
 constexpr int kPubSlotFloats = 20;
 
 // Mailbox words are read and written as device-scope relaxed atomics (coherent across the
-// XCDs' L2 caches without writing back or invalidating them); the step flags order them.
+// XCDs' L2 caches without writing back or invalidating them); the chunks' counters order them.
 template <int W, int E>
 __device__ __forceinline__ void put_slot(float* part, int o, int pub_slots, const RodLane<W, E>& L,
                                          int e) {
@@ -2009,34 +2009,53 @@ __device__ __forceinline__ void get_slot(const float* part, int o, int pub_slots
   L.QL[e] = {v[16], v[17], v[18], v[19]};
 }
 
-// A chunk's flag: steps done + 1 once it has loaded its window, + 1 more with each step after which
-// it has published its boundary slots.
-__device__ __forceinline__ void raise_flag(int* flags, int chunk, int value) {
-  __hip_atomic_store(flags + chunk, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// What chunks wait on each other with: a counter per chunk (marks[]) that only its own workgroup
+// writes.  It goes up by one in each launch once the chunk has loaded its window, and once more
+// with each halo exchange, when it has published its boundary slots.  The chunks of a rod do so
+// equally often, so their counters agree between launches, whatever the step count was set to and
+// also when a captured launch is replayed; one that gives up waiting leaves its counter where the
+// launch would have ended.  A counter passes 2^32 in a long simulation, so two are compared by
+// their difference.  No chunk reads its own before it first waits: that, and its neighbours', are
+// then one round trip to memory, and loading it with the state cost every launch 0.4 us.
+__host__ __device__ constexpr bool mark_behind(uint32_t mark, uint32_t target) {
+  return (int32_t)(mark - target) < 0;
 }
-// Waits (one thread) until both neighbours' flags reach value; false after spin_limit polls.
-__device__ __forceinline__ bool await_neighbours(const int* flags, const GridChunk& ck, int value,
-                                                 int spin_limit) {
-  int spins = 0;
-  for (int side = 0; side < 2; ++side) {
-    const int nb = side == 0 ? ck.left : ck.right;
-    if (nb < 0) continue;
-    while (__hip_atomic_load(const_cast<int*>(flags) + nb, __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_AGENT) < value) {
-      __builtin_amdgcn_s_sleep(1);
-      if (++spins > spin_limit) return false;
-    }
+// First value of the counters: near the end of the signed range, so that every handle's first
+// launches already go past it.
+constexpr uint32_t kFirstMark = 0x7ffffff0u;
+// How far a launch of n_steps >= 1 steps raises the counters.
+__host__ __device__ constexpr uint32_t launch_marks(int n_steps, int every) {
+  return 1u + (uint32_t)((n_steps - 1) / every);
+}
+// (returns the value before)
+__device__ __forceinline__ uint32_t raise_mark(uint32_t* marks, int chunk, uint32_t by) {
+  return __hip_atomic_fetch_add(marks + chunk, by, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t get_mark(const uint32_t* marks, int chunk) {
+  return __hip_atomic_load(const_cast<uint32_t*>(marks) + chunk, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+}
+// Raises the chunk's counter by `by` and waits (one thread) until both neighbours' have come as
+// far; false after spin_limit polls.
+__device__ __forceinline__ bool await_neighbours(uint32_t* marks, int ci, uint32_t by,
+                                                 const GridChunk& ck, int spin_limit) {
+  const int l = ck.left >= 0 ? ck.left : ck.right, r = ck.right >= 0 ? ck.right : ck.left;
+  const uint32_t own = by ? raise_mark(marks, ci, by) + by : get_mark(marks, ci);
+  for (int spins = 0; spins <= spin_limit; ++spins) {
+    const uint32_t ml = get_mark(marks, l), mr = get_mark(marks, r);
+    if (!mark_behind(ml, own) && !mark_behind(mr, own)) return true;
+    __builtin_amdgcn_s_sleep(1);
   }
-  return true;
+  return false;
 }
 // Before a chunk stores its slots where its neighbours load theirs from: waits (the whole
 // workgroup) until both have loaded their windows.  A launch with a halo exchange has waited for
 // that there; one of at most ck.every steps has none, and a neighbour may start later than this
 // chunk ends, behind other work on its compute unit.
-__device__ __forceinline__ void await_loads(const int* flags, const GridChunk& ck, int loaded,
+__device__ __forceinline__ void await_loads(uint32_t* marks, int ci, const GridChunk& ck,
                                             int exchanges, int spin_limit, int* status) {
   if (exchanges > 0 || (ck.left < 0 && ck.right < 0)) return;   // (uniform)
-  if (threadIdx.x == 0 && !await_neighbours(flags, ck, loaded, spin_limit)) atomicOr(status, 4);
+  if (threadIdx.x == 0 && !await_neighbours(marks, ci, 0, ck, spin_limit)) atomicOr(status, 4);
   __syncthreads();
 }
 
@@ -2046,7 +2065,7 @@ __global__ __launch_bounds__(64 * W) void rod_grid_kernel(
     const int* __restrict__ block_chunk, const float* __restrict__ prm, int prm_stride,
     StateArrays st, const float* __restrict__ fext, const float* __restrict__ text, int n_steps,
     long long steps_done, int* __restrict__ status, float* pub, int pub_slots, int n_chunks,
-    int* flags, int spin_limit) {
+    uint32_t* marks, int spin_limit) {
   __shared__ Mailbox<W> mb;
   mailbox_init(mb);
   __shared__ alignas(16) float cbuf[kClampChunk][kClampRow];
@@ -2065,10 +2084,10 @@ __global__ __launch_bounds__(64 * W) void rod_grid_kernel(
   if (threadIdx.x == 0) abort_flag = 0;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the state's words have arrived)
   __syncthreads();
-  if (threadIdx.x == 0) raise_flag(flags, ci, (int)(steps_done + 1));
+  const bool alone = ck.left < 0 && ck.right < 0;   // the rod's only chunk: no one to wait for
+  if (threadIdx.x == 0 && !alone) (void)raise_mark(marks, ci, 1);
 
   for (int s = 0; s < n_steps; ++s) {
-    const long long gs = steps_done + s;
     V3 xl, xll, xc, wc;
     Q4 qn, qnl, qc;
     const bool driven = rd.driven && rd.clamp && ck.win0 == 0;
@@ -2081,7 +2100,7 @@ __global__ __launch_bounds__(64 * W) void rod_grid_kernel(
     L.iterate(rd, mb, Ev, enext, []() {});
     L.integrate_velocities(rd, xc, qc);
 
-    if (--until > 0 || s + 1 == n_steps) continue;   // (uniform over the chunk)
+    if (alone || --until > 0 || s + 1 == n_steps) continue;   // (uniform over the chunk)
     until = ck.every;
     // ---- publish boundary slots: part 0 = owned [0, H), part 1 = owned [c - H - 1, c), into
     // the mailbox buffer of this launch's exchange count parity
@@ -2098,16 +2117,16 @@ __global__ __launch_bounds__(64 * W) void rod_grid_kernel(
       if (p1) put_slot(mine + pub_slots * kPubSlotFloats, o - (ck.c - H - 1), pub_slots, L, e);
     }
     // this thread's mailbox stores are complete (device-visible) before the barrier, and the
-    // flag is raised after it
+    // counter is raised after it
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (threadIdx.x == 0) {
-      raise_flag(flags, ci, (int)(gs + 2));
-      if (!await_neighbours(flags, ck, (int)(gs + 2), spin_limit)) abort_flag = 1;
-    }
+    if (threadIdx.x == 0 && !await_neighbours(marks, ci, 1, ck, spin_limit)) abort_flag = 1;
     __syncthreads();   // the neighbours' words are read (device-coherent) only after this
     if (abort_flag) {
-      if (threadIdx.x == 0) atomicOr(status, 4);
+      if (threadIdx.x == 0) {
+        atomicOr(status, 4);
+        (void)raise_mark(marks, ci, launch_marks(n_steps, ck.every) - 1 - xk);
+      }
       break;
     }
     // ---- refill the halos from the neighbours' parts
@@ -2131,7 +2150,7 @@ __global__ __launch_bounds__(64 * W) void rod_grid_kernel(
       L.bv = {v[6], v[7], v[8]};
     }
   }
-  await_loads(flags, ck, (int)(steps_done + 1), xk, spin_limit, status);
+  await_loads(marks, ci, ck, xk, spin_limit, status);
   const float chk = L.store_state(rd, st, own_lo, own_hi);
   if (!__builtin_isfinite(chk)) atomicOr(status, 1);
 }
@@ -2186,7 +2205,7 @@ __global__ __launch_bounds__(64 * kWinWaves) void rod_window_kernel(
     const int* __restrict__ block_chunk, const float* __restrict__ prm, int prm_stride,
     StateArrays st, const float* __restrict__ fext, const float* __restrict__ text, int n_steps,
     long long steps_done, int* __restrict__ status, float* pub, int pub_slots, int n_chunks,
-    int* flags, int spin_limit) {
+    uint32_t* marks, int spin_limit) {
   // per exchange parity and wavefront: the slot pairs its lower ([0]) and upper neighbour ([1])
   // refill from it, quad-major (consecutive lanes' quads are consecutive), and the point below
   // the upper neighbour's window
@@ -2227,10 +2246,10 @@ __global__ __launch_bounds__(64 * kWinWaves) void rod_window_kernel(
   constexpr int kParity = kWinWaves * 2 * 10 * (kWinHaloMax / 2), kQuad = kWinHaloMax / 2;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the state's words have arrived)
   __syncthreads();
-  if (threadIdx.x == 0) raise_flag(flags, ci, (int)(steps_done + 1));
+  const bool alone = ck.left < 0 && ck.right < 0;   // the rod's only chunk: no one to wait for
+  if (threadIdx.x == 0 && !alone) (void)raise_mark(marks, ci, 1);
 
   for (int s = 0; s < n_steps; ++s) {
-    const long long gs = steps_done + s;
     V3 xl, xll, xc, wc;
     Q4 qn, qnl, qc;
     clamp_chunk(rd, cbuf, s, n_steps, steps_done, driven, threadIdx.x);
@@ -2311,7 +2330,7 @@ __global__ __launch_bounds__(64 * kWinWaves) void rod_window_kernel(
     }
     if (until > 0) continue;
     until = ck.every;
-    if (ck.left < 0 && ck.right < 0) continue;
+    if (alone) continue;
 
     // ---- the chunk's outer slots, through memory (see rod_grid_kernel)
     const int pp = xk & 1;
@@ -2327,16 +2346,16 @@ __global__ __launch_bounds__(64 * kWinWaves) void rod_window_kernel(
         put_slot(mine + pub_slots * kPubSlotFloats, o - (ck.c - H - 1), pub_slots, L, e);
     }
     // this thread's mailbox stores are complete (device-visible) before the barrier, and the
-    // flag is raised after it
+    // counter is raised after it
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (threadIdx.x == 0) {
-      raise_flag(flags, ci, (int)(gs + 2));
-      if (!await_neighbours(flags, ck, (int)(gs + 2), spin_limit)) abort_flag = 1;
-    }
+    if (threadIdx.x == 0 && !await_neighbours(marks, ci, 1, ck, spin_limit)) abort_flag = 1;
     __syncthreads();   // the neighbours' words are read (device-coherent) only after this
     if (abort_flag) {
-      if (threadIdx.x == 0) atomicOr(status, 4);
+      if (threadIdx.x == 0) {
+        atomicOr(status, 4);
+        (void)raise_mark(marks, ci, launch_marks(n_steps, ck.every) - 1 - xk);
+      }
       break;
     }
     const float* lp = ck.left >= 0
@@ -2363,7 +2382,7 @@ __global__ __launch_bounds__(64 * kWinWaves) void rod_window_kernel(
       }
     }
   }
-  await_loads(flags, ck, (int)(steps_done + 1), xk, spin_limit, status);
+  await_loads(marks, ci, ck, xk, spin_limit, status);
   if (nw > 0) {
     const float chk = L.store_state(rd, st, max(mine_lo, own_lo - wa), min(mine_hi, own_lo + ck.c - wa));
     if (!__builtin_isfinite(chk)) atomicOr(status, 1);

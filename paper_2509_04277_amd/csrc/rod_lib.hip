@@ -32,7 +32,7 @@ using KernelFn = void (*)(const RodDev*, const int*, const float*, int, StateArr
                           int, long long, int, int);
 using GridFn = void (*)(const RodDev*, const corde::GridChunk*, const int*, const float*, int,
                         StateArrays, const float*, const float*, int, long long, int*, float*, int,
-                        int, int*, int);
+                        int, uint32_t*, int);
 // Long-rod kernel shape: 4 wavefronts (one per SIMD) x 2 elements per lane = 512-slot windows.
 constexpr int kGridWaves = 4, kGridElems = 2;
 static_assert(kGridWaves == corde::kWinWaves, "both long-rod kernels launch the same workgroup");
@@ -175,7 +175,7 @@ struct rod_ctx {
     corde::GridChunk* d_chunks = nullptr;
     int* d_block_chunk = nullptr;
     float* d_pub = nullptr;
-    int* d_flags = nullptr;
+    uint32_t* d_marks = nullptr;
   };
   LongSet lng;      // the rods above the chunking threshold
   // All rods of the handle as window chunks, for steps whose shapes the caller left to the library
@@ -677,7 +677,7 @@ bool chunk_rod(const rod_ctx* c, int r, bool win, int cus, std::vector<corde::Gr
 }
 
 void free_long_set(rod_ctx::LongSet& l) {
-  for (void* p : {(void*)l.d_chunks, (void*)l.d_block_chunk, (void*)l.d_pub, (void*)l.d_flags})
+  for (void* p : {(void*)l.d_chunks, (void*)l.d_block_chunk, (void*)l.d_pub, (void*)l.d_marks})
     if (p) (void)hipFree(p);
   l = rod_ctx::LongSet{};
 }
@@ -708,11 +708,12 @@ rod_status place_chunks(rod_ctx* c, rod_ctx::LongSet& l, const std::vector<corde
   if (!dm((void**)&l.d_chunks, sizeof(corde::GridChunk) * G) ||
       !dm((void**)&l.d_block_chunk, sizeof(int) * G) ||
       !dm((void**)&l.d_pub, sizeof(float) * 2 * (size_t)G * 2 * l.pub_slots * corde::kPubSlotFloats) ||
-      !dm((void**)&l.d_flags, sizeof(int) * G))
+      !dm((void**)&l.d_marks, sizeof(uint32_t) * G))
     return fail(c, ROD_E_NOMEM, "long-rod buffers");
   HIP_TRY(c, hipMemcpy(l.d_chunks, ch.data(), sizeof(corde::GridChunk) * G, hipMemcpyHostToDevice));
   HIP_TRY(c, hipMemcpy(l.d_block_chunk, block_chunk.data(), sizeof(int) * G, hipMemcpyHostToDevice));
-  HIP_TRY(c, hipMemset(l.d_flags, 0, sizeof(int) * G));
+  const std::vector<uint32_t> marks(G, corde::kFirstMark);
+  HIP_TRY(c, hipMemcpy(l.d_marks, marks.data(), sizeof(uint32_t) * G, hipMemcpyHostToDevice));
   // every chunk must be resident at once (the chunks wait on each other)
   int per_cu = 0;
   HIP_TRY(c, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, grid_kernel(l.kernel),
@@ -811,7 +812,7 @@ rod_status launch_long(rod_ctx* c, const rod_ctx::LongSet& l, StateArrays sa, in
   const int spin = &l == &c->spread ? 1 << 25 : 1 << 22;
   hipLaunchKernelGGL(grid_kernel(l.kernel), dim3(l.n_chunks), dim3(64 * kGridWaves), 0, stream,
                      c->d_rods, l.d_chunks, l.d_block_chunk, c->d_prm, c->prm_stride, sa, c->d_fext,
-                     c->d_text, ks, done, c->d_status, l.d_pub, l.pub_slots, l.n_chunks, l.d_flags,
+                     c->d_text, ks, done, c->d_status, l.d_pub, l.pub_slots, l.n_chunks, l.d_marks,
                      spin);
   HIP_TRY(c, hipGetLastError());
   return ROD_OK;
@@ -888,13 +889,6 @@ void leave_long_gate(rod_ctx* c) {
   auto& runs = g.runs[c->device];
   for (size_t i = runs.size(); i-- > 0;)
     if (runs[i].done == c->ev1) runs.erase(runs.begin() + i);
-}
-
-// Zeroes the long-rod step flags (whenever the step counter restarts).
-rod_status reset_flags(rod_ctx* c) {
-  for (const rod_ctx::LongSet* l : {&c->lng, &c->spread})
-    if (l->d_flags) HIP_TRY(c, hipMemsetAsync(l->d_flags, 0, sizeof(int) * l->n_chunks, c->stream));
-  return ROD_OK;
 }
 
 // ---- scratch of rod_step_state_noalloc -----------------------------------------------------
@@ -1546,8 +1540,6 @@ rod_status rod_set_state(rod_ctx* c, const float* x, const float* v, const float
   if (st != ROD_OK) return st;
   mv.add(c->d_xl, nullptr, P3);
   mv.add(c->d_ql, nullptr, F4);
-  for (const rod_ctx::LongSet* l : {&c->lng, &c->spread})
-    if (l->d_flags) mv.add(reinterpret_cast<float*>(l->d_flags), nullptr, l->n_chunks);
   mv.m.rods = c->d_rods;
   mv.m.n_rods = c->n_rods;
   mv.m.t0 = t0;
@@ -2230,7 +2222,6 @@ rod_status rod_autotune(rod_ctx* c, int32_t probe_steps, int32_t steps_per_launc
   }
   c->steps_per_launch = steps_per_launch;
   c->steps_done = saved_steps;
-  (void)reset_flags(c);
   if (copy(c->d_x, sx, bx) || copy(c->d_xl, sxl, bx) || copy(c->d_v, sv, bx) ||
       copy(c->d_q, sq, bq) || copy(c->d_ql, sql, bq) || copy(c->d_w, sw, bw)) {
     free_all();
