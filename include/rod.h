@@ -130,7 +130,12 @@ rod_status rod_destroy(rod_ctx* ctx);
 /* Copy a full state in (layouts above): the arrays the paper uploads once at initialisation
  * (Sec. 2.2).  Resets the simulation time to t0 [s].  Inside the handle, positions and
  * quaternions are kept as pairs of floats (value + a low part below half its ulp) so that
- * the small per-step increments are not rounded away; this call sets the low parts to 0. */
+ * the small per-step increments are not rounded away; this call sets the low parts to 0.
+ * on_device = 0: host arrays; 1: device arrays; both return when the copies are done, and the
+ * caller may overwrite or free the arrays.  on_device = ROD_DEVICE_QUEUED: device arrays, and the
+ * call returns with the copies queued on the handle's stream (about 13 us earlier): the arrays
+ * must stay as they are until that stream has passed them. */
+#define ROD_DEVICE_QUEUED 2
 rod_status rod_set_state(rod_ctx* ctx, const float* x, const float* v, const float* q,
                          const float* w, int32_t on_device, double t0);
 

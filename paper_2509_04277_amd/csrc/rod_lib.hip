@@ -1548,7 +1548,7 @@ rod_status rod_set_state(rod_ctx* c, const float* x, const float* v, const float
   c->t0 = t0;
   c->steps_done = 0;
   for (auto& r : c->rods) r.t0 = t0;
-  if (!on_device) HIP_TRY(c, hipStreamSynchronize(c->stream));
+  if (on_device != ROD_DEVICE_QUEUED) HIP_TRY(c, hipStreamSynchronize(c->stream));
   c->have_state = true;
   return ROD_OK;
 }

@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import sys
 from typing import Optional, Sequence
 
 import numpy as np
@@ -19,6 +20,9 @@ LIB_PATH = os.path.join(HERE, "libcorde_rod.so")
 ROD_OK = 0
 STATUS = {0: "ROD_OK", -1: "ROD_E_INVALID", -2: "ROD_E_NOMEM", -3: "ROD_E_DEVICE",
           -4: "ROD_E_UNSTABLE", -5: "ROD_E_ORDER", -6: "ROD_E_UNSUPPORTED", -7: "ROD_E_TIMEOUT"}
+
+
+DEVICE_QUEUED = 2   # rod_set_state: device arrays, copies queued on the handle's stream
 
 
 class RodError(RuntimeError):
@@ -205,12 +209,32 @@ class RodBatch:
         _check(lib().rod_create(arr, len(specs), C.c_void_p(stream), C.byref(h)))
         self.h = h
         self.stream = int(stream or 0)
+        torch = sys.modules.get("torch")
+        self._device = (torch.cuda.current_device()
+                        if torch is not None and torch.cuda.is_available() else None)
+        self._as_torch = None
 
     def _foreign_stream(self, device):
         """True if torch's current stream on ``device`` is not the handle's: memory that torch
         frees is then reused without regard to the handle's pending work."""
         import torch
         return torch.cuda.current_stream(device).cuda_stream != self.stream
+
+    def _torch_stream(self, device):
+        """The handle's stream as torch's."""
+        import torch
+        if self._as_torch is None:   # (torch makes a stream of its own from the address 0)
+            self._as_torch = (torch.cuda.ExternalStream(self.stream, device=device) if self.stream
+                              else torch.cuda.default_stream(device))
+        return self._as_torch
+
+    def _may_queue(self, arrays):
+        """True if a call may return with its reads of the tensors queued on the handle's stream:
+        it is the current stream (as for any torch operation, work on other streams that
+        overwrites them has to wait for it), and their memory is torch's own, on the handle's
+        device (fixed storage is some other library's), so that torch can keep it."""
+        return (all(a.device.index == self._device and a.untyped_storage().resizable()
+                    for a in arrays) and not self._foreign_stream(arrays[0].device))
 
     def close(self):
         if getattr(self, "h", None) is not None and self.h.value:
@@ -233,13 +257,17 @@ class RodBatch:
         for a, s in zip((x, v, q, w), sizes):
             if (a.size if isinstance(a, np.ndarray) else a.numel()) != s:
                 raise ValueError("state array of %d values expected" % s)
+        # device arrays: the call may return with the copies queued (see _may_queue)
         on_device = dev.pop()
-        _check(lib().rod_set_state(self.h, *[C.c_void_p(p) for p, _ in ptrs], on_device,
-                                   float(t0)), self.h)
-        if on_device and self._foreign_stream(x.device):
-            # the caller may free the arrays on its own stream when this returns
-            import torch
-            torch.cuda.ExternalStream(self.stream, device=x.device).synchronize()
+        queued = on_device and self._may_queue((x, v, q, w))
+        _check(lib().rod_set_state(self.h, *[C.c_void_p(p) for p, _ in ptrs],
+                                   DEVICE_QUEUED if queued else on_device, float(t0)), self.h)
+        if queued:
+            # each array's memory may belong to another stream, which hands it out again once
+            # the array is freed: not before the copies on the handle's stream are done
+            stream = self._torch_stream(x.device)
+            for a in (x, v, q, w):
+                a.record_stream(stream)
 
     def set_state_rods(self, states, t0: float = 0.0):
         """Set from a list of ``RodState`` (any float dtype), concatenated in rod order."""

@@ -1,0 +1,45 @@
+"""What the library's host code decides, on a HIP runtime that runs no kernel (tests/hip_stub.hip):
+waits, launches, captures and failed allocations."""
+import ctypes as C
+import os
+
+import numpy as np
+import pytest
+
+import host_stub
+from paper_2509_04277_amd import rod as R
+from paper_2509_04277_amd import workloads as W
+
+STREAM = 0x1000   # (any address: the runtime only compares them)
+
+
+@pytest.fixture(scope="module")
+def built(tmp_path_factory):
+    if not os.path.exists(host_stub.HIPCC):
+        pytest.skip("needs hipcc")
+    return host_stub.Stub(host_stub.build(str(tmp_path_factory.mktemp("stub"))))
+
+
+@pytest.fixture
+def stub(built, monkeypatch):
+    monkeypatch.setattr(R, "_lib", built.lib)
+    built.lib.stub_reset()
+    return built
+
+
+def _handle(n, stream=STREAM, inext=True, count=1):
+    """A handle of clamped rods of n elements with a state."""
+    spec, st = W.straight_rod(n, dt=1e-6, inextensible=inext)
+    b = R.RodBatch([spec] * count, stream)
+    b.set_state_rods([st] * count)
+    return b
+
+
+def test_set_state_waits_unless_told_not_to(stub):
+    b = _handle(100)
+    arrays = [np.zeros(k, np.float32) for k in (303, 303, 400, 300)]
+    for on_device, waits in ((0, 1), (1, 1), (R.DEVICE_QUEUED, 0)):
+        before = stub.lib.stub_syncs()
+        assert stub.lib.rod_set_state(b.h, *[C.c_void_p(a.ctypes.data) for a in arrays], on_device, 0.0) == 0
+        assert stub.lib.stub_syncs() - before == waits
+    b.close()
