@@ -1404,7 +1404,9 @@ __global__ __launch_bounds__(64 * W) void rod_resident_kernel(
 //   points, same order) of the points that were within contact distance + margin of it when
 //   the list was built; the lists are rebuilt, for the whole group, only when some point has
 //   moved more than 0.45 x margin since, so every contact is among the candidates and the
-//   contacts found are exactly those of a scan of all points.  A build groups 8 consecutive
+//   contacts found are exactly those of a scan of all points.  (Movements are told from
+//   positions of one float each, sqrt(3) ulps off at most: where the coordinates are so large that
+//   the margin's last tenth does not cover this, a point may move 0.5 x margin less 5 ulps.)  A build groups 8 consecutive
 //   points into a bounding sphere (one thread each), marks the pairs of spheres that come
 //   within the margin of each other, and scans the points of those spheres; a point with too
 //   many candidates falls back to its exact contacts and forces a new build next step.  The
@@ -1459,6 +1461,11 @@ __device__ __forceinline__ SphereGap sphere_gap(V3 xi, V3 li, V3 xj, V3 lj, floa
   const double S = __builtin_fma(dx, dx, __builtin_fma(dy, dy, dz * dz));
   const double D = (double)ri + (double)rj;
   return {{(float)dx, (float)dy, (float)dz}, (float)__builtin_fma(-D, D, S), (float)S, (float)D};
+}
+
+constexpr float kUlp = 0x1p-23f;   // no ulp of a float is larger, relative to it
+__device__ __forceinline__ float widest(V3 a) {
+  return fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fabsf(a.z));
 }
 
 template <int W, int E, bool CT>
@@ -1545,6 +1552,12 @@ __global__ __launch_bounds__(128 * W) void rod_group_kernel(
     cnt[e] = 0;
     ncand[e] = 0;
   }
+  // square of how far a point may move from `at` before lists are due (negative: at once)
+  auto list_holds = [&](float x, float y, float z) {
+    const float lim = fminf(0.45f * gp.margin, __builtin_fmaf(-5.f * kUlp, widest({x, y, z}), 0.5f * gp.margin));
+    return lim >= 0.f ? lim * lim : -1.f;
+  };
+  float reb2[E];
   if (contact) {
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -1552,13 +1565,13 @@ __global__ __launch_bounds__(128 * W) void rod_group_kernel(
       const int i = L.j0 + e, gs = rd.slot_off + i;
       const float4 b = cbuild[gs];   // NaN position: no valid list
       xbl[sub][i] = b;
+      reb2[e] = list_holds(b.x, b.y, b.z);
       ncand[e] = min(max(__float_as_int(b.w), 0), kContactCand);
       for (int c = 0; c < ncand[e]; ++c)
         quad_put(cand[sub][c >> 2][i], c & 3, ccand[(size_t)gs * kContactCand + c]);
     }
   }
   const int skip = rd.self_skip;
-  const float reb2 = (0.45f * gp.margin) * (0.45f * gp.margin);
   const int s0 = (nrod[0] + kSphereSize - 1) / kSphereSize;
   const int ns = s0 + (nrod[1] + kSphereSize - 1) / kSphereSize;
   clamp_init(rd, cbuf[sub], L.g);   // (the first step's barriers come before its read)
@@ -1633,7 +1646,7 @@ __global__ __launch_bounds__(128 * W) void rod_group_kernel(
         if (!L.ok[e]) continue;
         const float4 b = xbl[sub][L.j0 + e];
         const V3 d = L.X[e] - V3{b.x, b.y, b.z};
-        mv = mv || !(dot(d, d) <= reb2);
+        mv = mv || !(dot(d, d) <= reb2[e]);
       }
       const bool wmv = __ballot(mv) != 0ull;
       if ((threadIdx.x & 63) == 0) moved[s & 1][threadIdx.x >> 6] = wmv ? 1 : 0;
@@ -1661,7 +1674,7 @@ __global__ __launch_bounds__(128 * W) void rod_group_kernel(
             const float4 p = xs[r][j];
             d2 = fmaxf(d2, (p.x - cx) * (p.x - cx) + (p.y - cy) * (p.y - cy) + (p.z - cz) * (p.z - cz));
           }
-          sph[t] = make_float4(cx, cy, cz, sqrtf(d2) + rm);
+          sph[t] = make_float4(cx, cy, cz, sqrtf(d2) + rm + 2.f * kUlp * widest({cx, cy, cz}));
         }
         __syncthreads();
         // one 32-sphere word of one sphere's row per thread; neighbouring threads take
@@ -1692,6 +1705,7 @@ __global__ __launch_bounds__(128 * W) void rod_group_kernel(
             b.x = __int_as_float(0x7fc00000);   // build again next step
           }
           ncand[e] = n;
+          reb2[e] = list_holds(b.x, b.y, b.z);
           b.w = __int_as_float(n);
           xbl[sub][L.j0 + e] = b;
         }

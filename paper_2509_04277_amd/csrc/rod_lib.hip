@@ -124,7 +124,8 @@ const GroupEntry kGroups[] = {
 // in every step: half the radius where elements are as long as it, less as the square of their
 // length below.  50 steps of two crossing rods, radius 10 mm on 1 m, us, at 1/2 / this / 1/16 of
 // the radius: 2 x 16 195 / 194 / 254; 2 x 128 257 / 252 / 225; 2 x 300 683 / 545 / 548; 2 x 512
-// 3935 / 624 / 649.  (Not below 20 um: movements are told from positions of one float each.)
+// 3935 / 624 / 649.  (Not below 20 um: movements are told from positions of one float each; see the
+// group kernel's rule for large coordinates.)
 static float contact_margin(float rmax, int self_skip) {
   const float rel = std::min(0.5f, std::max(0.05f, 2.f / ((float)self_skip * (float)self_skip)));
   return std::max(rel * rmax, std::min(0.5f * rmax, 2e-5f));
