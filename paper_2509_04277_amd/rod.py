@@ -477,8 +477,10 @@ def rollout_function():
     class RodRollout(torch.autograd.Function):
         @staticmethod
         def forward(ctx, batch, bend, twist, x0, v0, q0, w0, n_steps, ckpt_every):
-            mult = torch.stack((bend.detach(), twist.detach())).cpu().numpy()   # one copy, one wait
-            batch.set_stiffness_mult(mult[0], mult[1])
+            mult = [bend.detach().reshape(-1), twist.detach().reshape(-1)]
+            if mult[0].device == mult[1].device and mult[0].dtype == mult[1].dtype:
+                mult = torch.cat(mult).cpu().split([m.numel() for m in mult])   # one copy, one wait
+            batch.set_stiffness_mult(*(m.cpu().numpy() for m in mult))
             batch.set_state(x0.detach().contiguous(), v0.detach().contiguous(),
                             q0.detach().contiguous(), w0.detach().contiguous())
             tips = torch.empty((len(batch.n), int(n_steps), 3), dtype=torch.float32, device=x0.device)
