@@ -451,7 +451,10 @@ void default_shape(int n, int* w, int* e) {
 // wavefronts of several 2 x 2 workgroups on a compute unit share two of its SIMDs: 4.8), while
 // one wavefront of four elements (3.4 and 1.64) issues half the instructions per element and
 // wins once the SIMDs are shared: 12 rods per compute unit take 9.2 us that way and 15.5 as 4 x 1.
-// Calls of 60 steps, 2 x 2 / 4 x 1 / 1 x 4: 300 rods 232 / 207 / - us, 1200 rods 309 / 299 / 259.
+// Calls of 60 steps of 130 to 256 elements, half the rods extensible, 2 x 2 / 4 x 1 / 1 x 4: 300
+// rods 232 / 207 / - us, 1200 rods 309 / 299 / 258 (331 with the extensible half alone as 4 x 1).
+// Handles of extensible rods iterate nothing, and four wavefronts overlap better until they are 8
+// per SIMD; device time 520 rods 106 / 95 / 112 us, 1200 rods 155 / 153 / 187, 3000 297 / 312 / 284.
 // (One wavefront of eight elements for 257 to 512 was slower than 4 x 2 at every load: 1000 rods
 // 614 against 327.)
 void plain_shape(const rod_ctx* c, int r, int* w, int* e) {
@@ -505,9 +508,12 @@ rod_status make_buckets(rod_ctx* c, ShapeFn shape) {
 // Buckets of the default shapes, for the load that the handle's rods make together.
 rod_status make_plain_buckets(rod_ctx* c) {
   long long waves = 0;   // in the shapes of shortest step
-  for (int r = 0; r < c->n_rods; ++r)
+  bool iterates = false;   // some rod that plain_shape asks about has constraint iterations
+  for (int r = 0; r < c->n_rods; ++r) {
     if (c->n[r] <= c->chunk_above) waves += c->n[r] <= 128 ? 1 : c->n[r] <= 1024 ? 4 : 8;
-  c->crowded = waves > 8LL * c->cus;   // more than two wavefronts per SIMD
+    iterates = iterates || (c->n[r] > 128 && c->n[r] <= 256 && c->rods[r].n_iter > 0);
+  }
+  c->crowded = waves > (iterates ? 8LL : 32LL) * c->cus;   // wavefronts per compute unit
   return make_buckets(c, [&](int r, int* w, int* e) { plain_shape(c, r, w, e); });
 }
 

@@ -43,3 +43,22 @@ def test_set_state_waits_unless_told_not_to(stub):
         assert stub.lib.rod_set_state(b.h, *[C.c_void_p(a.ctypes.data) for a in arrays], on_device, 0.0) == 0
         assert stub.lib.stub_syncs() - before == waits
     b.close()
+
+
+@pytest.mark.parametrize("count,inext,one_wave", [
+    (500, False, False), (1200, False, False), (2048, False, False), (2049, False, True),
+    (512, True, False), (513, True, True), (1200, True, True)])
+def test_shape_of_many_mid_rods(stub, count, inext, one_wave):
+    """Rods of 129 to 256 elements: one wavefront each from 8 wavefronts per compute unit on, in
+    the shape of four; for handles without constraint iterations, which lose by it, from 32 on."""
+    b = _handle(200, inext=inext, count=count)
+    assert [x[:3] for x in b.buckets()] == [(1, 4, count) if one_wave else (4, 1, count)]
+    b.close()
+
+
+def test_shape_of_mixed_mid_rods(stub):
+    """One bucket for extensible and inextensible rods together."""
+    (e, se), (i, si) = (W.straight_rod(200, dt=1e-6, inextensible=k) for k in (False, True))
+    b = R.RodBatch([e] * 400 + [i] * 400, STREAM)
+    assert [x[:3] for x in b.buckets()] == [(1, 4, 800)]
+    b.close()
