@@ -156,6 +156,8 @@ struct rod_ctx {
   float *d_fext = nullptr, *d_text = nullptr;
   int* d_status = nullptr;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
+  hipEvent_t ev_long = nullptr;   // the end of the last run of coupled chunks (see LongGate)
+  hipEvent_t ev_end = nullptr;    // of the two, the end of the last step
   bool have_state = false;
   long long steps_done = 0;
   double t0 = 0.0;
@@ -791,18 +793,19 @@ rod_status spread_rods(rod_ctx* c) {
   return ROD_OK;
 }
 
-// Whether the next step runs on c->spread: nothing set that its kernel does not do, and no stream
-// capture (the order among chunked runs is kept by events of other streams).
-bool spread_now(const rod_ctx* c) {
-  if (!c->spread.n_chunks || !c->own_shapes || c->lng.n_chunks || !c->groups.empty() || c->n_haptic ||
-      c->env_nodes)
-    return false;
+// Whether the handle's stream may be capturing (also where the runtime does not tell).
+bool captures(const rod_ctx* c) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
-  return cap == hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
+// Whether the next step runs on c->spread: nothing set that its kernel does not do, and no stream
+// capture (a replay is not kept apart from other chunked runs).
+bool spread_now(const rod_ctx* c) {
+  return c->spread.n_chunks && c->own_shapes && !c->lng.n_chunks && c->groups.empty() &&
+         !c->n_haptic && !c->env_nodes && !captures(c);
 }
 
 // Chunked long rods: one ordinary launch of ks steps.  The chunks wait on their neighbours, so
@@ -829,12 +832,14 @@ rod_status launch_long(rod_ctx* c, const rod_ctx::LongSet& l, StateArrays sa, in
 // within one workgroup per compute unit, so that no two grids hold the compute units against
 // each other: a run whose chunks do not fit beside those of other streams' unfinished runs waits
 // for them (their events; runs on one stream follow each other anyway).  Runs that fit go on
-// side by side.  rod_destroy takes the handle's event out.
+// side by side.  rod_destroy takes the handle's event out.  The events are the gate's alone: one
+// that a handle also recorded in a stream capture could neither be asked nor waited for.  Captured
+// runs do not pass the gate (it orders what is enqueued now; their replays come later).
 struct LongGate {
   struct Run {
     hipStream_t stream = nullptr;
-    hipEvent_t done = nullptr;   // the end event of the stream's last chunked run (a handle's ev1)
-    int chunks = 0;              // the largest of its unfinished runs; 0: finished
+    hipEvent_t done = nullptr;   // the end of the stream's last chunked run (a handle's ev_long)
+    int chunks = 0;              // the largest of its unfinished runs
   };
   std::mutex m;
   std::vector<Run> runs[kMaxDevices];
@@ -847,8 +852,19 @@ LongGate& long_gate() {
 // State arrays of a launch on the handle's own state.
 StateArrays handle_state(rod_ctx* c) { return {c->d_x, c->d_v, c->d_q, c->d_w, c->d_xl, c->d_ql}; }
 
-// Steps the chunks of l on the handle's stream, spl steps per launch, and records ev1 after
-// them if they are coupled.
+// Whether an event's work is done.  (A thread that another one's stream capture in the global mode
+// restricts may ask in the relaxed mode only; asking otherwise would end that capture.)
+bool event_passed(hipEvent_t e) {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  const bool passed = hipEventQuery(e) == hipSuccess;
+  if (!passed) (void)hipGetLastError();   // (not ready)
+  if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  return passed;
+}
+
+// Steps the chunks of l on the handle's stream, spl steps per launch, and records ev_long after
+// them if they are coupled (and not captured).
 rod_status step_long(rod_ctx* c, const rod_ctx::LongSet& l, int n_steps, int spl, int* launches) {
   auto run = [&]() -> rod_status {
     for (int done = 0; done < n_steps; done += spl) {
@@ -859,18 +875,18 @@ rod_status step_long(rod_ctx* c, const rod_ctx::LongSet& l, int n_steps, int spl
     }
     return ROD_OK;
   };
-  if (!l.coupled) return run();   // chunks that wait for nothing need no company
+  // chunks that wait for nothing need no company
+  if (!l.coupled || captures(c)) return run();
   const int dev = c->device;
   if (dev < 0 || dev >= kMaxDevices) return fail(c, ROD_E_DEVICE, "device index out of range");
   LongGate& g = long_gate();
   std::lock_guard<std::mutex> lock(g.m);
   auto& runs = g.runs[dev];
   for (size_t i = runs.size(); i-- > 0;) {   // finished runs of other streams leave
-    if (runs[i].stream == c->stream || hipEventQuery(runs[i].done) != hipSuccess) continue;
+    if (runs[i].stream == c->stream || !event_passed(runs[i].done)) continue;
     runs[i] = runs.back();
     runs.pop_back();
   }
-  (void)hipGetLastError();   // (hipErrorNotReady of the unfinished ones)
   LongGate::Run* mine = nullptr;
   int others = 0;
   for (LongGate::Run& o : runs) {
@@ -881,10 +897,11 @@ rod_status step_long(rod_ctx* c, const rod_ctx::LongSet& l, int n_steps, int spl
     for (const LongGate::Run& o : runs)
       if (o.stream != c->stream) HIP_TRY(c, hipStreamWaitEvent(c->stream, o.done, 0));
   const rod_status st = run();
-  HIP_TRY(c, hipEventRecord(c->ev1, c->stream));
+  HIP_TRY(c, hipEventRecord(c->ev_long, c->stream));
   // (of several handles on one stream the last one's event stands for all)
-  if (mine) *mine = {c->stream, c->ev1, std::max(mine->chunks, l.n_chunks)};
-  else runs.push_back({c->stream, c->ev1, l.n_chunks});
+  if (mine) *mine = {c->stream, c->ev_long, std::max(mine->chunks, l.n_chunks)};
+  else runs.push_back({c->stream, c->ev_long, l.n_chunks});
+  c->ev_end = c->ev_long;
   return st;
 }
 
@@ -895,7 +912,7 @@ void leave_long_gate(rod_ctx* c) {
   std::lock_guard<std::mutex> lock(g.m);
   auto& runs = g.runs[c->device];
   for (size_t i = runs.size(); i-- > 0;)
-    if (runs[i].done == c->ev1) runs.erase(runs.begin() + i);
+    if (runs[i].done == c->ev_long) runs.erase(runs.begin() + i);
 }
 
 // ---- scratch of rod_step_state_noalloc -----------------------------------------------------
@@ -1175,9 +1192,10 @@ rod_status launch_steps(rod_ctx* c, int n_steps, int spl, bool time_it, int buck
   if (bucket < 0 && spread_now(c)) {
     if (time_it) HIP_TRY(c, hipEventRecord(c->ev0, c->stream));
     int launches = 0;
+    c->ev_end = c->ev1;
     const rod_status rs = step_long(c, c->spread, n_steps, spl, &launches);
     if (rs != ROD_OK) return rs;
-    if (time_it && !c->spread.coupled) HIP_TRY(c, hipEventRecord(c->ev1, c->stream));
+    if (time_it && c->ev_end == c->ev1) HIP_TRY(c, hipEventRecord(c->ev1, c->stream));
     c->timed = time_it;
     c->last_launches = launches;
     c->steps_done += n_steps;
@@ -1223,14 +1241,14 @@ rod_status launch_steps(rod_ctx* c, int n_steps, int spl, bool time_it, int buck
       HIP_TRY(c, hipStreamWaitEvent(c->stream, c->bevents[gi], 0));
     }
   }
+  c->ev_end = c->ev1;
   // chunked long rods on the handle's stream, after the buckets (all of a chunked grid's
   // workgroups must be resident together)
   if (bucket < 0 && c->lng.n_chunks) {
     rod_status rs = step_long(c, c->lng, n_steps, spl, &launches);
     if (rs != ROD_OK) return rs;
   }
-  const bool recorded = bucket < 0 && c->lng.n_chunks && c->lng.coupled;   // by step_long
-  if (time_it && !recorded) HIP_TRY(c, hipEventRecord(c->ev1, c->stream));
+  if (time_it && c->ev_end == c->ev1) HIP_TRY(c, hipEventRecord(c->ev1, c->stream));
   c->timed = time_it;
   c->last_launches = launches;
   c->steps_done += n_steps;
@@ -1478,6 +1496,7 @@ rod_status rod_create(const rod_params* params, int32_t n_rods, void* hip_stream
   if (e == hipSuccess) e = hipMemset(c->d_status, 0, sizeof(int));
   if (e == hipSuccess) e = hipEventCreate(&c->ev0);
   if (e == hipSuccess) e = hipEventCreate(&c->ev1);
+  if (e == hipSuccess) e = hipEventCreate(&c->ev_long);
   if (e != hipSuccess) return cleanup(hip_fail(nullptr, e, "rod_create device setup"));
   {
     rod_status st = setup_long_rods(c);
@@ -1515,6 +1534,7 @@ rod_status rod_destroy(rod_ctx* c) {
   free_long_set(c->spread);
   if (c->ev0) (void)hipEventDestroy(c->ev0);
   if (c->ev1) (void)hipEventDestroy(c->ev1);
+  if (c->ev_long) (void)hipEventDestroy(c->ev_long);
   if (c->aux) {
     (void)hipStreamSynchronize(c->aux);
     (void)hipStreamDestroy(c->aux);
@@ -1853,8 +1873,8 @@ rod_status rod_set_contact(rod_ctx* c, int32_t n_sets, const int32_t* sets, doub
 rod_status rod_last_step_time(rod_ctx* c, float* ms, int32_t* launches) {
   if (!c || !ms || !launches) return fail(nullptr, ROD_E_INVALID, "null argument");
   if (!c->timed) return fail(c, ROD_E_ORDER, "no timed rod_step yet");
-  HIP_TRY(c, hipEventSynchronize(c->ev1));
-  HIP_TRY(c, hipEventElapsedTime(&c->last_ms, c->ev0, c->ev1));
+  HIP_TRY(c, hipEventSynchronize(c->ev_end));
+  HIP_TRY(c, hipEventElapsedTime(&c->last_ms, c->ev0, c->ev_end));
   *ms = c->last_ms;
   *launches = c->last_launches;
   return ROD_OK;

@@ -24,13 +24,20 @@ def built(tmp_path_factory):
 def stub(built, monkeypatch):
     monkeypatch.setattr(R, "_lib", built.lib)
     built.lib.stub_reset()
-    return built
+    _handles.clear()
+    yield built
+    for b in _handles:
+        b.close()
+
+
+_handles = []   # of the running test
 
 
 def _handle(n, stream=STREAM, inext=True, count=1):
     """A handle of clamped rods of n elements with a state."""
     spec, st = W.straight_rod(n, dt=1e-6, inextensible=inext)
     b = R.RodBatch([spec] * count, stream)
+    _handles.append(b)
     b.set_state_rods([st] * count)
     return b
 
@@ -42,7 +49,6 @@ def test_set_state_waits_unless_told_not_to(stub):
         before = stub.lib.stub_syncs()
         assert stub.lib.rod_set_state(b.h, *[C.c_void_p(a.ctypes.data) for a in arrays], on_device, 0.0) == 0
         assert stub.lib.stub_syncs() - before == waits
-    b.close()
 
 
 @pytest.mark.parametrize("count,inext,one_wave", [
@@ -53,12 +59,54 @@ def test_shape_of_many_mid_rods(stub, count, inext, one_wave):
     the shape of four; for handles without constraint iterations, which lose by it, from 32 on."""
     b = _handle(200, inext=inext, count=count)
     assert [x[:3] for x in b.buckets()] == [(1, 4, count) if one_wave else (4, 1, count)]
-    b.close()
 
 
 def test_shape_of_mixed_mid_rods(stub):
     """One bucket for extensible and inextensible rods together."""
     (e, se), (i, si) = (W.straight_rod(200, dt=1e-6, inextensible=k) for k in (False, True))
-    b = R.RodBatch([e] * 400 + [i] * 400, STREAM)
-    assert [x[:3] for x in b.buckets()] == [(1, 4, 800)]
-    b.close()
+    _handles.append(R.RodBatch([e] * 400 + [i] * 400, STREAM))
+    assert [x[:3] for x in _handles[0].buckets()] == [(1, 4, 800)]
+
+
+def _windows(launches):
+    return [l for l in launches if "rod_window_kernel" in l.kernel or "rod_grid_kernel" in l.kernel]
+
+
+def test_a_captured_step_leaves_other_handles_alone(stub):
+    """A handle that stepped as chunks and then steps under capture: the event that other handles'
+    chunks wait for is not the one recorded in the capture."""
+    a, b = _handle(2048, 0x1000), _handle(95000, 0x2000)
+    a.step(10, 10)
+    stub.lib.stub_capture(0x1000, 1)
+    before = stub.lib.stub_launches()
+    a.step(10, 10)
+    assert not _windows(stub.launches(before)), "a captured step is not spread"
+    stub.lib.stub_capture(0x1000, 0)
+    b.step(10, 10)   # its chunks do not fit beside the other's, which are finished
+    assert sum(l.grid for l in _windows(stub.launches())) > 256
+    assert stub.lib.stub_waits() == 0 and stub.lib.stub_broken_captures() == 0
+    a.step(10, 10)
+    a.last_step_time()
+
+
+def test_captured_long_rods_do_not_pass_the_gate(stub):
+    a, b = _handle(65536, 0x1000), _handle(65536, 0x2000)
+    a.step(10, 10)
+    stub.lib.stub_hold(0x1000, 1)
+    stub.lib.stub_capture(0x2000, 1)
+    b.step(10, 10)
+    stub.lib.stub_capture(0x2000, 0)
+    stub.lib.stub_hold(0x1000, 0)
+    a.step(10, 10)
+    assert len(_windows(stub.launches())) == 3
+    assert stub.lib.stub_waits() == 0 and stub.lib.stub_broken_captures() == 0
+
+
+def test_steps_beside_a_capture_of_another_thread(stub):
+    """Asking whether another handle's run is done would end a capture in the global mode."""
+    a, b = _handle(2048, 0x1000), _handle(2048, 0x2000)
+    a.step(10, 10)
+    stub.lib.stub_strict(1)
+    b.step(10, 10)
+    stub.lib.stub_strict(0)
+    assert stub.lib.stub_broken_captures() == 0
