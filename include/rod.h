@@ -115,11 +115,13 @@ typedef struct rod_tuning {
  * coefficients (masses, inertias, stiffnesses of eqs. (2), (3), (8)) in FP64 on the host.
  * Rods of up to 2048 elements are stepped by one workgroup each; longer rods are split into
  * chunks of up to about 500 elements, one workgroup per chunk, that exchange halos once every
- * few steps (see rod_set_chunking); so are shorter rods of a handle (more than 128 elements, or 256
- * with fewer than five constraint iterations) while it holds few plain rods and neither
- * rod_set_tuning, rod_set_chunking nor rod_autotune was called: the states are the same bits
- * (all chunks of a handle must be resident on the device at once: ROD_E_UNSUPPORTED if not,
- * and for any rod longer than 131072 elements).
+ * few steps (see rod_set_chunking): all chunks of a handle must be resident on the device at
+ * once (ROD_E_UNSUPPORTED if not, and for any rod longer than 131072 elements).
+ * Shorter rods of a handle (more than 128 elements, or 256 with fewer than five constraint
+ * iterations) are spread over chunks too while the handle holds few plain rods and neither
+ * rod_set_tuning, rod_set_chunking nor rod_autotune was called: the states are the same bits.
+ * This is decided at each rod_step: one that is captured, or whose chunks would have to wait for
+ * those of other handles, steps in one workgroup per rod (rod_chunk_info tells).
  * The state is zero until rod_set_state().  Errors: INVALID (bad sizes/values), NOMEM,
  * DEVICE, UNSUPPORTED. */
 rod_status rod_create(const rod_params* params, int32_t n_rods, void* hip_stream, rod_ctx** out);
@@ -183,6 +185,10 @@ rod_status rod_get_tuning(const rod_ctx* ctx, rod_tuning* t);
  * a pair bucket's shape is per rod); ROD_E_INVALID past the end. */
 rod_status rod_bucket_info(const rod_ctx* ctx, int32_t bucket, rod_tuning* t, int32_t* n_rods);
 
+/* Workgroups of chunks: planned for the next rod_step (0: every rod steps in one workgroup), and
+ * in the last one. */
+rod_status rod_chunk_info(const rod_ctx* ctx, int32_t* planned, int32_t* last);
+
 /* Step every rod longer than min_elements (1..2048; default 2048) with the chunked long-rod
  * kernel: one workgroup per chunk, neighbouring chunks trading H = T (2 n_constraint_iters + 2)
  * + 2 (rounded up to even) halo elements per side once every T steps, so a rod of up to 2048
@@ -197,12 +203,12 @@ rod_status rod_bucket_info(const rod_ctx* ctx, int32_t bucket, rod_tuning* t, in
  * default shapes (as after rod_create).  A held adjoint rollout is dropped if any rod ends up
  * chunked.  All chunks of a handle must be resident on the device together: chunked steps of the
  * process's handles run side by side on a device while their chunks together are at most its
- * compute units, else after each other (stream order through the handles' events), and a chunk
- * whose neighbour does not arrive gives up after a bounded wait of several seconds (rod_sync
- * then reports ROD_E_TIMEOUT), for instance when another
- * process holds the compute units.  Errors: INVALID, UNSUPPORTED (too many constraint
- * iterations to split a rod, or more chunks than the device holds at once; the default split
- * is then restored), DEVICE. */
+ * compute units, else after each other (stream order through the handles' events; captured ones
+ * are not ordered), and a chunk whose neighbour does not arrive gives up after a bounded wait
+ * (several seconds, half a minute for rods that the library spread by itself; rod_sync then
+ * reports ROD_E_TIMEOUT), for instance when another process holds the compute units.
+ * Errors: INVALID, UNSUPPORTED (too many constraint iterations to split a rod, or more chunks
+ * than the device holds at once; the default split is then restored), DEVICE. */
 rod_status rod_set_chunking(rod_ctx* ctx, int32_t min_elements, int32_t chunk_elements);
 
 /* ---- Binding constraints (Sec. 2.1 "Constraints"; Sec. 3.4 variants 1 and 2) ----------

@@ -242,6 +242,7 @@ struct rod_ctx {
   hipEvent_t ev_fork = nullptr;
   float last_ms = 0.f;
   int last_launches = 0;
+  int last_chunks = 0;   // workgroups of chunks in the last step
   bool timed = false;
   std::string err;
 };
@@ -801,12 +802,13 @@ bool captures(const rod_ctx* c) {
   return true;
 }
 
-// Whether the next step runs on c->spread: nothing set that its kernel does not do, and no stream
-// capture (a replay is not kept apart from other chunked runs).
-bool spread_now(const rod_ctx* c) {
+// Whether steps run on c->spread: nothing set that its kernel does not do, and no stream capture (a
+// replay is not kept apart from other chunked runs).
+bool spread_planned(const rod_ctx* c) {
   return c->spread.n_chunks && c->own_shapes && !c->lng.n_chunks && c->groups.empty() &&
-         !c->n_haptic && !c->env_nodes && !captures(c);
+         !c->n_haptic && !c->env_nodes;
 }
+bool spread_now(const rod_ctx* c) { return spread_planned(c) && !captures(c); }
 
 // Chunked long rods: one ordinary launch of ks steps.  The chunks wait on their neighbours, so
 // all workgroups of the grid must be resident together: the grid fits the device (checked when
@@ -831,8 +833,8 @@ rod_status launch_long(rod_ctx* c, const rod_ctx::LongSet& l, StateArrays sa, in
 // Keeps the chunked runs of all handles of the process that may be in flight together, per device,
 // within one workgroup per compute unit, so that no two grids hold the compute units against
 // each other: a run whose chunks do not fit beside those of other streams' unfinished runs waits
-// for them (their events; runs on one stream follow each other anyway).  Runs that fit go on
-// side by side.  rod_destroy takes the handle's event out.  The events are the gate's alone: one
+// for them (their events; runs on one stream follow each other anyway), or steps another way where
+// the library chose the chunks.  Runs that fit go on side by side.  rod_destroy takes the handle's event out.  The events are the gate's alone: one
 // that a handle also recorded in a stream capture could neither be asked nor waited for.  Captured
 // runs do not pass the gate (it orders what is enqueued now; their replays come later).
 struct LongGate {
@@ -864,7 +866,9 @@ bool event_passed(hipEvent_t e) {
 }
 
 // Steps the chunks of l on the handle's stream, spl steps per launch, and records ev_long after
-// them if they are coupled (and not captured).
+// them if they are coupled (and not captured).  Rods that only the library chose to spread do not
+// wait for others' runs: no launch is made if they would have to (one workgroup per rod steps them
+// as well, side by side with whatever is in flight).
 rod_status step_long(rod_ctx* c, const rod_ctx::LongSet& l, int n_steps, int spl, int* launches) {
   auto run = [&]() -> rod_status {
     for (int done = 0; done < n_steps; done += spl) {
@@ -893,9 +897,12 @@ rod_status step_long(rod_ctx* c, const rod_ctx::LongSet& l, int n_steps, int spl
     if (o.stream == c->stream) mine = &o;
     else others += o.chunks;
   }
+  if (others + l.n_chunks > c->cus && &l == &c->spread) return ROD_OK;
   if (others + l.n_chunks > c->cus)
     for (const LongGate::Run& o : runs)
       if (o.stream != c->stream) HIP_TRY(c, hipStreamWaitEvent(c->stream, o.done, 0));
+  // (an earlier, larger run of this stream that is over counts no more)
+  if (mine && mine->chunks > l.n_chunks && event_passed(mine->done)) mine->chunks = 0;
   const rod_status st = run();
   HIP_TRY(c, hipEventRecord(c->ev_long, c->stream));
   // (of several handles on one stream the last one's event stands for all)
@@ -1195,11 +1202,14 @@ rod_status launch_steps(rod_ctx* c, int n_steps, int spl, bool time_it, int buck
     c->ev_end = c->ev1;
     const rod_status rs = step_long(c, c->spread, n_steps, spl, &launches);
     if (rs != ROD_OK) return rs;
-    if (time_it && c->ev_end == c->ev1) HIP_TRY(c, hipEventRecord(c->ev1, c->stream));
-    c->timed = time_it;
-    c->last_launches = launches;
-    c->steps_done += n_steps;
-    return ROD_OK;
+    if (launches > 0) {
+      if (time_it && c->ev_end == c->ev1) HIP_TRY(c, hipEventRecord(c->ev1, c->stream));
+      c->timed = time_it;
+      c->last_launches = launches;
+      c->last_chunks = c->spread.n_chunks;
+      c->steps_done += n_steps;
+      return ROD_OK;
+    }
   }
   // the buckets (and the bound-pair buckets) are independent: with several, each steps on its
   // own stream (forked from and joined back to the handle's stream)
@@ -1251,6 +1261,7 @@ rod_status launch_steps(rod_ctx* c, int n_steps, int spl, bool time_it, int buck
   if (time_it && c->ev_end == c->ev1) HIP_TRY(c, hipEventRecord(c->ev1, c->stream));
   c->timed = time_it;
   c->last_launches = launches;
+  c->last_chunks = bucket < 0 ? c->lng.n_chunks : 0;
   c->steps_done += n_steps;
   return ROD_OK;
 }
@@ -1877,6 +1888,13 @@ rod_status rod_last_step_time(rod_ctx* c, float* ms, int32_t* launches) {
   HIP_TRY(c, hipEventElapsedTime(&c->last_ms, c->ev0, c->ev_end));
   *ms = c->last_ms;
   *launches = c->last_launches;
+  return ROD_OK;
+}
+
+rod_status rod_chunk_info(const rod_ctx* c, int32_t* planned, int32_t* last) {
+  if (!c || !planned || !last) return fail(nullptr, ROD_E_INVALID, "null argument");
+  *planned = spread_planned(c) ? c->spread.n_chunks : c->lng.n_chunks;
+  *last = c->last_chunks;
   return ROD_OK;
 }
 

@@ -87,6 +87,7 @@ _SIGS = {
     "rod_set_environment": (C.c_int, [C.c_void_p, C.c_int32, _DP, C.c_double]),
     "rod_environment_info": (C.c_int, [C.c_void_p, C.POINTER(C.c_int32), C.POINTER(C.c_int32)]),
     "rod_stable_dt": (C.c_int, [C.POINTER(rod_params), _DP]),
+    "rod_chunk_info": (C.c_int, [C.c_void_p, C.POINTER(C.c_int32), C.POINTER(C.c_int32)]),
     "rod_last_step_time": (C.c_int, [C.c_void_p, C.POINTER(C.c_float), C.POINTER(C.c_int32)]),
     "rod_set_stiffness_mult": (C.c_int, [C.c_void_p, C.POINTER(C.c_float), C.POINTER(C.c_float)]),
     "rod_step_state_noalloc": (C.c_int, [C.c_void_p, _FP, _FP, _FP, _FP, C.c_int64, C.c_int32,
@@ -445,6 +446,14 @@ class RodBatch:
         """Step rods longer than min_elements with the chunked multi-workgroup kernel, about
         chunk_elements owned elements per workgroup (0: the largest chunk)."""
         _check(lib().rod_set_chunking(self.h, int(min_elements), int(chunk_elements)), self.h)
+
+    @property
+    def chunks(self):
+        """(workgroups of chunks planned for the next step, in the last step); 0: one workgroup
+        per rod."""
+        a, b = C.c_int32(), C.c_int32()
+        _check(lib().rod_chunk_info(self.h, C.byref(a), C.byref(b)), self.h)
+        return int(a.value), int(b.value)
 
     def autotune(self, probe_steps: int = 200, steps_per_launch: int = 10):
         """rod_autotune: time each admissible kernel shape per bucket and keep the fastest;

@@ -110,3 +110,60 @@ def test_steps_beside_a_capture_of_another_thread(stub):
     b.step(10, 10)
     stub.lib.stub_strict(0)
     assert stub.lib.stub_broken_captures() == 0
+
+
+def test_spread_rods_do_not_wait_for_other_handles(stub):
+    """Handles of mid rods in flight on streams of their own: chunks while they fit the compute
+    units together, one workgroup per rod from there on, and nothing waits."""
+    hs = [_handle(2048, 0x1000 * (1 + i)) for i in range(24)]
+    chunks = hs[0].chunks[0]
+    fit = 256 // chunks
+    assert chunks > 1 and fit < len(hs)
+    for i, h in enumerate(hs):
+        h.step(10, 10)
+        stub.lib.stub_hold(0x1000 * (1 + i), 1)
+        assert h.chunks == (chunks, chunks if i < fit else 0)
+        assert h.time()[1] == 10 and h.last_step_time()[1] == 1
+        stub.lib.stub_hold(0x1000 * (1 + i), 1)   # (the timing waited for it)
+    assert stub.lib.stub_waits() == 0
+    stub.lib.stub_hold(0x1000, 0)      # the first is done: its room goes to the last
+    hs[-1].step(10, 10)
+    assert hs[-1].chunks == (chunks, chunks)
+
+
+def test_long_rods_wait_for_what_does_not_fit_beside_them(stub):
+    """Rods that step as chunks only: a run waits for every unfinished one of another stream."""
+    a, b, c = (_handle(17000, 0x1000 * (1 + i)) for i in range(3))
+    n = a.chunks[0]
+    assert 2 * n <= 256 < 3 * n
+    for i, h in enumerate((a, b, c)):
+        assert stub.lib.stub_waits() == 0
+        h.step(20, 10)
+        stub.lib.stub_hold(0x1000 * (1 + i), 1)
+    assert stub.lib.stub_waits() == 2
+    a.step(20, 10)
+    assert stub.lib.stub_waits() == 4
+    assert all(h.chunks == (n, n) for h in (a, b, c))
+    stub.lib.stub_hold(0x3000, 0)
+    b.step(20, 10)      # fits beside the one that is left
+    assert stub.lib.stub_waits() == 4
+
+
+def test_an_earlier_larger_run_of_a_stream_counts_while_it_lasts(stub):
+    """Two handles on one stream: room is taken by the larger run until it is over."""
+    big, small, other = _handle(80000, 0x1000), _handle(2048, 0x1000), _handle(2000, 0x2000)
+    room = 256 - big.chunks[0]
+    more = [_handle(2048, 0x1000 * (3 + i)) for i in range(room // small.chunks[0] + 1)]
+    for held in (1, 0):
+        big.step(10, 10)
+        stub.lib.stub_hold(0x1000, held)
+        small.step(10, 10)
+        stub.lib.stub_hold(0x1000, 1)
+        for i, h in enumerate(more):
+            h.step(10, 10)
+            stub.lib.stub_hold(0x1000 * (3 + i), 1)
+        other.step(10, 10)
+        assert (other.chunks[1] == 0) == bool(held)
+        for i in range(len(more)):
+            stub.lib.stub_hold(0x1000 * (3 + i), 0)
+        stub.lib.stub_hold(0x1000, 0)
