@@ -120,8 +120,9 @@ typedef struct rod_tuning {
  * Shorter rods of a handle (more than 128 elements, or 256 with fewer than five constraint
  * iterations) are spread over chunks too while the handle holds few plain rods and neither
  * rod_set_tuning, rod_set_chunking nor rod_autotune was called: the states are the same bits.
- * This is decided at each rod_step: one that is captured, or whose chunks would have to wait for
- * those of other handles, steps in one workgroup per rod (rod_chunk_info tells).
+ * This is decided at each rod_step: one that is captured, or whose chunks would not fit beside
+ * those of other handles in half the device's compute units, steps in one workgroup per rod
+ * (rod_chunk_info tells).
  * The state is zero until rod_set_state().  Errors: INVALID (bad sizes/values), NOMEM,
  * DEVICE, UNSUPPORTED. */
 rod_status rod_create(const rod_params* params, int32_t n_rods, void* hip_stream, rod_ctx** out);

@@ -771,6 +771,12 @@ rod_status setup_long_rods(rod_ctx* c) {
   return place_chunks(c, l, ch, hmax, cus);
 }
 
+// Most coupled chunks that may be in flight where the library chose to spread rods: half the
+// compute units.  Chunks of one process are counted, other processes' are not, and a device holds two
+// workgroups of chunks per compute unit: four processes that each fill their share still fit
+// together, and none can wait for a neighbour that another process's chunks keep out.
+int spread_room(const rod_ctx* c) { return c->cus / 2; }
+
 // Plans the handle's rods as window chunks (c->spread) where that steps them faster than one
 // workgroup of a resident shape each: plain rods, few enough for one chunk per compute unit, of
 // more than 128 elements with five or more constraint iterations (the windows exchange once per
@@ -790,7 +796,9 @@ rod_status spread_rods(rod_ctx* c) {
   }
   for (int r = 0; r < c->n_rods; ++r) c->spread.rods.push_back(r);
   c->spread.kernel = window_kernel(ch, c->cus);
-  if (place_chunks(c, c->spread, ch, hmax, c->cus) != ROD_OK) free_long_set(c->spread);
+  if (place_chunks(c, c->spread, ch, hmax, c->cus) != ROD_OK ||
+      (c->spread.coupled && c->spread.n_chunks > spread_room(c)))
+    free_long_set(c->spread);
   return ROD_OK;
 }
 
@@ -897,7 +905,7 @@ rod_status step_long(rod_ctx* c, const rod_ctx::LongSet& l, int n_steps, int spl
     if (o.stream == c->stream) mine = &o;
     else others += o.chunks;
   }
-  if (others + l.n_chunks > c->cus && &l == &c->spread) return ROD_OK;
+  if (&l == &c->spread && others + l.n_chunks > spread_room(c)) return ROD_OK;
   if (others + l.n_chunks > c->cus)
     for (const LongGate::Run& o : runs)
       if (o.stream != c->stream) HIP_TRY(c, hipStreamWaitEvent(c->stream, o.done, 0));

@@ -117,7 +117,7 @@ def test_spread_rods_do_not_wait_for_other_handles(stub):
     units together, one workgroup per rod from there on, and nothing waits."""
     hs = [_handle(2048, 0x1000 * (1 + i)) for i in range(24)]
     chunks = hs[0].chunks[0]
-    fit = 256 // chunks
+    fit = 128 // chunks   # half the compute units
     assert chunks > 1 and fit < len(hs)
     for i, h in enumerate(hs):
         h.step(10, 10)
@@ -151,8 +151,9 @@ def test_long_rods_wait_for_what_does_not_fit_beside_them(stub):
 
 def test_an_earlier_larger_run_of_a_stream_counts_while_it_lasts(stub):
     """Two handles on one stream: room is taken by the larger run until it is over."""
-    big, small, other = _handle(80000, 0x1000), _handle(2048, 0x1000), _handle(2000, 0x2000)
-    room = 256 - big.chunks[0]
+    big, small, other = _handle(10000, 0x1000), _handle(2048, 0x1000), _handle(2000, 0x2000)
+    room = 128 - big.chunks[0]
+    assert room > small.chunks[0]
     more = [_handle(2048, 0x1000 * (3 + i)) for i in range(room // small.chunks[0] + 1)]
     for held in (1, 0):
         big.step(10, 10)
@@ -167,3 +168,17 @@ def test_an_earlier_larger_run_of_a_stream_counts_while_it_lasts(stub):
         for i in range(len(more)):
             stub.lib.stub_hold(0x1000 * (3 + i), 0)
         stub.lib.stub_hold(0x1000, 0)
+
+
+def test_four_processes_of_spread_rods_fit_the_device(stub):
+    """A process has at most half the compute units' number of coupled chunks in flight where the
+    library chose them (the device holds two per unit), in one handle or in several; chunks that
+    wait for no neighbour are not limited by this."""
+    for n in (2048, 700, 400):
+        each = _handle(n).chunks[0]
+        assert each > 1
+        for count, spread in ((128 // each, True), (128 // each + 1, False)):
+            h = _handle(n, count=count)
+            assert h.chunks[0] == (count * each if spread else 0)
+            h.close()
+    assert _handle(300, count=200).chunks[0] == 200
