@@ -182,3 +182,23 @@ def test_four_processes_of_spread_rods_fit_the_device(stub):
             assert h.chunks[0] == (count * each if spread else 0)
             h.close()
     assert _handle(300, count=200).chunks[0] == 200
+
+
+def test_a_spread_plan_that_does_not_fit_the_memory_leaves_no_error(stub):
+    """The plan's buffers are an extra: without them rods step in one workgroup each, and the failed
+    allocation is not reported by a later call."""
+    plain = _handle(100)     # (how many allocations a handle makes without a plan)
+    plain.close()
+    before = stub.lib.stub_allocations()
+    full = _handle(2048)
+    made = stub.lib.stub_allocations() - before
+    full.close()
+    for skip in range(made - 4, made):   # the plan's four are a handle's last
+        stub.lib.stub_fail_malloc(skip)
+        h = _handle(2048)
+        stub.lib.stub_fail_malloc(-1)
+        assert h.chunks[0] == 0
+        h.step(10, 10)
+        h.sync()
+        h.close()
+    assert stub.lib.stub_allocations() == before
