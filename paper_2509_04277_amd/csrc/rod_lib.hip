@@ -1589,6 +1589,7 @@ rod_status rod_set_state(rod_ctx* c, const float* x, const float* v, const float
   if (st != ROD_OK) return st;
   mv.add(c->d_xl, nullptr, P3);
   mv.add(c->d_ql, nullptr, F4);
+  mv.add(reinterpret_cast<float*>(c->d_status), nullptr, 1);   // a new run's conditions
   mv.m.rods = c->d_rods;
   mv.m.n_rods = c->n_rods;
   mv.m.t0 = t0;
