@@ -65,7 +65,8 @@ def _counters(kernel_name, elements, spl):
     path = os.path.join(REPO, "profiles", "counters.json")
     if not os.path.exists(path):
         return None
-    e = json.load(open(path)).get(kernel_name)
+    d = json.load(open(path))
+    e = d.get("%s on %d elements" % (kernel_name, elements)) or d.get(kernel_name)
     if not e or e.get("source_hash") != kernel_source_hash():
         return None
     if e.get("elements") != elements or e.get("steps_per_launch") != spl:
@@ -524,7 +525,8 @@ def main():
     ap.add_argument("--steps-per-launch", type=int, default=10)
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--cpu-steps", type=int, default=60000)
-    ap.add_argument("--shape", default="", help="W,E kernel shape (default: autotune)")
+    ap.add_argument("--shape", default="",
+                    help="W,E kernel shape, or own: as the handle steps untuned (default: autotune)")
     ap.add_argument("--no-extras", action="store_true",
                     help="skip the batched (4096 rods), long-rod and adjoint measurements")
     ap.add_argument("--extras", default="batch,long_rod,adjoint,binding,contact,haptic,environment",
@@ -555,7 +557,9 @@ def main():
     specs = [s for s, _ in wl.rods]
     b = R.RodBatch(specs)
     b.set_state_rods([st for _, st in wl.rods])
-    if args.shape:
+    if args.shape == "own":
+        tune = b.tuning
+    elif args.shape:
         w, e = (int(v) for v in args.shape.split(","))
         b.set_tuning(w, e, spl)
         tune = b.tuning
@@ -573,6 +577,7 @@ def main():
     torch.cuda.synchronize()
     wall = time.perf_counter() - t
     ms_dev, launches = b.last_step_time()
+    chunks = b.chunks[1]
     elements = wl.n_elements
     value = elements * args.steps / wall
     # host-visible latency of one 10-step update including the position read-back (Sec. 3.1)
@@ -585,7 +590,9 @@ def main():
         lat.append(time.perf_counter() - t1)
     b.sync()
     b.close()
-    kernel = "rod_resident_kernel<%d,%d>" % (tune["waves"], tune["elems_per_lane"])
+    # (rods spread over chunks; these exchange velocities every step at 10 iterations)
+    kernel = ("rod_window_kernel<true>" if chunks else
+              "rod_resident_kernel<%d,%d>" % (tune["waves"], tune["elems_per_lane"]))
     launch_s = ms_dev / 1e3 / launches
     bytes_per_launch = BYTES_PER_ELEMENT_STEP * elements * spl
     achieved = bytes_per_launch / launch_s / 1e9
@@ -620,9 +627,9 @@ def main():
                      "traffic": traffic,
                      "measured_copy_GBs": copy["GB/s"],
                      "frac_of_measured_copy": achieved / copy["GB/s"],
-                     # what binds this small workload (two rods, one workgroup each): VALU issue
-                     # and waiting (mostly the cross-wavefront exchanges' barriers), as shares
-                     # of wavefront time from SQ counters of the same kernel and workload
+                     # what binds this small workload (two rods in a few workgroups): VALU issue
+                     # and waiting (mostly the exchanges' barriers), as shares of wavefront
+                     # time from SQ counters of the same kernel and workload
                      "valu_issue_frac": shares and shares["valu_issue_frac"],
                      "barrier_share": shares and shares["barrier_share"],
                      "valu_insts_per_wave_step": shares and shares["valu_insts_per_wave_step"],

@@ -118,8 +118,9 @@ typedef struct rod_tuning {
  * few steps (see rod_set_chunking): all chunks of a handle must be resident on the device at
  * once (ROD_E_UNSUPPORTED if not, and for any rod longer than 131072 elements).
  * Shorter rods of a handle (more than 128 elements, or 256 with fewer than five constraint
- * iterations) are spread over chunks too while the handle holds few plain rods and neither
- * rod_set_tuning, rod_set_chunking nor rod_autotune was called: the states are the same bits.
+ * iterations) are spread over chunks too while the handle holds few plain rods, unless
+ * rod_set_tuning or rod_set_chunking was called or rod_autotune found a faster shape: the states
+ * are the same bits.
  * This is decided at each rod_step: one that is captured, or whose chunks would not fit beside
  * those of other handles in half the device's compute units, steps in one workgroup per rod
  * (rod_chunk_info tells).
@@ -177,7 +178,8 @@ rod_status rod_get_time(const rod_ctx* ctx, double* t, int64_t* steps);
  * rod_set_tuning() puts all other rods into one bucket of the given shape (waves in
  * {1,2,4,8,16}, elems_per_lane in {1,2,4,8} as built; ROD_E_UNSUPPORTED if not built or too
  * small for the longest of them).  rod_get_tuning() reports the first bucket's shape and the
- * summed per-step time of the buckets measured by rod_autotune(). */
+ * summed per-step time of the buckets measured by rod_autotune(), or that of the spread rods where
+ * it found them faster (rod_chunk_info). */
 rod_status rod_set_tuning(rod_ctx* ctx, const rod_tuning* t);
 rod_status rod_get_tuning(const rod_ctx* ctx, rod_tuning* t);
 
@@ -317,7 +319,9 @@ rod_status rod_haptic_get_force(rod_ctx* ctx, int32_t rod, rod_haptic_force* out
  * Per bucket, time every built shape that holds its longest rod on probe_steps steps (the
  * state is saved and restored, the step counter unchanged) and keep the fastest, or a shape
  * that another bucket keeps if it is within 2 % of the fastest (the buckets then share one
- * launch); sets the handle's steps_per_launch.  steps_per_launch = 0: first, while the long-rod split is the
+ * launch); sets the handle's steps_per_launch.  Rods that the library spreads by itself (see
+ * rod_create) stay spread where the whole handle steps faster so than in the shapes found.
+ * steps_per_launch = 0: first, while the long-rod split is the
  * default one, the whole handle is timed with its rods of more than 512 elements in one
  * workgroup each and chunked as by rod_set_chunking(ctx, 512, 0), and the faster split is kept
  * (a chunked rod is not differentiated by the adjoint); then the shapes are timed at 10 steps

@@ -175,6 +175,7 @@ struct rod_ctx {
     LongKernel kernel = kLongGrid;
     int n_chunks = 0, pub_slots = 0;
     bool coupled = false;   // some rod has several chunks (they wait on each other)
+    float us_per_step = 0.f;   // measured by rod_autotune
     corde::GridChunk* d_chunks = nullptr;
     int* d_block_chunk = nullptr;
     float* d_pub = nullptr;
@@ -184,7 +185,8 @@ struct rod_ctx {
   // All rods of the handle as window chunks, for steps whose shapes the caller left to the library
   // (see spread_rods); empty where that is not the faster way.
   LongSet spread;
-  bool own_shapes = true;   // neither rod_set_tuning, rod_set_chunking nor rod_autotune was called
+  // rod_set_tuning and rod_set_chunking were not called, and rod_autotune found no faster shapes
+  bool own_shapes = true;
   std::vector<Bucket> buckets;
   bool crowded = false;   // the default shapes share every SIMD between several wavefronts
   // rod groups (bindings, contact): one or two rods per workgroup, grouped by kernel shape
@@ -1740,7 +1742,7 @@ rod_status rod_get_tuning(const rod_ctx* c, rod_tuning* t) {
   t->steps_per_launch = c->steps_per_launch;
   float us = 0.f;
   for (const auto& bb : c->buckets) us += bb.us_per_step;
-  t->us_per_step = us;
+  t->us_per_step = spread_planned(c) && c->spread.us_per_step > 0.f ? c->spread.us_per_step : us;
   return ROD_OK;
 }
 
@@ -2124,7 +2126,6 @@ rod_status rod_autotune(rod_ctx* c, int32_t probe_steps, int32_t steps_per_launc
   if (!c) return fail(nullptr, ROD_E_INVALID, "null handle");
   if (!c->have_state) return fail(c, ROD_E_ORDER, "rod_autotune before rod_set_state");
   if (probe_steps < 1 || steps_per_launch < 0) return fail(c, ROD_E_INVALID, "bad probe sizes");
-  c->own_shapes = false;   // the shapes picked here are the ones stepped
   const bool pick_k = steps_per_launch == 0;   // also choose the steps per launch
   if (pick_k) steps_per_launch = std::min(10, probe_steps);
   // save the state, probe the candidate shapes of every bucket, restore
@@ -2148,6 +2149,10 @@ rod_status rod_autotune(rod_ctx* c, int32_t probe_steps, int32_t steps_per_launc
   }
   const long long saved_steps = c->steps_done;
   rod_status st = ROD_OK;
+  // while the buckets' shapes are timed, rods step in them; the library's own chunk plan, if it was
+  // what the handle stepped by, is timed against the shapes found
+  const bool own = c->own_shapes;
+  c->own_shapes = false;
   // whole-handle time per step at steps_per_launch (best of two probes)
   auto whole = [&](float* us) -> rod_status {
     float ms_best = INFINITY;
@@ -2245,6 +2250,23 @@ rod_status rod_autotune(rod_ctx* c, int32_t probe_steps, int32_t steps_per_launc
       b.us_per_step = 0.f;
       for (const auto& u : us_of)
         if (u.first == (b.waves * 16 + b.elems) * 8 + b.feat) b.us_per_step += u.second;
+    }
+  }
+  if (own) {
+    c->own_shapes = true;
+    c->spread.us_per_step = 0.f;
+    if (st == ROD_OK && spread_planned(c)) {
+      float us_shapes = 0.f, us_spread = 0.f;
+      c->own_shapes = false;
+      st = whole(&us_shapes);
+      c->own_shapes = true;
+      if (st == ROD_OK) st = whole(&us_spread);
+      if (st == ROD_OK && c->last_chunks > 0) {   // (0: no room beside other handles' chunks)
+        c->own_shapes = us_spread < us_shapes;
+        c->spread.us_per_step = us_spread;
+      }
+    } else if (st == ROD_OK) {
+      c->own_shapes = false;   // the shapes picked here are the ones stepped
     }
   }
   if (st == ROD_OK && pick_k) {

@@ -456,7 +456,8 @@ class RodBatch:
         return int(a.value), int(b.value)
 
     def autotune(self, probe_steps: int = 200, steps_per_launch: int = 10):
-        """rod_autotune: time each admissible kernel shape per bucket and keep the fastest;
+        """rod_autotune: time each admissible kernel shape per bucket and keep the fastest (the
+        library's own chunks, see ``chunks``, where they are faster still);
         steps_per_launch = 0 also picks the steps per launch (the smallest count whose time per
         step is within 5 % of the best).  State and step counter are left as they were."""
         t = rod_tuning()

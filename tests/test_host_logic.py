@@ -202,3 +202,49 @@ def test_a_spread_plan_that_does_not_fit_the_memory_leaves_no_error(stub):
         h.sync()
         h.close()
     assert stub.lib.stub_allocations() == before
+
+
+@pytest.mark.parametrize("spl", [10, 0])
+@pytest.mark.parametrize("n", [200, 512, 2048])
+@pytest.mark.parametrize("chunk_us,shape_us", [(20.0, 50.0), (50.0, 20.0)])
+def test_autotune_keeps_the_faster_of_chunks_and_shapes(stub, n, spl, chunk_us, shape_us):
+    h = _handle(n)
+    planned = h.chunks[0]
+    assert planned > 0
+    stub.lib.stub_cost(b"rod_window_kernel", chunk_us)
+    stub.lib.stub_cost(b"rod_resident_kernel", shape_us)
+    t = h.autotune(probe_steps=10, steps_per_launch=spl)
+    h.step(10, 10)
+    assert (h.chunks[1] > 0) == (chunk_us < shape_us)
+    ran = stub.launches()[-1].kernel
+    assert ("rod_window_kernel" if chunk_us < shape_us else "rod_resident_kernel") in ran
+    if h.buckets()[0][3] > 0:    # (a rod that rod_set_chunking chunks reports no time)
+        assert t["us_per_step"] == pytest.approx(min(chunk_us, shape_us) / 10, rel=1e-3)
+    assert h.time()[1] == 10
+
+
+def test_autotune_that_fails_leaves_the_handle_as_it_was(stub):
+    h = _handle(2048)
+    planned = h.chunks[0]
+    stub.lib.stub_fail_malloc(2)
+    with pytest.raises(R.RodError):
+        h.autotune(probe_steps=10)
+    stub.lib.stub_fail_malloc(-1)
+    stub.lib.hipGetLastError()
+    assert h.chunks[0] == planned
+    h.step(10, 10)
+    assert h.chunks[1] == planned
+
+
+def test_autotune_without_room_for_the_chunks(stub):
+    """Other handles' chunks in flight: nothing to time, the handle keeps its plan for later."""
+    others = [_handle(2048, 0x1000 * (2 + i)) for i in range(8)]
+    for i, o in enumerate(others):
+        o.step(10, 10)
+        stub.lib.stub_hold(0x1000 * (2 + i), 1)
+    h = _handle(2048)
+    h.autotune(probe_steps=10)
+    for i in range(len(others)):
+        stub.lib.stub_hold(0x1000 * (2 + i), 0)
+    h.step(10, 10)
+    assert h.chunks[1] == h.chunks[0] > 0
