@@ -488,9 +488,9 @@ def environment_extras(R, W):
 def long_rod_extras(R, W, sizes=(1024, 2048, 4096, 16384, 65536), variants=(False, True),
                     ks=(1, 10, 100)):
     """c2: us/step vs rod length and steps per launch over the workload's 5000 steps.  Rods up
-    to 2048 elements run in one workgroup ("single") and, for comparison, split over several
-    ("chunked"); longer rods are always chunked (one workgroup per ~500 elements, halo exchange
-    through global memory every few steps)."""
+    to 2048 elements run in one workgroup ("single", the shape their bucket has) and, for
+    comparison, split over several ("chunked"); longer rods are always chunked (one workgroup per
+    up to 500 elements, halo exchange through global memory every few steps)."""
     out = []
     for n in sizes:
         for inext in variants:
@@ -501,6 +501,8 @@ def long_rod_extras(R, W, sizes=(1024, 2048, 4096, 16384, 65536), variants=(Fals
                     b = R.RodBatch([spec])
                     if mode == "chunked" and n <= 2048:
                         b.set_chunking(n - 1)
+                    elif mode == "single":   # (untuned, the library may spread it as well)
+                        b.set_tuning(*b.buckets()[0][:2])
                     b.set_state_rods([st])
                     b.step(200, spl)
                     b.set_state_rods([st])
