@@ -899,21 +899,25 @@ rod_status step_long(rod_ctx* c, const rod_ctx::LongSet& l, int n_steps, int spl
   LongGate& g = long_gate();
   std::lock_guard<std::mutex> lock(g.m);
   auto& runs = g.runs[dev];
+  // (the per-thread stream is another one in each thread: its runs count as others')
+  auto same = [&](const LongGate::Run& o) {
+    return o.stream == c->stream && (o.stream != hipStreamPerThread || o.done == c->ev_long);
+  };
   for (size_t i = runs.size(); i-- > 0;) {   // finished runs of other streams leave
-    if (runs[i].stream == c->stream || !event_passed(runs[i].done)) continue;
+    if (same(runs[i]) || !event_passed(runs[i].done)) continue;
     runs[i] = runs.back();
     runs.pop_back();
   }
   LongGate::Run* mine = nullptr;
   int others = 0;
   for (LongGate::Run& o : runs) {
-    if (o.stream == c->stream) mine = &o;
+    if (same(o)) mine = &o;
     else others += o.chunks;
   }
   if (&l == &c->spread && others + l.n_chunks > spread_room(c)) return ROD_OK;
   if (others + l.n_chunks > c->cus)
     for (const LongGate::Run& o : runs)
-      if (o.stream != c->stream) HIP_TRY(c, hipStreamWaitEvent(c->stream, o.done, 0));
+      if (!same(o)) HIP_TRY(c, hipStreamWaitEvent(c->stream, o.done, 0));
   // (an earlier, larger run of this stream that is over counts no more)
   if (mine && mine->chunks > l.n_chunks && event_passed(mine->done)) mine->chunks = 0;
   const rod_status st = run();

@@ -11,6 +11,7 @@ from paper_2509_04277_amd import rod as R
 from paper_2509_04277_amd import workloads as W
 
 STREAM = 0x1000   # (any address: the runtime only compares them)
+PER_THREAD = 2    # hipStreamPerThread
 
 
 @pytest.fixture(scope="module")
@@ -248,3 +249,15 @@ def test_autotune_without_room_for_the_chunks(stub):
         stub.lib.stub_hold(0x1000 * (2 + i), 0)
     h.step(10, 10)
     assert h.chunks[1] == h.chunks[0] > 0
+
+
+def test_per_thread_streams_are_not_one_stream(stub):
+    """Two handles on the per-thread stream may be stepped by two threads, side by side."""
+    a, b = _handle(60000, PER_THREAD), _handle(60000, PER_THREAD)
+    assert a.chunks[0] <= 256 < 2 * a.chunks[0]
+    a.step(10, 10)
+    stub.lib.stub_hold(PER_THREAD, 1)
+    a.step(10, 10)
+    assert stub.lib.stub_waits() == 0
+    b.step(10, 10)
+    assert stub.lib.stub_waits() == 1
