@@ -221,6 +221,13 @@ class RodBatch:
         import torch
         return torch.cuda.current_stream(device).cuda_stream != self.stream
 
+    def _await_current(self, device):
+        """Waits for torch's current stream if it is not the handle's, which is about to read what
+        it makes and to write memory that it may still use."""
+        import torch
+        if self._foreign_stream(device):
+            torch.cuda.current_stream(device).synchronize()
+
     def _torch_stream(self, device):
         """The handle's stream as torch's."""
         import torch
@@ -491,6 +498,7 @@ def rollout_function():
             if mult[0].device == mult[1].device and mult[0].dtype == mult[1].dtype:
                 mult = torch.cat(mult).cpu().split([m.numel() for m in mult])   # one copy, one wait
             batch.set_stiffness_mult(*(m.cpu().numpy() for m in mult))
+            batch._await_current(x0.device)
             batch.set_state(x0.detach().contiguous(), v0.detach().contiguous(),
                             q0.detach().contiguous(), w0.detach().contiguous())
             tips = torch.empty((len(batch.n), int(n_steps), 3), dtype=torch.float32, device=x0.device)
@@ -508,8 +516,10 @@ def rollout_function():
             out = dict(bend=torch.empty(len(b.n), device=dev), twist=torch.empty(len(b.n), device=dev),
                        x=torch.empty(3 * b.n_points, device=dev), v=torch.empty(3 * b.n_points, device=dev),
                        q=torch.empty(4 * b.n_frames, device=dev), w=torch.empty(3 * b.n_frames, device=dev))
+            grad_tips = grad_tips.contiguous().float()
+            b._await_current(dev)
             # (waits for the handle's stream before it returns)
-            b.adjoint_backward(grad_tips.contiguous().float(), out, rollout=ctx.rollout)
+            b.adjoint_backward(grad_tips, out, rollout=ctx.rollout)
             return (None, out["bend"], out["twist"], out["x"], out["v"], out["q"], out["w"], None, None)
 
     return RodRollout
