@@ -221,13 +221,6 @@ class RodBatch:
         import torch
         return torch.cuda.current_stream(device).cuda_stream != self.stream
 
-    def _await_current(self, device):
-        """Waits for torch's current stream if it is not the handle's, which is about to read what
-        it makes and to write memory that it may still use."""
-        import torch
-        if self._foreign_stream(device):
-            torch.cuda.current_stream(device).synchronize()
-
     def _torch_stream(self, device):
         """The handle's stream as torch's."""
         import torch
@@ -235,14 +228,6 @@ class RodBatch:
             self._as_torch = (torch.cuda.ExternalStream(self.stream, device=device) if self.stream
                               else torch.cuda.default_stream(device))
         return self._as_torch
-
-    def _may_queue(self, arrays):
-        """True if a call may return with its reads of the tensors queued on the handle's stream:
-        it is the current stream (as for any torch operation, work on other streams that
-        overwrites them has to wait for it), and their memory is torch's own, on the handle's
-        device (fixed storage is some other library's), so that torch can keep it."""
-        return (all(a.device.index == self._device and a.untyped_storage().resizable()
-                    for a in arrays) and not self._foreign_stream(arrays[0].device))
 
     def close(self):
         if getattr(self, "h", None) is not None and self.h.value:
@@ -257,24 +242,35 @@ class RodBatch:
 
     # ---- state ------------------------------------------------------------------
     def set_state(self, x, v, q, w, t0: float = 0.0):
-        ptrs = [_ptr(a) for a in (x, v, q, w)]
-        dev = {d for _, d in ptrs}
-        if len(dev) != 1:
+        self._set_state((x, v, q, w), t0)
+
+    def _set_state(self, arrays, t0, foreign=None):
+        """foreign: whether the handle's stream is another than torch's current one, if known."""
+        ptrs = [_ptr(a) for a in arrays]
+        on_device = ptrs[0][1]
+        if any(d != on_device for _, d in ptrs):
             raise ValueError("all state arrays must be on the same side")
         sizes = (3 * self.n_points, 3 * self.n_points, 4 * self.n_frames, 3 * self.n_frames)
-        for a, s in zip((x, v, q, w), sizes):
+        for a, s in zip(arrays, sizes):
             if (a.size if isinstance(a, np.ndarray) else a.numel()) != s:
                 raise ValueError("state array of %d values expected" % s)
-        # device arrays: the call may return with the copies queued (see _may_queue)
-        on_device = dev.pop()
-        queued = on_device and self._may_queue((x, v, q, w))
-        _check(lib().rod_set_state(self.h, *[C.c_void_p(p) for p, _ in ptrs],
+        # The call may return with its reads of device arrays queued on the handle's stream if that
+        # is the current one (as for any torch operation, work on other streams that overwrites
+        # them has to wait for it) and their memory is torch's own, on the handle's device (fixed
+        # storage is some other library's), so that torch can keep it.
+        queued = False
+        if on_device and self._device is not None:
+            queued = all([a.get_device() == self._device and a.untyped_storage().resizable()
+                          for a in arrays])
+            if queued:
+                queued = not (self._foreign_stream(self._device) if foreign is None else foreign)
+        _check(lib().rod_set_state(self.h, ptrs[0][0], ptrs[1][0], ptrs[2][0], ptrs[3][0],
                                    DEVICE_QUEUED if queued else on_device, float(t0)), self.h)
         if queued:
             # each array's memory may belong to another stream, which hands it out again once
             # the array is freed: not before the copies on the handle's stream are done
-            stream = self._torch_stream(x.device)
-            for a in (x, v, q, w):
+            stream = self._torch_stream(self._device)
+            for a in arrays:
                 a.record_stream(stream)
 
     def set_state_rods(self, states, t0: float = 0.0):
@@ -494,16 +490,19 @@ def rollout_function():
     class RodRollout(torch.autograd.Function):
         @staticmethod
         def forward(ctx, batch, bend, twist, x0, v0, q0, w0, n_steps, ckpt_every):
-            mult = [bend.detach().reshape(-1), twist.detach().reshape(-1)]
-            if mult[0].device == mult[1].device and mult[0].dtype == mult[1].dtype:
-                mult = torch.cat(mult).cpu().split([m.numel() for m in mult])   # one copy, one wait
-            batch.set_stiffness_mult(*(m.cpu().numpy() for m in mult))
-            batch._await_current(x0.device)
-            batch.set_state(x0.detach().contiguous(), v0.detach().contiguous(),
-                            q0.detach().contiguous(), w0.detach().contiguous())
+            if bend.shape == twist.shape and bend.device == twist.device and bend.dtype == twist.dtype:
+                mult = torch.stack((bend.detach(), twist.detach())).cpu().numpy()   # one copy, one wait
+            else:
+                mult = bend.detach().cpu().numpy(), twist.detach().cpu().numpy()
+            batch.set_stiffness_mult(mult[0], mult[1])
+            foreign = batch._foreign_stream(x0.device)
+            if foreign:   # the handle's stream is about to read what the current one makes
+                torch.cuda.current_stream(x0.device).synchronize()
+            batch._set_state((x0.detach().contiguous(), v0.detach().contiguous(),
+                              q0.detach().contiguous(), w0.detach().contiguous()), 0.0, foreign)
             tips = torch.empty((len(batch.n), int(n_steps), 3), dtype=torch.float32, device=x0.device)
             batch.adjoint_forward(int(n_steps), int(ckpt_every), tips)
-            if batch._foreign_stream(x0.device):   # else the tips are ready in stream order
+            if foreign:   # else the tips are ready in stream order
                 torch.cuda.synchronize(x0.device)
             ctx.batch = batch
             ctx.rollout = batch.rollout   # a later forward on the handle makes backward refuse
@@ -517,7 +516,8 @@ def rollout_function():
                        x=torch.empty(3 * b.n_points, device=dev), v=torch.empty(3 * b.n_points, device=dev),
                        q=torch.empty(4 * b.n_frames, device=dev), w=torch.empty(3 * b.n_frames, device=dev))
             grad_tips = grad_tips.contiguous().float()
-            b._await_current(dev)
+            if b._foreign_stream(dev):
+                torch.cuda.current_stream(dev).synchronize()
             # (waits for the handle's stream before it returns)
             b.adjoint_backward(grad_tips, out, rollout=ctx.rollout)
             return (None, out["bend"], out["twist"], out["x"], out["v"], out["q"], out["w"], None, None)
