@@ -240,8 +240,8 @@ rod_status rod_set_bindings(rod_ctx* ctx, int32_t n_pairs, const int32_t* pairs,
  * must be inextensible with equal dt and n_constraint_iters, at most 512 elements each, and
  * a point may have at most 8 contacts (more: rod_sync reports ROD_E_UNSUPPORTED).  The first
  * call with contact allocates 48 bytes per element of the handle for per-point candidate lists
- * (pairs within contact distance + half the largest radius of the set), which the kernel keeps
- * between launches and rebuilds only when a point has moved far enough to need it; the
+ * (pairs within contact distance + a margin of at most half the largest radius of the set), which
+ * the kernel keeps between launches and rebuilds only when a point has moved far enough to need it; the
  * contacts found are those of a check of all point pairs.  n_sets = 0 removes all contact
  * sets.  Errors: INVALID, UNSUPPORTED, NOMEM, DEVICE. */
 rod_status rod_set_contact(rod_ctx* ctx, int32_t n_sets, const int32_t* sets, double mu);

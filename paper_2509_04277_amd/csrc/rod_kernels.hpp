@@ -7,8 +7,8 @@
 // of N elements needs exactly N slots.
 //
 // Neighbour data moves between lanes of a wavefront with DPP whole-wave shifts (wave_shr:1,
-// wave_shl:1), and between wavefronts through a double-buffered LDS mailbox with one
-// s_barrier per exchange.  One time step needs, in order (Sec. 2.1, Fig. 5 of the paper):
+// wave_shl:1), and between wavefronts through an LDS mailbox (a section per kind of exchange) with
+// one s_barrier per exchange.  One time step needs, in order (Sec. 2.1, Fig. 5 of the paper):
 //   A  exchange x of the left point and q of the right frame,
 //   F  segment forces (stretch eq. (2), penalty eq. (8)), joint torques (bend/twist eq. (3)
 //      with the Darboux vector of eqs. (5)-(6)),
@@ -163,7 +163,9 @@ __device__ __forceinline__ float rsq(float x) { return __builtin_amdgcn_rsqf(x);
 
 // a / b with rb = 1 / b (rounded to nearest): the product refined twice by the remainder.  The
 // second refinement of a quotient that is already faithful rounds as the division does
-// (Markstein): the same bits in five dependent instructions instead of a dozen.
+// (Markstein): the same bits in five dependent instructions instead of a dozen.  This needs
+// remainders that do not underflow, |a| above 2^-102 (and normal b, rb and quotient): here a is a
+// separation [m] or a speed, and an ulp of a smaller one's quotient is lost in any velocity.
 __device__ __forceinline__ float div_by(float a, float b, float rb) {
   const float q = a * rb;
   const float q1 = __builtin_fmaf(__builtin_fmaf(-q, b, a), rb, q);

@@ -825,10 +825,10 @@ bool spread_now(const rod_ctx* c) { return spread_planned(c) && !captures(c); }
 
 // Chunked long rods: one ordinary launch of ks steps.  The chunks wait on their neighbours, so
 // all workgroups of the grid must be resident together: the grid fits the device (checked when
-// the chunks are set up), and every chunked run of the process is ordered after the previous
-// one on the same device (LongGate), so two such grids never hold the compute units against
-// each other.  A workgroup whose neighbour still does not arrive gives up after a bounded wait
-// (status 4) instead of hanging.
+// the chunks are set up), and chunked runs of the process that do not fit together are ordered one
+// after the other (LongGate), so no two such grids hold the compute units against each other.  A
+// workgroup whose neighbour still does not arrive gives up after a bounded wait (status 4) instead
+// of hanging.
 rod_status launch_long(rod_ctx* c, const rod_ctx::LongSet& l, StateArrays sa, int ks, long long done,
                        hipStream_t stream) {
   if (!l.n_chunks) return ROD_OK;
