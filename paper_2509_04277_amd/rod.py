@@ -194,6 +194,7 @@ class RodBatch:
         self.n = [int(s.n) for s in specs]
         self.n_points = sum(n + 1 for n in self.n)
         self.n_frames = sum(self.n)
+        self._sizes = (3 * self.n_points, 3 * self.n_points, 4 * self.n_frames, 3 * self.n_frames)
         arr = (rod_params * len(specs))()
         self._keep = []
         for i, s in enumerate(specs):
@@ -250,8 +251,7 @@ class RodBatch:
         on_device = ptrs[0][1]
         if any(d != on_device for _, d in ptrs):
             raise ValueError("all state arrays must be on the same side")
-        sizes = (3 * self.n_points, 3 * self.n_points, 4 * self.n_frames, 3 * self.n_frames)
-        for a, s in zip(arrays, sizes):
+        for a, s in zip(arrays, self._sizes):
             if (a.size if isinstance(a, np.ndarray) else a.numel()) != s:
                 raise ValueError("state array of %d values expected" % s)
         # The call may return with its reads of device arrays queued on the handle's stream if that
