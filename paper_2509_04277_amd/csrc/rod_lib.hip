@@ -807,12 +807,13 @@ rod_status spread_rods(rod_ctx* c) {
   return ROD_OK;
 }
 
-// Whether the handle's stream may be capturing (also where the runtime does not tell).
-bool captures(const rod_ctx* c) {
+// Whether the handle's stream is capturing; if_unknown where the runtime does not tell (the null
+// stream while another one captures).
+bool captures(const rod_ctx* c, bool if_unknown) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(c->stream, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
   (void)hipGetLastError();
-  return true;
+  return if_unknown;
 }
 
 // Whether steps run on c->spread: nothing set that its kernel does not do, and no stream capture (a
@@ -821,7 +822,7 @@ bool spread_planned(const rod_ctx* c) {
   return c->spread.n_chunks && c->own_shapes && !c->lng.n_chunks && c->groups.empty() &&
          !c->n_haptic && !c->env_nodes;
 }
-bool spread_now(const rod_ctx* c) { return spread_planned(c) && !captures(c); }
+bool spread_now(const rod_ctx* c) { return spread_planned(c) && !captures(c, true); }
 
 // Chunked long rods: one ordinary launch of ks steps.  The chunks wait on their neighbours, so
 // all workgroups of the grid must be resident together: the grid fits the device (checked when
@@ -893,7 +894,7 @@ rod_status step_long(rod_ctx* c, const rod_ctx::LongSet& l, int n_steps, int spl
     return ROD_OK;
   };
   // chunks that wait for nothing need no company
-  if (!l.coupled || captures(c)) return run();
+  if (!l.coupled || captures(c, false)) return run();
   const int dev = c->device;
   if (dev < 0 || dev >= kMaxDevices) return fail(c, ROD_E_DEVICE, "device index out of range");
   LongGate& g = long_gate();

@@ -37,6 +37,7 @@ std::vector<std::pair<std::string, double>> costs;
 int waits, syncs, broken_captures;
 long long fail_malloc = -1;   // allocations until one fails
 bool strict;                  // another thread captures in the global mode
+bool implicit;                // the null stream's capture status is not to be had
 hipStreamCaptureMode mode = hipStreamCaptureModeGlobal;
 double now_us;
 hipError_t last = hipSuccess;
@@ -141,6 +142,7 @@ hipError_t hipStreamSynchronize(hipStream_t s) {
   return hipSuccess;
 }
 hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* st) {
+  if (implicit && !s) return ret(hipErrorStreamCaptureImplicit);
   *st = capturing.count(s) ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
   return hipSuccess;
 }
@@ -192,11 +194,12 @@ const char* hipGetErrorString(hipError_t) { return "error of the test's runtime"
 void stub_reset() {
   held.clear(), capturing.clear(), launches.clear(), costs.clear();
   waits = syncs = broken_captures = 0;
-  fail_malloc = -1, strict = false, mode = hipStreamCaptureModeGlobal, now_us = 0.0, last = hipSuccess;
+  fail_malloc = -1, strict = implicit = false, mode = hipStreamCaptureModeGlobal, now_us = 0.0, last = hipSuccess;
 }
 void stub_hold(hipStream_t s, int on) { on ? (void)held.insert(s) : (void)held.erase(s); }
 void stub_capture(hipStream_t s, int on) { on ? (void)capturing.insert(s) : (void)capturing.erase(s); }
 void stub_strict(int on) { strict = on; }
+void stub_implicit(int on) { implicit = on; }
 void stub_fail_malloc(long long after) { fail_malloc = after; }
 void stub_cost(const char* part, double us) { costs.push_back({part, us}); }
 int stub_waits() { return waits; }

@@ -261,3 +261,17 @@ def test_per_thread_streams_are_not_one_stream(stub):
     assert stub.lib.stub_waits() == 0
     b.step(10, 10)
     assert stub.lib.stub_waits() == 1
+
+
+def test_the_null_stream_beside_a_capture_keeps_the_order(stub):
+    """The runtime does not tell the null stream's capture status while another stream captures:
+    long rods are ordered as ever, mid rods step in one workgroup each."""
+    a, b, c = _handle(60000, 0x2000), _handle(60000, 0), _handle(700, 0)
+    a.step(10, 10)
+    stub.lib.stub_hold(0x2000, 1)
+    stub.lib.stub_implicit(1)
+    b.step(10, 10)
+    assert stub.lib.stub_waits() == 1
+    c.step(10, 10)
+    assert c.chunks[0] > 0 == c.chunks[1]
+    stub.lib.stub_implicit(0)
