@@ -904,21 +904,31 @@ rod_status step_long(rod_ctx* c, const rod_ctx::LongSet& l, int n_steps, int spl
   auto same = [&](const LongGate::Run& o) {
     return o.stream == c->stream && (o.stream != hipStreamPerThread || o.done == c->ev_long);
   };
-  for (size_t i = runs.size(); i-- > 0;) {   // finished runs of other streams leave
-    if (same(runs[i]) || !event_passed(runs[i].done)) continue;
-    runs[i] = runs.back();
-    runs.pop_back();
-  }
   LongGate::Run* mine = nullptr;
   int others = 0;
-  for (LongGate::Run& o : runs) {
-    if (same(o)) mine = &o;
-    else others += o.chunks;
+  auto count = [&]() {
+    mine = nullptr;
+    others = 0;
+    for (LongGate::Run& o : runs) {
+      if (same(o)) mine = &o;
+      else others += o.chunks;
+    }
+  };
+  const int room = &l == &c->spread ? spread_room(c) : c->cus;
+  count();
+  if (others + l.n_chunks > room) {   // finished runs leave (asked only here: 0.5 us of host time each)
+    for (size_t i = runs.size(); i-- > 0;) {
+      if (same(runs[i]) || !event_passed(runs[i].done)) continue;
+      runs[i] = runs.back();
+      runs.pop_back();
+    }
+    count();
   }
-  if (&l == &c->spread && others + l.n_chunks > spread_room(c)) return ROD_OK;
-  if (others + l.n_chunks > c->cus)
+  if (others + l.n_chunks > room) {
+    if (&l == &c->spread) return ROD_OK;
     for (const LongGate::Run& o : runs)
       if (!same(o)) HIP_TRY(c, hipStreamWaitEvent(c->stream, o.done, 0));
+  }
   // (an earlier, larger run of this stream that is over counts no more)
   if (mine && mine->chunks > l.n_chunks && event_passed(mine->done)) mine->chunks = 0;
   const rod_status st = run();

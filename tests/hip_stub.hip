@@ -34,7 +34,7 @@ std::map<uintptr_t, size_t> blocks;   // allocations
 std::set<hipStream_t> held, capturing;
 std::vector<Launch> launches;
 std::vector<std::pair<std::string, double>> costs;
-int waits, syncs, broken_captures;
+int waits, syncs, queries, broken_captures;
 long long fail_malloc = -1;   // allocations until one fails
 bool strict;                  // another thread captures in the global mode
 bool implicit;                // the null stream's capture status is not to be had
@@ -168,6 +168,7 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
 }
 hipError_t hipEventQuery(hipEvent_t e) {
   const Event& ev = *(Event*)e;
+  ++queries;
   if (hipError_t r = unsafe_call()) return r;
   if (ev.captured) return ret(hipErrorCapturedEvent);
   return ev.recorded && held.count(ev.stream) ? ret(hipErrorNotReady) : hipSuccess;
@@ -193,7 +194,7 @@ const char* hipGetErrorString(hipError_t) { return "error of the test's runtime"
 // ---- what the tests set and read
 void stub_reset() {
   held.clear(), capturing.clear(), launches.clear(), costs.clear();
-  waits = syncs = broken_captures = 0;
+  waits = syncs = queries = broken_captures = 0;
   fail_malloc = -1, strict = implicit = false, mode = hipStreamCaptureModeGlobal, now_us = 0.0, last = hipSuccess;
 }
 void stub_hold(hipStream_t s, int on) { on ? (void)held.insert(s) : (void)held.erase(s); }
@@ -204,6 +205,7 @@ void stub_fail_malloc(long long after) { fail_malloc = after; }
 void stub_cost(const char* part, double us) { costs.push_back({part, us}); }
 int stub_waits() { return waits; }
 int stub_syncs() { return syncs; }
+int stub_queries() { return queries; }
 int stub_broken_captures() { return broken_captures; }
 int stub_allocations() { return (int)blocks.size(); }
 int stub_launches() { return (int)launches.size(); }

@@ -105,12 +105,13 @@ def test_captured_long_rods_do_not_pass_the_gate(stub):
 
 def test_steps_beside_a_capture_of_another_thread(stub):
     """Asking whether another handle's run is done would end a capture in the global mode."""
-    a, b = _handle(2048, 0x1000), _handle(2048, 0x2000)
-    a.step(10, 10)
+    hs = [_handle(2048, 0x1000 * (1 + i)) for i in range(10)]   # (room runs short: it asks)
+    for h in hs[:-1]:
+        h.step(10, 10)
     stub.lib.stub_strict(1)
-    b.step(10, 10)
+    hs[-1].step(10, 10)
     stub.lib.stub_strict(0)
-    assert stub.lib.stub_broken_captures() == 0
+    assert stub.lib.stub_queries() > 0 and stub.lib.stub_broken_captures() == 0
 
 
 def test_spread_rods_do_not_wait_for_other_handles(stub):
@@ -275,3 +276,16 @@ def test_the_null_stream_beside_a_capture_keeps_the_order(stub):
     c.step(10, 10)
     assert c.chunks[0] > 0 == c.chunks[1]
     stub.lib.stub_implicit(0)
+
+
+def test_runs_of_other_streams_are_asked_for_only_where_room_is_short(stub):
+    """What a step of a handle costs does not grow with the handles there are."""
+    hs = [_handle(512, 0x1000 * (1 + i)) for i in range(40)]
+    fit = 128 // hs[0].chunks[0]
+    assert fit < len(hs)
+    for i, h in enumerate(hs):
+        h.step(10, 10)
+        if i < fit:
+            assert stub.lib.stub_queries() == 0
+    assert stub.lib.stub_queries() > 0
+    assert all(h.chunks[1] for h in hs)   # the earlier ones were over
